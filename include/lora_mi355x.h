@@ -234,11 +234,10 @@ size_t lora_linear_workspace_bytes(int64_t T, int32_t K, int32_t N, int32_t r_ma
 
 /* The workspace size that lets every batch take its fastest path: the size
  * above plus room for the adapter term in fp32 ([T, N]; bf16 batches of any
- * size, fp32 ones of more than 128 rows).  Batches of many small segments,
- * and decode-sized batches with much adapter work, then compute that term
- * in a weight-streaming kernel of its own and the GEMM (or the decode path's
- * reduction) adds it before the single rounding of Y; with a smaller
- * workspace the term is computed inside the GEMM / the reduction (same
+ * size, fp32 ones of more than 128 rows).  Batches of many small segments
+ * then compute that term in a weight-streaming kernel of its own and the GEMM
+ * adds it before the single rounding of Y; with a smaller
+ * workspace the term is computed inside the GEMM (same
  * result within the rounding of the intermediate V and fp32 summation order).  For batches of 129 to
  * 1024 rows whose output tiles would leave most of the chip idle (and larger
  * ones with K >= 10240 into few columns) it also has
@@ -263,9 +262,8 @@ int lora_shrink(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *
  * X) taken from the workspace as lora_shrink() left them for the same plan,
  * desc->X and K (decode-sized bf16 batches: sums the partial sums lora_shrink()
  * left, adds V B_a in fp32 -- V never rounded -- and stores Y; with much
- * adapter work and a workspace of the preferred size V is reduced and rounded
- * to bf16 by a launch of its own and the term comes from the weight-streaming
- * kernel below).  Otherwise two forms, same result up
+ * adapter work V is rounded to bf16 and the launch streams every used B_a
+ * once, work unit by work unit).  Otherwise two forms, same result up
  * to fp32 summation order: the expand
  * as extra K-steps of the GEMM's own MFMA loop (always, with a workspace of the
  * minimal size; and for segments of 64 rows and more up to rank 64), or -- with
@@ -305,8 +303,8 @@ int lora_linear_static(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear
  * lora_linear compute (same formula per projection; fp32 summation order may
  * differ, as between tile shapes); every kernel runs as one launch whose grid
  * holds the work of all projections (decode-sized batches: unless one of the
- * projections has much adapter work or takes the tiled path -- then projection
- * by projection).
+ * projections takes the tiled path -- then projection by projection; those
+ * with much adapter work share a second launch of their own).
  * Errors: those of lora_linear for any desc; INVALID_ARG also for n out of
  * range, descs that differ in X / ldx / K / dtype, or two descs with the same Y
  * or workspace. */

@@ -11,9 +11,9 @@
 //   2. decode_reduce_kernel: one workgroup per 16 output columns sums the slices' partial tiles in slice order
 //      (fixed order: reproducible), gathers every row's V from the partial tiles of its adapter's rank block,
 //      scales it by s_a, adds V B_a in fp32 (V is never rounded here) and stores Y once.
-//   With much adapter work (many high-rank adapters in the batch) two launches go in between: decode_v_kernel
-//   reduces V once (rounded to bf16 like the shrink kernel's V), the expand kernel turns it into the fp32 adapter
-//   term segment by segment, and decode_reduce_kernel only adds that term.
+//   With much adapter work (many high-rank adapters in the batch) the second launch is decode_finish_kernel instead:
+//   one workgroup per work unit of the plan and 512 output columns, V reduced for the unit's rows (rounded to bf16 like
+//   the shrink kernel's V), V B_a on the matrix cores, the partial tiles added, Y stored.
 //
 // Same contraction as the tiled path:  Y[t, n] = sum_k X[t, k] W0[n, k] + s_a sum_j (sum_k X[t, k] A_a[j, k]) B_a[n, j].
 //
@@ -102,6 +102,12 @@ __global__ __launch_bounds__(MAXW * 64) void decode_stream_kernel(DecodeArgs p0)
         for (int i = 0; i < 2; ++i)
             if (blk * 2 + i < nrec) rec[i] = reinterpret_cast<const int4 *>(p.plan.ext_rec)[blk * 2 + i];
         if (lane < p.n_adapters) a_guess = p.A[lane];
+    }
+    int row_ad[TBLK];  // extension blocks: the adapter of this lane's tokens (-2: no such row)
+#pragma unroll
+    for (int tb = 0; tb < TBLK; ++tb) {
+        row_ad[tb] = -2;
+        if (is_ext && tb * 16 + li < p.T) row_ad[tb] = p.plan.row_adapter[tb * 16 + li];
     }
 
     // ---- the X slice: requested first (L2), all threads, whole rows per wave instruction ----
@@ -198,10 +204,19 @@ __global__ __launch_bounds__(MAXW * 64) void decode_stream_kernel(DecodeArgs p0)
         }
     }
     LORA_TS(p.trace, 3);  // stages consumed (MFMAs may still run)
-    // acc[tb][e] = D[weight row blk * 16 + lg * 4 + e][token tb * 16 + li]: one contiguous KiB per 16-row token block
-    float4 *P4 = reinterpret_cast<float4 *>(p.P) + ((int64_t)(blk * p.ks + slice) * TBLK) * 64 + lane;
+    // acc[tb][e] = D[weight row blk * 16 + lg * 4 + e][token tb * 16 + li]: one contiguous KiB per 16-row token block, in it
+    // 64 bytes (the block's 16 weight rows) per token.  Of an extension block only the tokens of the rows' own adapter are
+    // ever read back, so only those are stored (64 adapters of rank 128 for 64 tokens: 21 MB of partial tiles less).
+    float4 *P4 = reinterpret_cast<float4 *>(p.P) + ((int64_t)(blk * p.ks + slice) * TBLK) * 64 + li * 4 + lg;
+    if (is_ext) {
+        const int own = lg < 2 ? rec[0].x : rec[1].x;  // adapter of this lane's weight rows (records of 8 ranks)
 #pragma unroll
-    for (int tb = 0; tb < TBLK; ++tb) P4[tb * 64] = make_float4(acc[tb][0], acc[tb][1], acc[tb][2], acc[tb][3]);
+        for (int tb = 0; tb < TBLK; ++tb)
+            if (row_ad[tb] == own) P4[tb * 64] = make_float4(acc[tb][0], acc[tb][1], acc[tb][2], acc[tb][3]);
+    } else {
+#pragma unroll
+        for (int tb = 0; tb < TBLK; ++tb) P4[tb * 64] = make_float4(acc[tb][0], acc[tb][1], acc[tb][2], acc[tb][3]);
+    }
     LORA_TS(p.trace, 4);
 }
 
@@ -233,9 +248,6 @@ __global__ __launch_bounds__(TBLK * 64) void decode_reduce_kernel(DecodeArgs p0)
     const int status = p.plan.scalars[kScStatus];
     const int a0 = has ? p.plan.row_adapter[t] : -1;
     const int rx0 = has ? p.plan.row_ext[t] : 0;
-    const bool hasd = tv && p.D != nullptr;
-    const int a0d = hasd ? p.plan.row_adapter[t] : -1;
-    const int rx0d = hasd ? p.plan.row_ext[t] : 0;
     const bool gl = p.B != nullptr && lane < p.n_adapters;  // entry `lane` of the two tables, in the same round trip
     const void *b_guess = gl ? p.B[lane] : nullptr;
     const float s_guess = gl ? p.scale[lane] : 0.f;
@@ -251,7 +263,7 @@ __global__ __launch_bounds__(TBLK * 64) void decode_reduce_kernel(DecodeArgs p0)
     if (a < 0 || r <= 0) Bp = nullptr;
     const float4 *P4 = reinterpret_cast<const float4 *>(p.P);
     const int64_t sstride = (int64_t)TBLK * 64;
-    const float4 *pb = P4 + ((int64_t)(p.nbe_cap + cb) * p.ks * TBLK + tb) * 64 + lane;
+    const float4 *pb = P4 + ((int64_t)(p.nbe_cap + cb) * p.ks * TBLK + tb) * 64 + li * 4 + lg;
     float4 pq[8];
 #pragma unroll
     for (int s = 0; s < 8; ++s) pq[s] = pb[min(s, p.ks - 1) * sstride];
@@ -278,7 +290,7 @@ __global__ __launch_bounds__(TBLK * 64) void decode_reduce_kernel(DecodeArgs p0)
 #pragma unroll
             for (int i = 0; i < RQ; ++i) {
                 const int e = e0 + min(j0 + 4 * (lg + 4 * i), r - 4);
-                pv[i] = P4 + ((int64_t)(e >> 4) * p.ks * TBLK + tb) * 64 + ((e & 15) >> 2) * 16 + li;
+                pv[i] = P4 + ((int64_t)(e >> 4) * p.ks * TBLK + tb) * 64 + li * 4 + ((e & 15) >> 2);
                 q[i] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
             for (int s0 = 0; s0 < p.ks; s0 += 8) {
@@ -344,13 +356,6 @@ __global__ __launch_bounds__(TBLK * 64) void decode_reduce_kernel(DecodeArgs p0)
 
     LORA_TS(p.trace, 2);  // base partial sums added
     if (!tv) return;
-    if (p.D != nullptr && a0d >= 0 && row_ext_rank(rx0d) > 0) {  // the adapter term, computed by the expand kernel
-        const float4 d = *reinterpret_cast<const float4 *>(p.D + (int64_t)t * p.ldd + min(n, (int)p.ldd - 4));
-        acc[0] += d.x;
-        acc[1] += d.y;
-        acc[2] += d.z;
-        acc[3] += d.w;
-    }
     E *yrow = static_cast<E *>(p.Y) + (int64_t)t * p.ldy;
     if (n + 3 < p.N) {
         store4(yrow + n, acc[0], acc[1], acc[2], acc[3]);
@@ -362,45 +367,203 @@ __global__ __launch_bounds__(TBLK * 64) void decode_reduce_kernel(DecodeArgs p0)
     LORA_TS(p.trace, 3);
 }
 
-// V[t, j .. j + 3] = scale_a * sum over the K slices (in order) of the extension rows' partial tiles, rounded to E: one
-// thread per row and quad of ranks.  For batches with much adapter work, whose term the expand kernel then computes from
-// V segment by segment instead of every workgroup of the reduction gathering V B_a row by row.
-template <int TBLK>
-__global__ __launch_bounds__(256) void decode_v_kernel(DecodeArgs p) {
+constexpr int kFinWaves = 8;
+constexpr int kFinBlocks = 4;                            // 16-column blocks per wave
+constexpr int kFinCols = kFinWaves * kFinBlocks * 16;    // output columns per workgroup
+constexpr int kFinTile = kFinCols + 4;                   // floats per row of the staged adapter term (4 of padding)
+constexpr int kFinRows = kShrinkRowsSmall;               // most rows of a work unit
+
+// Second launch for batches with much adapter work.  The reduction above gathers B_a row by row (T x r x N elements,
+// 16 bytes at a time) and every one of its workgroups re-reduces V; here a workgroup = one work unit of the plan (at
+// most 16 rows of one adapter) x 512 output columns: V of the unit's rows from their extension partial tiles (slices in
+// order, scaled, rounded to bf16 as the shrink kernel's V is), V B_a on the matrix cores with B_a streamed once, then
+// the base product's partial tiles of the same rows and columns in slice order, and Y is stored.  Rows without an
+// adapter come in units of their own behind the adapters'.  Everything after the streaming launch is this one launch:
+// as V, adapter term (fp32 through memory) and sum in a launch each, 64 rows on 64 adapters of rank 128 at
+// 5120 -> 13824 took 75.8 us, here 60.5.
+// Bound by the stream of B_a behind a chain of four dependent reads (unit -> rows, pointer -> B_a, partial tiles), so
+// two workgroups share a CU (128 registers) and B_a is requested before everything that takes longer to address.
+template <int TBLK, int S>
+__device__ __forceinline__ void finish_unit(const DecodeArgs &p, const __bf16 *Ba, float sc, int r, int slot0, int nrows, int n00,
+                                            chunk_t *vs, float *tile) {
     typedef __bf16 E;
-    if (p.plan.scalars[kScStatus] != 0) return;
-    const int quads = p.r_max >> 2;
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long)p.T * quads) return;
-    const int t = (int)(idx / quads), j = (int)(idx % quads) * 4;
-    const int a = p.plan.row_adapter[t];
-    const int rx = p.plan.row_ext[t];
-    if (a < 0 || j >= row_ext_rank(rx)) return;
-    const float sc = p.scale[a];
-    const int e = row_ext_offset(rx) + j;
-    const float4 *src = reinterpret_cast<const float4 *>(p.P) + ((int64_t)(e >> 4) * p.ks * TBLK + (t >> 4)) * 64 + ((e & 15) >> 2) * 16 + (t & 15);
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s0 = 0; s0 < p.ks; s0 += 8) {
-        float4 g[8];
+    constexpr int CE = 8;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, lg = lane >> 4;
+    const float4 *P4 = reinterpret_cast<const float4 *>(p.P);
+    const int64_t sstride = (int64_t)TBLK * 64;
+    const int rchunks = r / CE;
+    const int vstride = rchunks + 1;
+
+    auto local_n = [&](int b) { return (wave * kFinBlocks + b) * 16; };
+    chunk_t bq[kFinBlocks][S];
+    auto load_b = [&](int c0) {  // chunks c0 .. c0 + 4 S - 1 of the rank (past it: chunk 0, which meets a zero of V)
 #pragma unroll
-        for (int s = 0; s < 8; ++s) g[s] = src[(int64_t)min(s0 + s, p.ks - 1) * TBLK * 64];
+        for (int b = 0; b < kFinBlocks; ++b) {
+            const E *brow = Ba + (int64_t)min(n00 + local_n(b) + li, p.N - 1) * r;  // columns past N: never stored
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const float m = s0 + s < p.ks ? 1.f : 0.f;
-            v.x += m * g[s].x;
-            v.y += m * g[s].y;
-            v.z += m * g[s].z;
-            v.w += m * g[s].w;
+            for (int st = 0; st < S; ++st) {
+                const int c = c0 + (st >> 1) * 8 + 2 * lg + (st & 1);
+                bq[b][st] = load_chunk(brow + (c < rchunks ? c : 0) * CE);
+            }
+        }
+    };
+    if (r > 0) load_b(0);
+
+    // the rows: lane i of every 16 keeps row i (clamped)
+    const int my_t = p.plan.perm[slot0 + min(li, nrows - 1)];
+    if (r > 0) {
+        const int e0 = row_ext_offset(p.plan.row_ext[__builtin_amdgcn_readfirstlane(my_t)]);  // (one adapter: the same for all)
+        const int quads = r >> 2;
+        for (int q = tid; q < nrows * quads; q += kFinWaves * 64) {
+            const int i = q / quads, j = (q - i * quads) * 4;
+            const int t = p.plan.perm[slot0 + i], e = e0 + j;
+            const float4 *src = P4 + ((int64_t)(e >> 4) * p.ks * TBLK + (t >> 4)) * 64 + (t & 15) * 4 + ((e & 15) >> 2);
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int s0 = 0; s0 < p.ks; s0 += 8) {
+                float4 g[8];
+#pragma unroll
+                for (int s = 0; s < 8; ++s) g[s] = src[min(s0 + s, p.ks - 1) * sstride];
+#pragma unroll
+                for (int s = 0; s < 8; ++s) {
+                    const float m = s0 + s < p.ks ? 1.f : 0.f;
+                    v.x += m * g[s].x;
+                    v.y += m * g[s].y;
+                    v.z += m * g[s].z;
+                    v.w += m * g[s].w;
+                }
+            }
+            store4(reinterpret_cast<E *>(vs + i * vstride) + j, v.x * sc, v.y * sc, v.z * sc, v.w * sc);
+        }
+        lds_barrier();  // (LDS only: B_a stays in flight)
+        f32x4_t acc[kFinBlocks];
+#pragma unroll
+        for (int b = 0; b < kFinBlocks; ++b) acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        const chunk_t *vrow = vs + min(li, nrows - 1) * vstride;
+        for (int c0 = 0; c0 < rchunks; c0 += 4 * S) {
+            if (c0 > 0) load_b(c0);
+            chunk_t vop[S];
+#pragma unroll
+            for (int st = 0; st < S; ++st) {
+                const int c = c0 + (st >> 1) * 8 + 2 * lg + (st & 1);
+                vop[st] = keep_if(c < rchunks, vrow[c < rchunks ? c : 0]);
+            }
+#pragma unroll
+            for (int b = 0; b < kFinBlocks; ++b)
+#pragma unroll
+                for (int st = 0; st < S; ++st) Elem<E>::mma16(acc[b], bq[b][st], vop[st]);
+        }
+        // acc[b][e] = adapter term of column local_n(b) + lg * 4 + e of row li
+        if (li < nrows) {
+#pragma unroll
+            for (int b = 0; b < kFinBlocks; ++b)
+                *reinterpret_cast<float4 *>(tile + li * kFinTile + local_n(b) + lg * 4) = make_float4(acc[b][0], acc[b][1], acc[b][2], acc[b][3]);
+        }
+        lds_barrier();
+    }
+    // ---- base product: one thread = 4 columns of a row, the slices' partial tiles in slice order ----
+    for (int q = tid; q < nrows * (kFinCols / 4); q += kFinWaves * 64) {
+        const int i = q / (kFinCols / 4), ln = (q - i * (kFinCols / 4)) * 4, n = n00 + ln;
+        if (n >= p.N) continue;
+        const int t = p.plan.perm[slot0 + i];
+        const float4 *src = P4 + ((int64_t)(p.nbe_cap + (n >> 4)) * p.ks * TBLK + (t >> 4)) * 64 + (t & 15) * 4 + ((n & 15) >> 2);
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int s0 = 0; s0 < p.ks; s0 += 8) {
+            float4 g[8];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) g[s] = src[min(s0 + s, p.ks - 1) * sstride];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                if (s0 + s < p.ks) {
+                    v.x += g[s].x;
+                    v.y += g[s].y;
+                    v.z += g[s].z;
+                    v.w += g[s].w;
+                }
+            }
+        }
+        if (r > 0) {
+            const float4 d = *reinterpret_cast<const float4 *>(tile + i * kFinTile + ln);
+            v.x += d.x;
+            v.y += d.y;
+            v.z += d.z;
+            v.w += d.w;
+        }
+        E *y = static_cast<E *>(p.Y) + (int64_t)t * p.ldy + n;
+        if (n + 3 < p.N) {
+            store4(y, v.x, v.y, v.z, v.w);
+        } else {
+            store1(y, v.x);
+            if (n + 1 < p.N) store1(y + 1, v.y);
+            if (n + 2 < p.N) store1(y + 2, v.z);
         }
     }
-    store4(static_cast<E *>(p.V) + (int64_t)t * p.r_max + j, v.x * sc, v.y * sc, v.z * sc, v.w * sc);
 }
 
 template <int TBLK>
-hipError_t launch_v_t(const DecodeArgs &a, hipStream_t stream, const KernelTimer *timer) {
-    const long threads = (long)a.T * (a.r_max >> 2);
-    if (threads <= 0) return hipSuccess;
-    return launch_kernel(decode_v_kernel<TBLK>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream, timer, a);
+__global__ __launch_bounds__(kFinWaves * 64, 4) void decode_finish_kernel(DecodeArgs p0, int units_cap, int bare_cap) {
+    typedef __bf16 E;
+    __shared__ __attribute__((aligned(16))) chunk_t vs[kFinRows * (kMaxRank / 8 + 1)];
+    __shared__ __attribute__((aligned(16))) float tile[kFinRows * kFinTile];
+    int bid = blockIdx.x;
+    DecodeArgs p = p0;
+    if (p0.n_sets > 0) {
+        int si = 0;
+        while (si + 1 < p0.n_sets && bid >= p0.set[si + 1].fb0) ++si;
+        bid -= p0.set[si].fb0;
+        p.B = p0.set[si].B;
+        p.scale = p0.set[si].scale;
+        p.Y = p0.set[si].Y;
+        p.ldy = p0.set[si].ldy;
+        p.P = p0.set[si].P;
+        p.N = p0.set[si].N;
+    }
+    const int cgs = (p.N + kFinCols - 1) / kFinCols;
+    const int u = bid / cgs, cg = bid - u * cgs;
+    if (p.plan.scalars[kScStatus] != 0) return;
+    int slot0, nrows, r = 0;
+    const E *Ba = nullptr;
+    float sc = 0.f;
+    if (u < units_cap) {
+        const int4 rec = reinterpret_cast<const int4 *>(p.plan.unit_rec)[u];
+        if (u >= p.plan.scalars[kScNUnits]) return;
+        slot0 = rec.z;
+        nrows = min(rec.w, kFinRows);
+        r = rec.y & 0xffff;
+        Ba = static_cast<const E *>(p.B[rec.x]);
+        sc = p.scale[rec.x];
+        if (Ba == nullptr) {  // slot emptied after the plan was built: flag it, the rows get the base product
+            if (threadIdx.x == 0) atomicMin(&p.plan.scalars[kScEvicted], kErrNotResident);
+            r = 0;
+        }
+    } else {  // rows without an adapter: the last segment, if it is theirs
+        const int n_seg = p.plan.scalars[kScNSeg];
+        if (n_seg <= 0 || p.plan.seg_adapter[n_seg - 1] >= 0) return;
+        slot0 = p.plan.seg_indptr[n_seg - 1] + (u - units_cap) * kFinRows;
+        nrows = min(kFinRows, p.T - slot0);
+    }
+    if (nrows <= 0) return;
+    if (r <= 64)
+        finish_unit<TBLK, 2>(p, Ba, sc, r, slot0, nrows, cg * kFinCols, vs, tile);
+    else
+        finish_unit<TBLK, 4>(p, Ba, sc, r, slot0, nrows, cg * kFinCols, vs, tile);
+}
+
+template <int TBLK>
+hipError_t launch_finish_t(const DecodeArgs &a0, int units_cap, hipStream_t stream, const KernelTimer *timer) {
+    DecodeArgs a = a0;
+    const int bare_cap = TBLK;  // (at most T rows without an adapter)
+    long grid = 0;
+    if (a.n_sets > 0) {
+        for (int i = 0; i < a.n_sets; ++i) {
+            a.set[i].fb0 = (int32_t)grid;
+            grid += (long)(units_cap + bare_cap) * ((a.set[i].N + kFinCols - 1) / kFinCols);
+        }
+    } else {
+        grid = (long)(units_cap + bare_cap) * ((a.N + kFinCols - 1) / kFinCols);
+    }
+    if (grid <= 0) return hipSuccess;
+    return launch_kernel(decode_finish_kernel<TBLK>, dim3((unsigned)grid), dim3(kFinWaves * 64), 0, stream, timer, a, units_cap, bare_cap);
 }
 
 template <int TBLK, int MAXW>
@@ -538,19 +701,23 @@ hipError_t launch_decode_reduce(const DecodeArgs &a, int tblk, hipStream_t strea
     }
 }
 
-hipError_t launch_decode_v(const DecodeArgs &a, int tblk, hipStream_t stream, const KernelTimer *timer) {
-    if (!decode_args_ok(a, tblk) || a.n_sets != 0 || a.V == nullptr || a.scale == nullptr || (a.r_max & 7) != 0) return hipErrorInvalidValue;
+// units_cap: upper bound of the plan's work units, which must be units of at most kShrinkRowsSmall rows.
+hipError_t launch_decode_finish(const DecodeArgs &a, int tblk, int units_cap, hipStream_t stream, const KernelTimer *timer) {
+    if (!decode_args_ok(a, tblk) || units_cap < 0 || a.r_max > kMaxRank) return hipErrorInvalidValue;
+    if (a.n_sets == 0 && (a.B == nullptr || a.scale == nullptr)) return hipErrorInvalidValue;
+    for (int i = 0; i < a.n_sets; ++i)
+        if (a.set[i].B == nullptr || a.set[i].scale == nullptr) return hipErrorInvalidValue;
     switch (tblk) {
         case 1:
-            return launch_v_t<1>(a, stream, timer);
+            return launch_finish_t<1>(a, units_cap, stream, timer);
         case 2:
-            return launch_v_t<2>(a, stream, timer);
+            return launch_finish_t<2>(a, units_cap, stream, timer);
         case 4:
-            return launch_v_t<4>(a, stream, timer);
+            return launch_finish_t<4>(a, units_cap, stream, timer);
         case 6:
-            return launch_v_t<6>(a, stream, timer);
+            return launch_finish_t<6>(a, units_cap, stream, timer);
         case 8:
-            return launch_v_t<8>(a, stream, timer);
+            return launch_finish_t<8>(a, units_cap, stream, timer);
         default:
             return hipErrorInvalidValue;
     }

@@ -227,7 +227,7 @@ struct DecodeSet {
     int32_t n_adapters;
     int32_t blk0;  // first block of weight rows (set by the launcher)
     int32_t cb0;   // first column block of the reduction's grid (set by the launcher)
-    int32_t pad_;
+    int32_t fb0;   // first workgroup of the finishing kernel's grid (set by the launcher)
 };
 
 // Decode-sized batches (bf16, at most kDecodeMaxRows rows): two launches, see decode_kernels.hip.
@@ -242,7 +242,7 @@ struct DecodeArgs {
     const float *scale;
     void *Y;
     int64_t ldy;
-    float *P;              // workspace: fp32 partial tiles, [nbe_cap + nbw][ks][tblk][64 lanes][4]
+    float *P;              // workspace: fp32 partial tiles, [nbe_cap + nbw][ks][tblk][16 tokens][16 weight rows]
     int32_t T, K, N;
     int32_t r_max;         // the plan's largest rank
     int32_t n_adapters;    // entries of the A / B / scale tables
@@ -253,19 +253,13 @@ struct DecodeArgs {
     long long *trace = nullptr;  // phase stamps (trace builds only)
     int32_t n_sets = 0;    // > 0: the projections of the launch (W .. P, N, nbw, n_adapters above are then unused)
     DecodeSet set[kMaxGemmSets];
-    // Adapter term through the expand kernel (batches with much adapter work; one projection): launch_decode_v reduces
-    // the extension rows' partial tiles to V ([T, r_max] of E, original row order, scaled), the expand kernel turns V
-    // into the fp32 term D, and the reduction adds D instead of computing V B_a itself (B null).
-    void *V = nullptr;
-    const float *D = nullptr;
-    int64_t ldd = 0;
 };
 constexpr int kDecodeMaxRows = 128;
 constexpr int kDecodeMinWaves = 8, kDecodeMaxWaves = 12;
 hipError_t init_decode_kernels();
 hipError_t launch_decode_stream(const DecodeArgs &a, int tblk, hipStream_t stream, const KernelTimer *timer);
 hipError_t launch_decode_reduce(const DecodeArgs &a, int tblk, hipStream_t stream, const KernelTimer *timer);
-hipError_t launch_decode_v(const DecodeArgs &a, int tblk, hipStream_t stream, const KernelTimer *timer);
+hipError_t launch_decode_finish(const DecodeArgs &a, int tblk, int units_cap, hipStream_t stream, const KernelTimer *timer);
 
 // Dynamic-LDS grants of every kernel instantiation, for the current device (context creation).
 hipError_t init_gemm_tile_kernels();

@@ -441,7 +441,7 @@ WorkspaceLayout workspace_layout(int64_t T, int32_t K, int32_t N, int32_t r_max,
     w.total = off < 256 ? 256 : off;
     w.ldd = align_up((size_t)N, 8);  // (the GEMM's epilogue reads whole 8-column pieces of a row)
     w.d_off = w.total;
-    // (also for decode-sized bf16 batches: the decode path hands batches with much adapter work to the expand kernel)
+    // (also for decode-sized bf16 batches, whose wide outputs may take the tiled path)
     w.d_bytes = (T > kDecodeMaxRows || (dtype == LORA_DTYPE_BF16 && T > 0)) ? (size_t)T * w.ldd * sizeof(float) : 0;
     w.sk_off = align_up(w.d_off + w.d_bytes, 256);
     const SplitK sk = choose_split_k(T, K, N, dtype);
@@ -512,13 +512,19 @@ bool has_adapters(const lora_plan_t *plan, const lora_linear_desc *d) {
     return d->tbl != nullptr && plan->n_adapters > 0 && plan->r_max > 0;
 }
 
-// Decode path, one projection: when the reduction's own expand -- every row gathers its adapter's B_a for the
-// workgroup's 16 columns, and every workgroup re-reduces V -- would move more than ~24 MB through 16-byte gathers
-// (T x r_max x N x 2 bytes: 8 MB at 64 rows of rank 16 and 4096 columns), V is reduced once by a launch of its own
-// and the expand kernel streams each used B_a once, segment by segment.  Measured per layer, 64 rows on 64 adapters
-// of rank 128: 4096 -> 4096 95 -> 59 us, 5120 -> 13824 306 -> 130 us.  Needs the workspace of the preferred size.
+// Upper bound of the plan's work units: sum over the adapter segments of ceil(rows / unit_rows).
+int64_t max_units_of(const lora_plan_t *plan) {
+    const int64_t segs = std::min<int64_t>(std::min<int64_t>(plan->n_adapters, plan->n_req), plan->T);
+    return plan->T / plan->unit_rows + segs;
+}
+
+// Decode path: when the reduction's own expand -- every row gathers its adapter's B_a for the workgroup's 16 columns,
+// and every workgroup re-reduces V -- would move more than ~24 MB through 16-byte gathers (T x r_max x N x 2 bytes:
+// 8 MB at 64 rows of rank 16 and 4096 columns), the second launch is the finishing kernel, which streams each used B_a
+// once, unit by unit.
 bool decode_adapters_heavy(const lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *d) {
     if (!has_adapters(plan, d)) return false;
+    if (plan->unit_rows > kShrinkRowsSmall) return false;  // (does not happen at decode sizes)
     if (ctx->opt_expand_split == 0) return false;
     if (ctx->opt_expand_split == 1) return true;
     return 2.0e-6 * (double)plan->T * (double)plan->r_max * (double)d->N > 24.0;
@@ -558,7 +564,7 @@ DecodeArgs decode_args(const lora_ctx *ctx, const lora_plan_t *plan, const lora_
         st.N = di->N;
         st.nbw = g.nbw;
         st.n_adapters = ad ? di->tbl->n_adapters : 0;
-        st.blk0 = st.cb0 = st.pad_ = 0;
+        st.blk0 = st.cb0 = st.fb0 = 0;
         a.nbe_cap = g.nbe_cap;
         a.ks = g.ks;
         nblk += (long)g.nbe_cap + g.nbw;
@@ -591,15 +597,36 @@ DecodeArgs decode_args(const lora_ctx *ctx, const lora_plan_t *plan, const lora_
     return a;
 }
 
+// The second launch of the decode path: sums the slices, adds V B_a, stores Y.  Projections with much adapter work go
+// through the finishing kernel, the others through the reduction: one launch of each at most.
+int do_decode_second(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *const *descs, int n, const DecodeArgs &a,
+                     const GemmChoice &c, hipStream_t stream) {
+    DecodeArgs part[2] = {a, a};  // [0] reduction, [1] finishing kernel
+    int cnt[2] = {0, 0};
+    for (int i = 0; i < n; ++i) {
+        const int k = decode_adapters_heavy(ctx, plan, descs[i]) ? 1 : 0;
+        part[k].set[cnt[k]++] = a.set[i];
+    }
+    for (int k = 0; k < 2; ++k) {
+        if (cnt[k] == 0) continue;
+        part[k].n_sets = n > 1 ? cnt[k] : 0;
+        KernelTimer timer;
+        const bool timed = next_timer(ctx, kProfGemm, &timer);
+        if (k == 0)
+            LORA_HIP(launch_decode_reduce(part[k], c.tblk, stream, timed ? &timer : nullptr));
+        else
+            LORA_HIP(launch_decode_finish(part[k], c.tblk, (int)max_units_of(plan), stream, timed ? &timer : nullptr));
+    }
+    return LORA_OK;
+}
+
 int do_decode(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *const *descs, int n, const GemmChoice &c,
               hipStream_t stream) {
     const DecodeArgs a = decode_args(ctx, plan, descs, n, c);
-    KernelTimer t1, t2;
+    KernelTimer t1;
     const bool timed1 = next_timer(ctx, kProfShrink, &t1);
     LORA_HIP(launch_decode_stream(a, c.tblk, stream, timed1 ? &t1 : nullptr));  // streams W0 and the used A_a against X
-    const bool timed2 = next_timer(ctx, kProfGemm, &t2);
-    LORA_HIP(launch_decode_reduce(a, c.tblk, stream, timed2 ? &t2 : nullptr));  // sums the slices, adds V B_a, stores Y
-    return LORA_OK;
+    return do_decode_second(ctx, plan, descs, n, a, c, stream);
 }
 
 // (multi: several projections of the same X that go through one launch)
@@ -642,9 +669,7 @@ int do_shrink(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *d,
         a.set[i].pad_ = 0;
     }
     // units <= sum over segments of ceil(rows / unit_rows) <= T / unit_rows + number of adapter segments
-    const int64_t seg_bound = plan->n_adapters < plan->n_req ? plan->n_adapters : plan->n_req;
-    const int64_t seg_bound2 = seg_bound < plan->T ? seg_bound : plan->T;
-    a.max_units = ad ? (int32_t)(plan->T / plan->unit_rows + seg_bound2) : 0;
+    a.max_units = ad ? (int32_t)max_units_of(plan) : 0;
     // With few units (decode-sized batches) a unit's ranks are dealt to several workgroups: every A_a
     // is streamed once either way, and it takes most of the chip to stream them at HBM speed.
     const int64_t wide_groups = (plan->r_max + kShrinkRanks - 1) / kShrinkRanks;
@@ -703,9 +728,7 @@ int prepare_set(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *
         e.ldd = (int64_t)w.ldd;
         e.r_max = plan->r_max;
         e.N = d->N;
-        const int64_t seg_bound = plan->n_adapters < plan->n_req ? plan->n_adapters : plan->n_req;
-        const int64_t seg_bound2 = seg_bound < plan->T ? seg_bound : plan->T;
-        e.max_units = (int32_t)(plan->T / plan->unit_rows + seg_bound2);  // as for the shrink grid
+        e.max_units = (int32_t)max_units_of(plan);  // as for the shrink grid
         e.unit_rows = plan->unit_rows;
         e.col_groups = 0;
         // The tiled GEMM keeps the long segments' term to itself (an extension stage per 64 ranks of each such segment
@@ -741,40 +764,11 @@ int prepare_set(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *
 
 int do_gemm(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *d, hipStream_t stream) {
     GemmChoice c = choose_gemm(ctx, plan->T, d->K, d->N, d->dtype);
+    if (c.variant == kGemmDecode)
+        return do_decode_second(ctx, plan, &d, 1, decode_args(ctx, plan, &d, 1, c), c, stream);
     KernelTimer timer, etimer;
     const bool timed = next_timer(ctx, kProfGemm, &timer);
     const WorkspaceLayout w = workspace_layout(plan->T, d->K, d->N, plan->r_max, d->dtype);
-    if (c.variant == kGemmDecode) {  // decode-sized: the second launch sums the slices, adds V B_a, stores Y
-        DecodeArgs a = decode_args(ctx, plan, &d, 1, c);
-        if (d->workspace_bytes >= w.total_preferred && w.d_bytes > 0 && decode_adapters_heavy(ctx, plan, d)) {
-            // much adapter work: V once, the expand kernel for the term, the reduction only adds it
-            unsigned char *ws = static_cast<unsigned char *>(d->workspace);
-            a.V = ws + w.v_off;
-            KernelTimer vt;
-            const bool vtimed = timed && next_timer(ctx, kProfShrink, &vt);
-            LORA_HIP(launch_decode_v(a, c.tblk, stream, vtimed ? &vt : nullptr));
-            ExpandArgs e;
-            e.plan = a.plan;
-            e.V = a.V;
-            e.B = d->tbl->B;
-            e.D = reinterpret_cast<float *>(ws + w.d_off);
-            e.ldd = (int64_t)w.ldd;
-            e.r_max = plan->r_max;
-            e.N = d->N;
-            const int64_t seg_bound = std::min<int64_t>(std::min<int64_t>(plan->n_adapters, plan->n_req), plan->T);
-            e.max_units = (int32_t)(plan->T / plan->unit_rows + seg_bound);
-            e.unit_rows = plan->unit_rows;
-            e.col_groups = 0;
-            e.skip_long = 0;
-            const bool etimed = timed && next_timer(ctx, kProfExpand, &etimer);
-            LORA_HIP(launch_expand(e, d->dtype, stream, etimed ? &etimer : nullptr));
-            a.B = nullptr;
-            a.D = e.D;
-            a.ldd = e.ldd;
-        }
-        LORA_HIP(launch_decode_reduce(a, c.tblk, stream, timed ? &timer : nullptr));
-        return LORA_OK;
-    }
     SplitK sk = choose_split_k(plan->T, d->K, d->N, d->dtype);
     if (ctx->opt_gemm_split_k == 0 || (ctx->opt_gemm_variant >= 0 && ctx->opt_gemm_variant != sk.variant) ||
         d->workspace_bytes < w.total_preferred || (has_adapters(plan, d) && w.d_bytes == 0))
@@ -852,12 +846,8 @@ int multi_kind(const lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_d
     for (int i = 0; i < n; ++i) ns[i] = descs[i]->N;
     *c = choose_gemm(ctx, plan->T, descs[0]->K, descs[0]->N, descs[0]->dtype);
     if (c->variant == kGemmDecode) {
-        // (much adapter work: each projection through its own launches and the expand kernel, see decode_adapters_heavy)
-        for (int i = 0; i < n; ++i) {
-            const WorkspaceLayout w = workspace_layout(plan->T, descs[i]->K, descs[i]->N, plan->r_max, descs[i]->dtype);
-            if (descs[i]->workspace_bytes >= w.total_preferred && decode_adapters_heavy(ctx, plan, descs[i])) return 0;
+        for (int i = 1; i < n; ++i)
             if (choose_gemm(ctx, plan->T, descs[i]->K, descs[i]->N, descs[i]->dtype).variant != kGemmDecode) return 0;
-        }
         return 2;
     }
     *c = choose_gemm_sets(ctx, plan->T, descs[0]->K, ns, n, descs[0]->dtype);
