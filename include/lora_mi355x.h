@@ -34,7 +34,7 @@
  *   - Run-to-run results are bitwise reproducible (no floating-point atomics).
  *   - Thread safety: a ctx may be shared by threads as long as calls that use
  *     the same plan_buf / workspace / Y are ordered by the caller; lora_plan()
- *     takes an internal lock for its pinned staging ring.
+ *     takes an internal lock for its pinned memory.
  */
 #ifndef LORA_MI355X_H
 #define LORA_MI355X_H
@@ -110,8 +110,8 @@ typedef struct lora_plan_t {
     int32_t n_req;
     int32_t n_adapters;
     int32_t r_max;          /* row stride of the intermediate V, >= every used rank         */
-    int32_t seg_cap;        /* capacity of the seg_* arrays                                 */
-    int32_t ext_cap;        /* capacity of ext_rec                                          */
+    int32_t seg_cap;        /* most segments: entries of the seg_* arrays (lora_plan: in use) */
+    int32_t ext_cap;        /* most records of ext_rec (lora_plan: in use)                  */
     int32_t magic;
     int32_t unit_rows;      /* most rows of a work unit: 64, or 16 in a plan of few rows and segments */
     const int32_t *perm;        /* device [T]        slot -> row index of X / Y             */
@@ -148,7 +148,7 @@ typedef struct lora_linear_desc {
 /* ---- context ----------------------------------------------------------- */
 
 /* Creates a context on device `device_ordinal` (host int).  It caches device
- * properties, owns a small pinned host staging ring used by lora_plan(), and
+ * properties, owns a little pinned host memory used by lora_plan(), and
  * does the per-device set-up of the kernels (dynamic-LDS grants; the address
  * of lora_linear_static()'s scratch on that device), so that no later call
  * has to: create contexts outside stream capture.  *out is set to NULL on
@@ -190,12 +190,13 @@ size_t lora_plan_bytes(int32_t n_req, int64_t T, int32_t n_adapters, int32_t r_m
 
 /* Builds the plan from HOST request arrays (the batcher is CPU code: section
  * 4.2, the batching scheduler forms per-function batches on the controller).
- * Validates as lora_plan_validate() before touching the GPU, copies the three
- * small arrays through the context's pinned ring (they may be freed on
- * return) and builds every T-sized array on the device, in plan_buf (DEVICE,
- * 256-byte aligned, >= lora_plan_bytes()).  Asynchronous on `stream`; may
- * block only when the pinned ring is full (4 plans in flight).  T == 0 is
- * valid.  Errors: as lora_plan_validate, plus WORKSPACE_TOO_SMALL, ALIGNMENT, HIP. */
+ * Validates as lora_plan_validate() before touching the GPU, hands what the
+ * arrays say to the device through the context's pinned memory (they may be
+ * freed on return; up to 2048 requests and 16384 rows: a sorted table that the
+ * kernel reads in place, else the arrays) and builds every T-sized array on the
+ * device, in plan_buf (DEVICE, 256-byte aligned, >= lora_plan_bytes()).
+ * Asynchronous on `stream`; may block only when the pinned memory is in use (16
+ * plans in flight; 4 larger ones).  T == 0 is valid.  Errors: as lora_plan_validate, plus WORKSPACE_TOO_SMALL, ALIGNMENT, HIP. */
 int lora_plan(lora_ctx *ctx, const int32_t *req_adapter, const int32_t *req_ntok, int32_t n_req,
               const int32_t *adapter_rank, int32_t n_adapters, int32_t r_max, int64_t T_expected,
               void *plan_buf, size_t plan_buf_bytes, lora_stream_t stream, lora_plan_t *out);

@@ -37,6 +37,28 @@ struct PlanBuildArgs {
     long long *trace = nullptr;  // phase stamps (trace builds only)
 };
 
+// What the host knows of a batch whose request arrays it holds, one int array in pinned memory: per request the first
+// row (n_req + 1 entries), the first slot and the segment; per segment the adapter (-1 = none), the first slot (+ 1
+// entry), the rank, and the prefix sums of ranks and of work units (+ 1 entry each).
+constexpr int kApplyReq = 2048;   // largest batch that takes this route: its table is read into one workgroup's LDS
+constexpr int kApplyRows = 16384; // (one workgroup writes every row; 1024 rows cost it ~0.5 us)
+constexpr int kPlanTableInts = (3 * kApplyReq + 1 + 5 * (kApplyReq + 1) + 3 + 3) & ~3;
+struct PlanTable {
+    const int32_t *data;  // 16-byte aligned, readable in whole 16-byte pieces
+    uint32_t *done;       // pinned host memory: receives `ticket` when the table has been read
+    uint32_t ticket;
+    int32_t n_req, n_seg, ext_total, n_units;
+    __host__ __device__ int tok() const { return 0; }
+    __host__ __device__ int dst() const { return n_req + 1; }
+    __host__ __device__ int rseg() const { return 2 * n_req + 1; }
+    __host__ __device__ int sad() const { return 3 * n_req + 1; }
+    __host__ __device__ int sip() const { return sad() + n_seg; }
+    __host__ __device__ int srk() const { return sip() + n_seg + 1; }
+    __host__ __device__ int sex() const { return srk() + n_seg; }
+    __host__ __device__ int sun() const { return sex() + n_seg + 1; }
+    __host__ __device__ int ints() const { return sun() + n_seg + 1; }
+};
+
 // Optional pair of events recorded tightly around one kernel (profiling mode): the elapsed time
 // between them is the kernel's own execution time, as a profiler reports it.
 struct KernelTimer {
@@ -71,6 +93,10 @@ inline hipError_t launch_kernel(F kernel, dim3 grid, dim3 block, size_t smem, hi
 // workgroup of the first kernel also fills the T-sized arrays.  `variant`: 0 = pick by size, 1 = never the
 // decode-sized (one lane per request) kernel.  timers: [0] segments, [1] fill.
 hipError_t launch_plan_build(const PlanBuildArgs &a, bool fuse_fill, int variant, hipStream_t stream, const KernelTimer *timers);
+
+// Writes the plan described by a table of the host's (one workgroup).
+hipError_t launch_plan_apply(const PlanBuildArgs &a, const PlanTable &t, hipStream_t stream, const KernelTimer *timer);
+hipError_t init_plan_kernels();
 
 constexpr int kMaxGemmSets = 4;
 // One projection of a launch that covers several projections of the same X (fused QKV, gate + up): the grid of the

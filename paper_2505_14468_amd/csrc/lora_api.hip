@@ -5,8 +5,11 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <mutex>
 #include <new>
+#include <thread>
+#include <vector>
 
 #include "../../include/lora_mi355x.h"
 #include "kernels.h"
@@ -45,6 +48,7 @@ static_assert(kProfKinds == LORA_PROFILE_KINDS, "profile kinds out of sync");
 
 constexpr int kRingSlots = 4;
 constexpr size_t kRingSlotInts = 2 * (size_t)LORA_MAX_REQUESTS + LORA_MAX_ADAPTERS;
+constexpr int kTableSlots = 16;  // plan tables in flight (a batch of a few hundred requests: ~10 KB, and a plan lasts as long as its layers)
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -59,7 +63,13 @@ struct lora_ctx {
     hipEvent_t ring_event[kRingSlots] = {};
     bool ring_used[kRingSlots] = {};
     int ring_next = 0;
-    std::mutex ring_mutex;
+    // pinned tables that plan_apply_kernel reads in place, and the words in which it reports having read them
+    int32_t *tables = nullptr;
+    uint32_t *table_done = nullptr;
+    uint32_t table_ticket[kTableSlots] = {};
+    int table_next = 0;
+    std::vector<int32_t> key_rows, key_seg;  // scratch of lora_plan()
+    std::mutex ring_mutex;  // guards everything above
     // tuning overrides (-1 = heuristic)
     int opt_gemm_variant = -1;
     int opt_decode_waves = -1;
@@ -214,9 +224,8 @@ int validate_batch(const int32_t *req_adapter, const int32_t *req_ntok, int32_t 
     return LORA_OK;
 }
 
-int build_plan(lora_ctx *ctx, const int32_t *req_adapter_dev, const int32_t *req_ntok_dev, const int32_t *rank_dev,
-               int32_t n_req, int32_t n_adapters, int32_t r_max, int64_t T, const PlanLayout &L, int32_t *base,
-               hipStream_t stream, lora_plan_t *out) {
+PlanBuildArgs plan_args(const lora_ctx *ctx, const int32_t *req_adapter_dev, const int32_t *req_ntok_dev, const int32_t *rank_dev,
+                        int32_t n_req, int32_t n_adapters, int32_t r_max, int64_t T, const PlanLayout &L, int32_t *base) {
     PlanBuildArgs a;
     a.req_adapter = req_adapter_dev;
     a.req_ntok = req_ntok_dev;
@@ -251,21 +260,16 @@ int build_plan(lora_ctx *ctx, const int32_t *req_adapter_dev, const int32_t *req
     a.unit_rec = base + L.unit_rec;
     a.ext_rec = base + L.ext_rec;
     a.scalars = base + L.scalars;
-    // One workgroup builds the whole plan (per-row arrays included) up to 4096 rows, up to 8192 for batches of at
-    // most 64 requests (the one-lane-per-request kernel leaves its workgroup more time for the rows); beyond that
-    // the per-row arrays are filled by a second, grid-wide kernel.
-    const int fused_rows = ctx->opt_plan_fused_rows >= 0 ? ctx->opt_plan_fused_rows : (n_req <= 64 ? 8192 : 4096);
-    const bool fuse = T <= fused_rows && L.ext_cap <= 8192;
-    KernelTimer timers[2];
-    const bool timed = next_timer(ctx, kProfPlanSegments, &timers[0]) && (fuse || next_timer(ctx, kProfPlanFill, &timers[1]));
-    LORA_HIP(launch_plan_build(a, fuse, ctx->opt_plan_variant > 0 ? ctx->opt_plan_variant : 0, stream, timed ? timers : nullptr));
+    return a;
+}
 
-    out->T = T;
-    out->n_req = n_req;
-    out->n_adapters = n_adapters;
-    out->r_max = r_max;
-    out->seg_cap = L.seg_cap;
-    out->ext_cap = L.ext_cap;
+void fill_plan(const PlanBuildArgs &a, lora_plan_t *out) {
+    out->T = a.T;
+    out->n_req = a.n_req;
+    out->n_adapters = a.n_adapters;
+    out->r_max = a.r_max;
+    out->seg_cap = a.seg_cap;
+    out->ext_cap = a.ext_cap;
     out->magic = kPlanMagic;
     out->unit_rows = a.unit_rows;
     out->perm = a.perm;
@@ -281,7 +285,74 @@ int build_plan(lora_ctx *ctx, const int32_t *req_adapter_dev, const int32_t *req
     out->ext_rec = a.ext_rec;
     out->tok_off = a.tok_off;
     out->scalars = a.scalars;
+}
+
+int build_plan(lora_ctx *ctx, const PlanBuildArgs &a, hipStream_t stream, lora_plan_t *out) {
+    // One workgroup builds the whole plan (per-row arrays included) up to 4096 rows, up to 8192 for batches of at
+    // most 64 requests (the one-lane-per-request kernel leaves its workgroup more time for the rows); beyond that
+    // the per-row arrays are filled by a second, grid-wide kernel.
+    const int fused_rows = ctx->opt_plan_fused_rows >= 0 ? ctx->opt_plan_fused_rows : (a.n_req <= 64 ? 8192 : 4096);
+    const bool fuse = a.T <= fused_rows && a.ext_cap <= 8192;
+    KernelTimer timers[2];
+    const bool timed = next_timer(ctx, kProfPlanSegments, &timers[0]) && (fuse || next_timer(ctx, kProfPlanFill, &timers[1]));
+    LORA_HIP(launch_plan_build(a, fuse, ctx->opt_plan_variant > 0 ? ctx->opt_plan_variant : 0, stream, timed ? timers : nullptr));
+
+    fill_plan(a, out);
     return LORA_OK;
+}
+
+// Request- and segment-level quantities of a validated batch, in the order of PlanTable: a counting sort by adapter.
+void build_table(const int32_t *req_adapter, const int32_t *req_ntok, const int32_t *adapter_rank, int32_t n_adapters, const PlanBuildArgs &a,
+                 std::vector<int32_t> &rows, std::vector<int32_t> &seg, int32_t *out, PlanTable *t) {
+    const int R = a.n_req;
+    rows.assign((size_t)n_adapters + 1, 0);  // (key n_adapters: requests without an adapter)
+    seg.resize((size_t)n_adapters + 1);
+    for (int i = 0; i < R; ++i) rows[req_adapter[i] < 0 ? n_adapters : req_adapter[i]] += req_ntok[i];
+    int32_t *sad = out + t->sad(), *sip = out + t->sip(), *srk = out + t->srk(), *sex = out + t->sex(), *sun = out + t->sun();
+    int s = 0, slot = 0, ext = 0, units = 0;
+    for (int k = 0; k <= n_adapters; ++k) {
+        if (rows[k] == 0) continue;
+        sad[s] = k < n_adapters ? k : -1;
+        sip[s] = slot;
+        srk[s] = k < n_adapters ? adapter_rank[k] : 0;
+        sex[s] = ext;
+        sun[s] = units;
+        seg[k] = s;
+        ext += srk[s];
+        if (k < n_adapters) units += (rows[k] + a.unit_rows - 1) >> a.unit_shift;
+        const int n = rows[k];
+        rows[k] = slot;  // from here on: the key's running slot
+        slot += n;
+        ++s;
+    }
+    sip[s] = slot;
+    sex[s] = ext;
+    sun[s] = units;
+    int32_t *tok = out + t->tok(), *dst = out + t->dst(), *rseg = out + t->rseg();
+    int row = 0;
+    for (int i = 0; i < R; ++i) {
+        const int k = req_adapter[i] < 0 ? n_adapters : req_adapter[i];
+        const int n = req_ntok[i];
+        tok[i] = row;
+        row += n;
+        dst[i] = n > 0 ? rows[k] : 0;
+        rseg[i] = n > 0 ? seg[k] : 0;  // (a request without rows has no segment; nothing looks its entries up)
+        if (n > 0) rows[k] += n;
+    }
+    tok[R] = row;
+    t->ext_total = ext;
+    t->n_units = units;
+}
+
+// Waits until the kernel that was given slot `i`'s table has read it (it stands in a stream, so it will).
+void wait_table(const lora_ctx *ctx, int i) {
+    const auto t0 = std::chrono::steady_clock::now();
+    while (__atomic_load_n(ctx->table_done + i, __ATOMIC_ACQUIRE) != ctx->table_ticket[i]) {
+        if (std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(1))
+            std::this_thread::yield();
+        else
+            std::this_thread::sleep_for(std::chrono::microseconds(50));
+    }
 }
 
 int check_plan_buf(const void *plan_buf, size_t plan_buf_bytes, const PlanLayout &L, lora_plan_t *out) {
@@ -514,7 +585,7 @@ bool has_adapters(const lora_plan_t *plan, const lora_linear_desc *d) {
 
 // Upper bound of the plan's work units: sum over the adapter segments of ceil(rows / unit_rows).
 int64_t max_units_of(const lora_plan_t *plan) {
-    const int64_t segs = std::min<int64_t>(std::min<int64_t>(plan->n_adapters, plan->n_req), plan->T);
+    const int64_t segs = std::min<int64_t>(std::min<int64_t>(plan->n_adapters, plan->n_req), std::min<int64_t>(plan->T, plan->seg_cap));
     return plan->T / plan->unit_rows + segs;
 }
 
@@ -536,8 +607,9 @@ DecodeArgs decode_args(const lora_ctx *ctx, const lora_plan_t *plan, const lora_
     const lora_linear_desc *d = descs[0];
     bool any_ad = false;
     for (int i = 0; i < n; ++i) any_ad = any_ad || has_adapters(plan, descs[i]);
-    // ranks the batch can use at most: one adapter per request, per slot, per row
+    // ranks the batch can use at most: one adapter per request, per slot, per row; those in use where the host built the plan
     const int64_t segs = std::min<int64_t>(std::min<int64_t>(plan->n_req, plan->n_adapters), plan->T);
+    const int64_t ext_rows = std::min<int64_t>(segs * plan->r_max, 8 * (int64_t)plan->ext_cap);
     DecodeArgs a;
     a.plan = view_of(plan);
     a.X = d->X;
@@ -550,7 +622,7 @@ DecodeArgs decode_args(const lora_ctx *ctx, const lora_plan_t *plan, const lora_
     for (int i = 0; i < n; ++i) {
         const lora_linear_desc *di = descs[i];
         const WorkspaceLayout w = workspace_layout(plan->T, di->K, di->N, plan->r_max, di->dtype);
-        const DecodeGeom g = decode_geom(plan->T, di->K, di->N, any_ad ? segs * plan->r_max : 0);
+        const DecodeGeom g = decode_geom(plan->T, di->K, di->N, any_ad ? ext_rows : 0);
         const bool ad = has_adapters(plan, di);
         DecodeSet &st = a.set[i];
         st.W = di->W0;
@@ -915,9 +987,16 @@ int lora_ctx_create(lora_ctx **out, int device_ordinal) {
         ctx->num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
         e = hipHostMalloc(reinterpret_cast<void **>(&ctx->ring), kRingSlots * kRingSlotInts * sizeof(int32_t), hipHostMallocDefault);
     }
+    if (e == hipSuccess)
+        e = hipHostMalloc(reinterpret_cast<void **>(&ctx->tables), kTableSlots * (kPlanTableInts * sizeof(int32_t) + sizeof(uint32_t)), hipHostMallocDefault);
+    if (e == hipSuccess) {
+        ctx->table_done = reinterpret_cast<uint32_t *>(ctx->tables + (size_t)kTableSlots * kPlanTableInts);
+        memset(ctx->table_done, 0, kTableSlots * sizeof(uint32_t));
+    }
     for (int i = 0; i < kRingSlots && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&ctx->ring_event[i], hipEventDisableTiming);
     // per-device set-up of the kernels: dynamic-LDS grants of every instantiation (so that no launch has to make one,
     // under stream capture or from two threads at once), and this device's address of the static scratch array
+    if (e == hipSuccess) e = init_plan_kernels();
     if (e == hipSuccess) e = init_gemm_tile_kernels();
     if (e == hipSuccess) e = init_decode_kernels();
     if (e == hipSuccess) e = init_shrink_kernels();
@@ -927,6 +1006,7 @@ int lora_ctx_create(lora_ctx **out, int device_ordinal) {
         for (int i = 0; i < kRingSlots; ++i)
             if (ctx->ring_event[i]) (void)hipEventDestroy(ctx->ring_event[i]);
         if (ctx->ring) (void)hipHostFree(ctx->ring);
+        if (ctx->tables) (void)hipHostFree(ctx->tables);
         delete ctx;
         return hip_fail(e);
     }
@@ -943,7 +1023,9 @@ int lora_ctx_destroy(lora_ctx *ctx) {
             (void)hipEventDestroy(ctx->ring_event[i]);
         }
     }
+    for (int i = 0; i < kTableSlots; ++i) wait_table(ctx, i);
     if (ctx->ring) (void)hipHostFree(ctx->ring);
+    (void)hipHostFree(ctx->tables);
     free_profiler(ctx);
     delete ctx;
     return LORA_OK;
@@ -992,7 +1074,9 @@ size_t lora_plan_bytes(int32_t n_req, int64_t T, int32_t n_adapters, int32_t r_m
 int lora_plan(lora_ctx *ctx, const int32_t *req_adapter, const int32_t *req_ntok, int32_t n_req, const int32_t *adapter_rank,
               int32_t n_adapters, int32_t r_max, int64_t T_expected, void *plan_buf, size_t plan_buf_bytes,
               lora_stream_t stream_, lora_plan_t *out) {
-    int rc = validate_batch(req_adapter, req_ntok, n_req, adapter_rank, n_adapters, r_max, T_expected, nullptr, nullptr);
+    int32_t n_seg = 0;
+    int64_t ext_total = 0;
+    int rc = validate_batch(req_adapter, req_ntok, n_req, adapter_rank, n_adapters, r_max, T_expected, &n_seg, &ext_total);
     if (rc != LORA_OK) return rc;
     const PlanLayout L = plan_layout(n_req, T_expected, n_adapters, r_max);
     rc = check_plan_buf(plan_buf, plan_buf_bytes, L, out);
@@ -1003,24 +1087,52 @@ int lora_plan(lora_ctx *ctx, const int32_t *req_adapter, const int32_t *req_ntok
     if (guard.err != hipSuccess) return hip_fail(guard.err);
     int32_t *base = static_cast<int32_t *>(plan_buf);
     int32_t *staged = base + L.staged;
-    const size_t n_ints = 2 * (size_t)n_req + (size_t)n_adapters;
-    if (n_ints > 0) {
+    const PlanBuildArgs a = plan_args(ctx, staged, staged + n_req, staged + 2 * (size_t)n_req, n_req, n_adapters, r_max, T_expected, L, base);
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    LORA_HIP(hipStreamIsCapturing(stream, &capturing));
+    // The host's table for the batches one workgroup can serve; the arrays themselves and the device's own builders for
+    // larger ones, and under stream capture (nothing runs that would report the table read).
+    if (n_req <= kApplyReq && T_expected <= kApplyRows && ext_total <= 8 * kApplyRows && capturing == hipStreamCaptureStatusNone) {
         std::lock_guard<std::mutex> lock(ctx->ring_mutex);
-        const int slot = ctx->ring_next;
-        ctx->ring_next = (slot + 1) % kRingSlots;
-        if (ctx->ring_used[slot]) LORA_HIP(hipEventSynchronize(ctx->ring_event[slot]));
-        int32_t *host = ctx->ring + (size_t)slot * kRingSlotInts;
-        if (n_req > 0) {
-            memcpy(host, req_adapter, sizeof(int32_t) * (size_t)n_req);
-            memcpy(host + n_req, req_ntok, sizeof(int32_t) * (size_t)n_req);
+        const int slot = ctx->table_next;
+        wait_table(ctx, slot);
+        PlanTable t;
+        t.data = ctx->tables + (size_t)slot * kPlanTableInts;
+        t.done = ctx->table_done + slot;
+        t.ticket = ctx->table_ticket[slot] + 1;
+        t.n_req = n_req;
+        t.n_seg = n_seg;
+        build_table(req_adapter, req_ntok, adapter_rank, n_adapters, a, ctx->key_rows, ctx->key_seg, ctx->tables + (size_t)slot * kPlanTableInts, &t);
+        KernelTimer timer;
+        const bool timed = next_timer(ctx, kProfPlanSegments, &timer);
+        LORA_HIP(launch_plan_apply(a, t, stream, timed ? &timer : nullptr));
+        ctx->table_ticket[slot] = t.ticket;  // (only now: a launch that failed reports nothing)
+        ctx->table_next = (slot + 1) % kTableSlots;
+        fill_plan(a, out);
+    } else {
+        const size_t n_ints = 2 * (size_t)n_req + (size_t)n_adapters;
+        if (n_ints > 0) {
+            std::lock_guard<std::mutex> lock(ctx->ring_mutex);
+            const int slot = ctx->ring_next;
+            ctx->ring_next = (slot + 1) % kRingSlots;
+            if (ctx->ring_used[slot]) LORA_HIP(hipEventSynchronize(ctx->ring_event[slot]));
+            int32_t *host = ctx->ring + (size_t)slot * kRingSlotInts;
+            if (n_req > 0) {
+                memcpy(host, req_adapter, sizeof(int32_t) * (size_t)n_req);
+                memcpy(host + n_req, req_ntok, sizeof(int32_t) * (size_t)n_req);
+            }
+            if (n_adapters > 0) memcpy(host + 2 * (size_t)n_req, adapter_rank, sizeof(int32_t) * (size_t)n_adapters);
+            LORA_HIP(hipMemcpyAsync(staged, host, n_ints * sizeof(int32_t), hipMemcpyHostToDevice, stream));
+            LORA_HIP(hipEventRecord(ctx->ring_event[slot], stream));
+            ctx->ring_used[slot] = true;
         }
-        if (n_adapters > 0) memcpy(host + 2 * (size_t)n_req, adapter_rank, sizeof(int32_t) * (size_t)n_adapters);
-        LORA_HIP(hipMemcpyAsync(staged, host, n_ints * sizeof(int32_t), hipMemcpyHostToDevice, stream));
-        LORA_HIP(hipEventRecord(ctx->ring_event[slot], stream));
-        ctx->ring_used[slot] = true;
+        rc = build_plan(ctx, a, stream, out);
+        if (rc != LORA_OK) return rc;
     }
-    return build_plan(ctx, staged, staged + n_req, staged + 2 * (size_t)n_req, n_req, n_adapters, r_max, T_expected, L, base,
-                      stream, out);
+    // (the host knows what the batch uses: launches that are sized by these bounds get no surplus workgroups)
+    out->seg_cap = n_seg;
+    out->ext_cap = (int32_t)(ext_total >> 3);
+    return LORA_OK;
 }
 
 int lora_plan_device(lora_ctx *ctx, const int32_t *req_adapter, const int32_t *req_ntok, int32_t n_req,
@@ -1035,8 +1147,8 @@ int lora_plan_device(lora_ctx *ctx, const int32_t *req_adapter, const int32_t *r
     if (!ctx) return LORA_ERR_INVALID_ARG;
     DeviceGuard guard(ctx->device);
     if (guard.err != hipSuccess) return hip_fail(guard.err);
-    return build_plan(ctx, req_adapter, req_ntok, adapter_rank, n_req, n_adapters, r_max, T_expected, L,
-                      static_cast<int32_t *>(plan_buf), static_cast<hipStream_t>(stream_), out);
+    return build_plan(ctx, plan_args(ctx, req_adapter, req_ntok, adapter_rank, n_req, n_adapters, r_max, T_expected, L, static_cast<int32_t *>(plan_buf)),
+                      static_cast<hipStream_t>(stream_), out);
 }
 
 int lora_plan_status(lora_ctx *ctx, const lora_plan_t *plan, lora_stream_t stream_, int32_t *n_seg_out) {

@@ -1125,6 +1125,85 @@ __global__ __launch_bounds__(kPlanThreads) void plan_mid_kernel(PlanBuildArgs p)
     }
 }
 
+// A batch whose request arrays are on the host (lora_plan): the host has validated them and, in the same pass, knows
+// every request-level and segment-level quantity, so only the arrays of the plan are left to write.  The table comes
+// straight out of pinned host memory -- one wide read per thread and 16 KB of table, ~2 us of link latency in all --
+// instead of a copy in front of the kernel; `done` tells the host that the table has been read.  Bound by that read and a
+// binary search in LDS per row: 64 requests 4.1 us where plan_tiny_kernel takes 5.2 behind a copy (~5 us of
+// stream time), 1500 requests on 209 adapters 7.6 where plan_small_kernel takes 27 behind the copy.
+__global__ __launch_bounds__(kPlanThreads) void plan_apply_kernel(PlanBuildArgs p, PlanTable tb) {
+    extern __shared__ __attribute__((aligned(16))) int s_tab[];
+    const int tid = threadIdx.x;
+    const int R = p.n_req, S = tb.n_seg;
+    const int n4 = (tb.ints() + 3) >> 2;
+    for (int i = tid; i < n4; i += kPlanThreads) {
+        const chunk_t c = load_chunk(reinterpret_cast<const chunk_t *>(tb.data) + i);
+        reinterpret_cast<chunk_t *>(s_tab)[i] = c;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        __hip_atomic_store(tb.done, tb.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        p.scalars[kScNSeg] = S;
+        p.scalars[kScStatus] = 0;
+        p.scalars[kScEvicted] = 0;
+        p.scalars[kScExtTotal] = tb.ext_total;
+        p.scalars[kScNUnits] = tb.n_units;
+        p.scalars[kScT] = p.T;
+    }
+    const int *tok = s_tab + tb.tok(), *dst = s_tab + tb.dst(), *rseg = s_tab + tb.rseg();
+    const int *sad = s_tab + tb.sad(), *sip = s_tab + tb.sip(), *srk = s_tab + tb.srk(), *sex = s_tab + tb.sex(), *sun = s_tab + tb.sun();
+    for (int t = tid; t < p.T; t += kPlanThreads) {
+        int lo = 0, hi = R;  // first request whose end offset exceeds t
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (tok[mid + 1] > t)
+                hi = mid;
+            else
+                lo = mid + 1;
+        }
+        const int slot = dst[lo] + (t - tok[lo]), sg = rseg[lo];
+        p.perm[slot] = t;
+        p.row_seg[slot] = sg;
+        p.row_adapter[t] = sad[sg];
+        p.row_ext[t] = pack_row_ext(sex[sg], srk[sg]);
+    }
+    for (int i = tid; i <= R; i += kPlanThreads) p.tok_off[i] = tok[i];
+    for (int s = tid; s <= S; s += kPlanThreads) {
+        if (s < S) {
+            p.seg_adapter[s] = sad[s];
+            p.seg_rank[s] = srk[s];
+        }
+        p.seg_indptr[s] = sip[s];
+        p.seg_ext[s] = sex[s];
+        p.seg_unit[s] = sun[s];
+    }
+    for (int q = tid; q < (tb.ext_total >> 3); q += kPlanThreads) {
+        const int pel = q << 3;
+        int lo = 0, hi = S;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (sex[mid + 1] > pel)
+                hi = mid;
+            else
+                lo = mid + 1;
+        }
+        reinterpret_cast<int4 *>(p.ext_rec)[q] = make_int4(sad[lo], (srk[lo] << 16) | (pel - sex[lo]), sip[lo], sip[lo + 1]);
+    }
+    for (int u = tid; u < tb.n_units; u += kPlanThreads) {
+        int lo = 0, hi = S;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (sun[mid + 1] > u)
+                hi = mid;
+            else
+                lo = mid + 1;
+        }
+        const int slot0 = sip[lo] + (u - sun[lo]) * p.unit_rows;
+        reinterpret_cast<int4 *>(p.unit_rec)[u] =
+            make_int4(sad[lo], srk[lo] | (sip[lo + 1] - sip[lo] >= kLongSegRows ? kUnitLongFlag : 0), slot0, min(p.unit_rows, sip[lo + 1] - slot0));
+    }
+}
+
 __global__ __launch_bounds__(256) void plan_fill_kernel(PlanBuildArgs p) {
     if (p.scalars[kScStatus] != 0) return;
     const int start = blockIdx.x * 256 + threadIdx.x;
@@ -1135,6 +1214,16 @@ __global__ __launch_bounds__(256) void plan_fill_kernel(PlanBuildArgs p) {
 }
 
 }  // namespace
+
+hipError_t init_plan_kernels() {
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(plan_apply_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               kPlanTableInts * (int)sizeof(int));
+}
+
+hipError_t launch_plan_apply(const PlanBuildArgs &a, const PlanTable &t, hipStream_t stream, const KernelTimer *timer) {
+    if (t.n_req != a.n_req || t.ints() > kPlanTableInts || t.data == nullptr || t.done == nullptr) return hipErrorInvalidValue;
+    return launch_kernel(plan_apply_kernel, dim3(1), dim3(kPlanThreads), (size_t)((t.ints() + 3) & ~3) * sizeof(int), stream, timer, a, t);
+}
 
 hipError_t launch_plan_build(const PlanBuildArgs &a, bool fuse_fill, int variant, hipStream_t stream, const KernelTimer *timers) {
     if (fuse_fill && variant != 1 && a.n_req <= kTinyReq && a.T <= kSmallRows)

@@ -1,0 +1,39 @@
+"""lora_plan() at the edges of the route that hands the device a table made by the host: the largest batch it takes and the
+first one beyond it, empty requests, and more plans in flight than there are tables (bit-exact, as all plan tests)."""
+import numpy as np
+import pytest
+
+from test_gpu_plan import _check_plan
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("R,T,n_ad", [(1, 1, 1), (2048, 2048, 2048), (2049, 4000, 300), (300, 16384, 40), (300, 16385, 40), (2048, 9000, 5000)])
+def test_plan_from_host_arrays_at_the_edges(R, T, n_ad):
+    rng = np.random.default_rng(R + T)
+    cuts = np.sort(rng.integers(0, T + 1, R - 1))
+    L = np.diff(np.concatenate([[0], cuts, [T]]))  # empty requests among them
+    ids = rng.integers(-1, n_ad, R) if R > 1 else [0]
+    _check_plan(ids, L, rng.choice([8, 16, 64], n_ad), False)
+
+
+def test_rank_axis_longer_than_one_workgroup_serves():
+    _check_plan(np.arange(300), np.ones(300, int), np.full(300, 512), False)      # 19200 records: beyond the table's limit
+    _check_plan(np.arange(256), np.ones(256, int), np.full(256, 512), False)      # 16384: at it
+
+
+def test_more_plans_in_flight_than_tables():
+    import torch
+    from gpu_common import ctx, plan_reference, rt
+    c = ctx()
+    rng = np.random.default_rng(3)
+    batches = [(rng.integers(-1, 9, 50 + i), rng.integers(0, 4, 50 + i)) for i in range(40)]
+    ranks = rng.choice([8, 16, 32], 9)
+    torch.cuda.synchronize()
+    x = torch.randn(8192, 8192, device=c.device)
+    x @ x  # (keeps the stream busy while the plans queue up)
+    plans = [rt.plan(c, ids, L, ranks) for ids, L in batches]
+    for (ids, L), pl in zip(batches, plans):
+        got, ref = pl.to_host(c), plan_reference(ids.astype(np.int32), L.astype(np.int32), ranks.astype(np.int32))
+        for k in ("perm", "row_seg", "seg_adapter", "seg_indptr", "seg_rank", "seg_ext"):
+            assert np.array_equal(got[k], ref[k]), k
