@@ -13,7 +13,8 @@ from . import binding as B
 
 
 def _stream() -> int:
-    return int(torch.cuda.current_stream().cuda_stream)
+    # the current stream of the current device without the wrapper object: 0.2 us where torch.cuda.current_stream() takes 2.7
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def tensor_from_bits(a: np.ndarray, device) -> torch.Tensor:
@@ -35,9 +36,9 @@ def bits_from_tensor(t: torch.Tensor) -> np.ndarray:
 
 
 def dtype_code(t: torch.dtype) -> int:
-    if t == torch.bfloat16:
+    if t is torch.bfloat16:
         return B.LORA_DTYPE_BF16
-    if t == torch.float32:
+    if t is torch.float32:
         return B.LORA_DTYPE_F32
     raise TypeError(f"unsupported dtype {t}")
 
@@ -105,11 +106,11 @@ class Plan:
 
     @property
     def T(self) -> int:
-        return int(self.struct.T)
+        return self.struct.T
 
     @property
     def r_max(self) -> int:
-        return int(self.struct.r_max)
+        return self.struct.r_max
 
     def status(self, ctx: Context):
         return B.lora_plan_status(ctx.handle, self.struct, _stream())
@@ -152,7 +153,7 @@ def plan(ctx: Context, req_adapter, req_ntok, adapter_rank, r_max: Optional[int]
     ra = np.ascontiguousarray(req_adapter, np.int32)
     rn = np.ascontiguousarray(req_ntok, np.int32)
     rk = np.ascontiguousarray(adapter_rank, np.int32)
-    T = int(rn.astype(np.int64).sum())
+    T = int(rn.sum(dtype=np.int64))
     if r_max is None:
         r_max = int(rk.max()) if rk.size else 0
     if buf is None:
@@ -184,40 +185,49 @@ def workspace(T: int, K: int, N: int, r_max: int, dtype: torch.dtype, device, mi
 def linear_desc(pl: Plan, X: torch.Tensor, W0: torch.Tensor, Y: torch.Tensor, table: Optional[AdapterTable],
                 ws: torch.Tensor) -> B.lora_linear_desc:
     assert X.dim() == 2 and W0.dim() == 2 and Y.dim() == 2
-    assert X.stride(1) == 1 and W0.stride(1) == 1 and Y.stride(1) == 1
-    assert X.dtype == W0.dtype == Y.dtype
-    K, N = W0.shape[1], W0.shape[0]
-    assert X.shape[1] == K and Y.shape[1] == N and X.shape[0] == pl.T and Y.shape[0] == pl.T
-    ldx = X.stride(0) if X.shape[0] > 1 else max(K, X.stride(0))
-    ldy = Y.stride(0) if Y.shape[0] > 1 else max(N, Y.stride(0))
-    return B.make_linear_desc(dtype_code(X.dtype), K, N, X.data_ptr(), ldx, W0.data_ptr(), W0.stride(0),
-                              Y.data_ptr(), ldy, table.struct if table is not None else None,
-                              ws.data_ptr(), ws.numel())
+    T, (rows, K), (N, Kw), (rows_y, Ny) = pl.T, X.shape, W0.shape, Y.shape
+    ldx, cx = X.stride()
+    ldw, cw = W0.stride()
+    ldy, cy = Y.stride()
+    assert cx == cw == cy == 1
+    assert X.dtype is W0.dtype is Y.dtype
+    assert K == Kw and N == Ny and rows == T and rows_y == T
+    if T <= 1:
+        ldx, ldy = max(K, ldx), max(N, ldy)
+    return B.make_linear_desc(dtype_code(X.dtype), K, N, X.data_ptr(), ldx, W0.data_ptr(), ldw, Y.data_ptr(), ldy,
+                              table.struct if table is not None else None, ws.data_ptr(), ws.numel())
+
+
+def _output(T: int, N: int, X: torch.Tensor) -> torch.Tensor:
+    """[T, N] with rows padded to a 16-byte multiple, as the ABI requires of ldy."""
+    pad = -N % (8 if X.dtype is torch.bfloat16 else 4)
+    Y = torch.empty((T, N + pad), dtype=X.dtype, device=X.device)
+    return Y[:, :N] if pad else Y
+
+
+_STAGES = {"linear": "lora_linear", "shrink": "lora_shrink", "gemm_expand": "lora_gemm_expand"}
 
 
 def linear(ctx: Context, pl: Plan, X: torch.Tensor, W0: torch.Tensor, table: Optional[AdapterTable],
            Y: Optional[torch.Tensor] = None, ws: Optional[torch.Tensor] = None, stage: str = "linear") -> torch.Tensor:
     """Run lora_linear (or one of its two stages) on the current stream; returns Y."""
     N = W0.shape[0]
-    if Y is None:  # rows padded to a 16-byte multiple, as the ABI requires of ldy
-        ce = 8 if X.dtype == torch.bfloat16 else 4
-        Y = torch.empty((pl.T, (N + ce - 1) // ce * ce), dtype=X.dtype, device=X.device)[:, :N]
+    if Y is None:
+        Y = _output(pl.T, N, X)
     if ws is None:
         ws = workspace(pl.T, W0.shape[1], N, pl.r_max, X.dtype, X.device)
     d = linear_desc(pl, X, W0, Y, table, ws)
-    fn = {"linear": B.lora_linear, "shrink": B.lora_shrink, "gemm_expand": B.lora_gemm_expand}[stage]
-    fn(ctx.handle, pl.struct, d, _stream())
+    getattr(B, _STAGES[stage])(ctx.handle, pl.struct, d, _stream())
     return Y
 
 
 def linear_multi(ctx: Context, pl: Plan, X: torch.Tensor, projections) -> List[torch.Tensor]:
     """Run lora_linear_multi on the current stream: ``projections`` is a list of (W0, table) that share X;
     returns the list of outputs."""
-    ce = 8 if X.dtype == torch.bfloat16 else 4
     descs, outs, keep = [], [], []
     for W0, table in projections:
         N = W0.shape[0]
-        Y = torch.empty((pl.T, (N + ce - 1) // ce * ce), dtype=X.dtype, device=X.device)[:, :N]
+        Y = _output(pl.T, N, X)
         ws = workspace(pl.T, W0.shape[1], N, pl.r_max, X.dtype, X.device)
         descs.append(linear_desc(pl, X, W0, Y, table, ws))
         outs.append(Y)
