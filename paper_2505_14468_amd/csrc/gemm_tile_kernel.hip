@@ -605,6 +605,7 @@ hipError_t init_tiles() {
     if (e == hipSuccess) e = init_tile<E, 128, 192, 2, 2>();
     if (e == hipSuccess) e = init_tile<E, 256, 192, 2, 2>();
     if (e == hipSuccess) e = init_tile<E, 256, 224, 4, 1>();
+    if (e == hipSuccess) e = init_tile<E, 192, 128, 2, 2, true>();
     return e;
 }
 
@@ -625,6 +626,8 @@ hipError_t launch_variant(const GemmArgs &a, int variant, hipStream_t stream, co
             return launch_tile<E, 256, 192, 2, 2>(a, stream, timer);
         case kGemmTile256x224:
             return launch_tile<E, 256, 224, 4, 1>(a, stream, timer);
+        case kGemmTile192x128:
+            return launch_tile<E, 192, 128, 2, 2, true>(a, stream, timer);
         default:
             return hipErrorInvalidValue;
     }

@@ -423,6 +423,7 @@ GemmChoice choose_gemm_sets(const lora_ctx *ctx, int64_t T, int32_t K, const int
         return c;
     }
     const int cus = ctx ? ctx->num_cu : 256;
+    // (192x128: 1500 rows on 4096 -> 4096 in fp32 481 -> 368 us per layer, in bf16 65 -> 62; 1300 rows on 5120 -> 13824 221 -> 205)
     // Time model: rounds of one tile per CU, a tile costing its area over its MFMA efficiency (measured per
     // round at K = 4096: 256x256 104 us, 256x224 100 us, 256x192 88 us, 256x128 64 us, 128x192 51 us, 128x128 34 us, all on 4 waves).
     struct Cand {
@@ -434,6 +435,7 @@ GemmChoice choose_gemm_sets(const lora_ctx *ctx, int64_t T, int32_t K, const int
                           {kGemmTile256x224, 256, 224, 0.905},
                           {kGemmTile256x192, 256, 192, 0.89},
                           {kGemmTile128x192, 128, 192, 0.77},
+                          {kGemmTile192x128, 192, 128, 0.77},
                           {kGemmTile128x128, 128, 128, 0.77},
                           {kGemmTile64x64, 64, 64, 0.45}};
     double best = 0.0;
@@ -473,11 +475,32 @@ SplitK choose_split_k(int64_t T, int32_t K, int32_t N, int32_t dtype) {
     if (T <= kDecodeMaxRows) return r;  // (the decode path, or a batch too small to matter)
     const int stage = dtype == LORA_DTYPE_BF16 ? 64 : 32;
     int64_t s = 0;
-    if (T <= 1024) {
-        // Mid-sized batches on 128x128 tiles.  Worth it while the tiles alone leave most of the chip idle (measured at
-        // 4096 -> 4096: 129 rows 46.7 -> 37.8 us per layer, 256 rows 48.5 -> 42.7, 512 rows no gain; 11008 -> 4096, 512
-        // rows: 126 -> 108 us; at 4096 -> 11008, 172 tiles and more, the partial outputs cost more than the idle CUs:
-        // 72 -> 84 us).
+    if (T <= 1024 && dtype == LORA_DTYPE_BF16) {
+        // Mid-sized batches.  As many stretches of K as fit one round of at most one workgroup per CU, on 128x128 or on
+        // 192x128 tiles: with one and a half workgroups per CU (the earlier rule) half the CUs worked twice as long as the
+        // rest (11008 -> 4096, 384 rows: 4 x 96 workgroups of 128x128 88 us per layer, 2 x 96 of them 86, 4 x 64 of 192x128
+        // 75; 160 rows: 61 -> 52 with 8 x 32 of 192x128; 13824 -> 5120, 450 rows: 145 unsplit, 110 with 2 x 120 of 192x128).
+        // The choice between the two is a fit to such layer times: a stage of K costs 0.36 us on 128x128 and 0.45 on
+        // 192x128 tiles, the partial outputs are written and read at ~5 TB/s.  Short contraction axes take 192x128 tiles
+        // up to 384 rows only (4096 -> 4096: 700 rows 52 -> 55 us, 450 rows even; 4096 -> 11008: 160 rows 60 -> 55), and
+        // below 4096 none (2048 -> 6000, 333 rows: 38 -> 41).
+        double best = 0.0;
+        for (int v = 0; v < 2; ++v) {
+            const int bm = v ? 192 : 128;
+            if (v && (K < 4096 || (K < 8192 && T > 384))) continue;
+            const int64_t tiles = ((T + bm - 1) / bm) * (((int64_t)N + 127) / 128);
+            if (tiles > 96 && K < 4096) continue;
+            const int64_t sv = std::min<int64_t>(std::min<int64_t>(256 / tiles, 8), K / (16 * stage));  // (256: the part's CUs)
+            if (sv < 2) continue;
+            const double cost = (v ? 0.45 : 0.36) * (double)((K / stage + sv - 1) / sv) + (double)sv * (double)T * (double)N * 1.6e-6;
+            if (s < 2 || cost < best) {
+                best = cost;
+                s = sv;
+                r.variant = v ? kGemmTile192x128 : kGemmTile128x128;
+            }
+        }
+    } else if (T <= 1024) {
+        // The same in fp32, on 128x128 tiles, while the tiles alone leave most of the chip idle.
         const int64_t tiles = ((T + 127) / 128) * (((int64_t)N + 127) / 128);
         if (tiles > 128 || (tiles > 96 && K < 8192)) return r;
         s = (384 + tiles - 1) / tiles;  // about one and a half workgroups per CU (two of them fit one)
@@ -1360,7 +1383,8 @@ const char *lora_gemm_kernel_name(lora_ctx *ctx, int64_t T, int32_t K, int32_t N
     const SplitK sk = choose_split_k(T, K, N, dtype);
     if (c.variant != kGemmDecode && sk.s > 1 && !(ctx && ctx->opt_gemm_split_k == 0) &&
         !(ctx && ctx->opt_gemm_variant >= 0 && ctx->opt_gemm_variant != sk.variant)) {
-        snprintf(buf, sizeof buf, sk.variant == kGemmTile128x128 ? "tile_128x128_splitk%d" : "tile_256x256_splitk%d", sk.s);
+        const char *shape = sk.variant == kGemmTile128x128 ? "128x128" : sk.variant == kGemmTile192x128 ? "192x128" : "256x256";
+        snprintf(buf, sizeof buf, "tile_%s_splitk%d", shape, sk.s);
         return buf;
     }
     switch (c.variant) {
@@ -1387,6 +1411,9 @@ const char *lora_gemm_kernel_name(lora_ctx *ctx, int64_t T, int32_t K, int32_t N
             break;
         case kGemmTile256x224:
             snprintf(buf, sizeof buf, "tile_256x224");
+            break;
+        case kGemmTile192x128:
+            snprintf(buf, sizeof buf, "tile_192x128");
             break;
         default:
             snprintf(buf, sizeof buf, "unknown");
