@@ -68,6 +68,7 @@ __global__ __launch_bounds__(MAXW * 64) void decode_stream_kernel(DecodeArgs p0)
     typedef __bf16 E;
     constexpr int CE = 8;
     constexpr int XROWS = TBLK * 16;
+    constexpr bool MASKED = TBLK < 8;  // partial tiles that are never read back are not stored (see `keep`)
     constexpr int XIT = TBLK * 2;  // chunk loads per thread that cover the X slice with at least 512 threads
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(MAXW * 64) void decode_stream_kernel(DecodeArgs p0)
 #pragma unroll
     for (int tb = 0; tb < TBLK; ++tb) {
         row_ad[tb] = -2;
-        if (is_ext && tb * 16 + li < p.T) row_ad[tb] = p.plan.row_adapter[tb * 16 + li];
+        if (MASKED && is_ext && tb * 16 + li < p.T) row_ad[tb] = p.plan.row_adapter[tb * 16 + li];
     }
 
     // ---- the X slice: requested first (L2), all threads, whole rows per wave instruction ----
@@ -126,6 +127,18 @@ __global__ __launch_bounds__(MAXW * 64) void decode_stream_kernel(DecodeArgs p0)
 
     const char *rowp[2];
     bool rowok[2];
+    // The token blocks whose results this lane stores, one bit each.  Of an extension block only the tokens of the rows' own
+    // adapter are ever read back (64 adapters of rank 128 for 64 tokens: 21 MB of partial tiles less), of W0's all but
+    // the rows past T.  Settled here, so that one register lives through the stream.  Batches of more than 112 rows store
+    // everything: their 168 registers have no room (with the mask 9 spill, 4096 -> 4096 at 128 rows 20.6 -> 23.5 us).
+    unsigned keep = 0;
+    if (MASKED && is_ext) {
+        const int own = lg < 2 ? rec[0].x : rec[1].x;  // adapter of this lane's weight rows (records of 8 ranks)
+#pragma unroll
+        for (int tb = 0; tb < TBLK; ++tb) keep |= row_ad[tb] == own ? 1u << tb : 0u;
+    } else {
+        keep = (TBLK - 1) * 16 + li < p.T ? (1u << TBLK) - 1u : (1u << (TBLK - 1)) - 1u;
+    }
     if (is_ext) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -205,18 +218,11 @@ __global__ __launch_bounds__(MAXW * 64) void decode_stream_kernel(DecodeArgs p0)
     }
     LORA_TS(p.trace, 3);  // stages consumed (MFMAs may still run)
     // acc[tb][e] = D[weight row blk * 16 + lg * 4 + e][token tb * 16 + li]: one contiguous KiB per 16-row token block, in it
-    // 64 bytes (the block's 16 weight rows) per token.  Of an extension block only the tokens of the rows' own adapter are
-    // ever read back, so only those are stored (64 adapters of rank 128 for 64 tokens: 21 MB of partial tiles less).
+    // 64 bytes (the block's 16 weight rows) per token
     float4 *P4 = reinterpret_cast<float4 *>(p.P) + ((int64_t)(blk * p.ks + slice) * TBLK) * 64 + li * 4 + lg;
-    if (is_ext) {
-        const int own = lg < 2 ? rec[0].x : rec[1].x;  // adapter of this lane's weight rows (records of 8 ranks)
 #pragma unroll
-        for (int tb = 0; tb < TBLK; ++tb)
-            if (row_ad[tb] == own) P4[tb * 64] = make_float4(acc[tb][0], acc[tb][1], acc[tb][2], acc[tb][3]);
-    } else {
-#pragma unroll
-        for (int tb = 0; tb < TBLK; ++tb) P4[tb * 64] = make_float4(acc[tb][0], acc[tb][1], acc[tb][2], acc[tb][3]);
-    }
+    for (int tb = 0; tb < TBLK; ++tb)
+        if (!MASKED || (keep >> tb & 1u)) P4[tb * 64] = make_float4(acc[tb][0], acc[tb][1], acc[tb][2], acc[tb][3]);
     LORA_TS(p.trace, 4);
 }
 
@@ -642,7 +648,7 @@ hipError_t launch_reduce_t(const DecodeArgs &a, hipStream_t stream, const Kernel
 }
 
 bool decode_args_ok(const DecodeArgs &a, int tblk) {
-    if (!(a.T > 0 && a.T <= tblk * 16 && a.K > 0 && (a.K & 7) == 0 && a.nbe_cap >= 0 && a.X != nullptr &&
+    if (!(a.T > (tblk - 1) * 16 && a.T <= tblk * 16 && a.K > 0 && (a.K & 7) == 0 && a.nbe_cap >= 0 && a.X != nullptr &&
           a.ks == (a.K / 8 + kDsSliceChunks - 1) / kDsSliceChunks && a.n_sets >= 0 && a.n_sets <= kMaxGemmSets))
         return false;
     if (a.n_sets == 0) return a.N > 0 && a.nbw == (a.N + 15) / 16 && a.P != nullptr && a.W != nullptr && a.Y != nullptr;
@@ -658,13 +664,16 @@ bool decode_args_ok(const DecodeArgs &a, int tblk) {
 hipError_t init_decode_kernels() {
     hipError_t e = init_stream<1, kDecodeMaxWaves>();
     if (e == hipSuccess) e = init_stream<2, kDecodeMaxWaves>();
+    if (e == hipSuccess) e = init_stream<3, kDecodeMaxWaves>();
     if (e == hipSuccess) e = init_stream<4, kDecodeMaxWaves>();
+    if (e == hipSuccess) e = init_stream<5, kDecodeMaxWaves>();
     if (e == hipSuccess) e = init_stream<6, kDecodeMaxWaves>();
+    if (e == hipSuccess) e = init_stream<7, kDecodeMaxWaves>();
     if (e == hipSuccess) e = init_stream<8, kDecodeMaxWaves>();
     return e;
 }
 
-// tblk: 16-row blocks of the batch (1, 2, 4, 6, 8).
+// tblk: 16-row blocks of the batch (1 .. 8).
 hipError_t launch_decode_stream(const DecodeArgs &a, int tblk, hipStream_t stream, const KernelTimer *timer) {
     if (!decode_args_ok(a, tblk)) return hipErrorInvalidValue;
     switch (tblk) {
@@ -672,10 +681,16 @@ hipError_t launch_decode_stream(const DecodeArgs &a, int tblk, hipStream_t strea
             return launch_stream_t<1, kDecodeMaxWaves>(a, stream, timer);
         case 2:
             return launch_stream_t<2, kDecodeMaxWaves>(a, stream, timer);
+        case 3:
+            return launch_stream_t<3, kDecodeMaxWaves>(a, stream, timer);
         case 4:
             return launch_stream_t<4, kDecodeMaxWaves>(a, stream, timer);
+        case 5:
+            return launch_stream_t<5, kDecodeMaxWaves>(a, stream, timer);
         case 6:
             return launch_stream_t<6, kDecodeMaxWaves>(a, stream, timer);
+        case 7:
+            return launch_stream_t<7, kDecodeMaxWaves>(a, stream, timer);
         case 8:
             return launch_stream_t<8, kDecodeMaxWaves>(a, stream, timer);
         default:
@@ -690,10 +705,16 @@ hipError_t launch_decode_reduce(const DecodeArgs &a, int tblk, hipStream_t strea
             return launch_reduce_t<1>(a, stream, timer);
         case 2:
             return launch_reduce_t<2>(a, stream, timer);
+        case 3:
+            return launch_reduce_t<3>(a, stream, timer);
         case 4:
             return launch_reduce_t<4>(a, stream, timer);
+        case 5:
+            return launch_reduce_t<5>(a, stream, timer);
         case 6:
             return launch_reduce_t<6>(a, stream, timer);
+        case 7:
+            return launch_reduce_t<7>(a, stream, timer);
         case 8:
             return launch_reduce_t<8>(a, stream, timer);
         default:
@@ -712,10 +733,16 @@ hipError_t launch_decode_finish(const DecodeArgs &a, int tblk, int units_cap, hi
             return launch_finish_t<1>(a, units_cap, stream, timer);
         case 2:
             return launch_finish_t<2>(a, units_cap, stream, timer);
+        case 3:
+            return launch_finish_t<3>(a, units_cap, stream, timer);
         case 4:
             return launch_finish_t<4>(a, units_cap, stream, timer);
+        case 5:
+            return launch_finish_t<5>(a, units_cap, stream, timer);
         case 6:
             return launch_finish_t<6>(a, units_cap, stream, timer);
+        case 7:
+            return launch_finish_t<7>(a, units_cap, stream, timer);
         case 8:
             return launch_finish_t<8>(a, units_cap, stream, timer);
         default:

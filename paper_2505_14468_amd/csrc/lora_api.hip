@@ -364,7 +364,8 @@ int check_plan_buf(const void *plan_buf, size_t plan_buf_bytes, const PlanLayout
 }
 
 // ---- kernel selection ---------------------------------------------------------------------------------
-int decode_tblk(int64_t T) { return T <= 16 ? 1 : T <= 32 ? 2 : T <= 64 ? 4 : T <= 96 ? 6 : 8; }
+// Blocks of exactly as many 16-row pieces as the batch has: padding costs partial tiles written and read, MFMAs and LDS.
+int decode_tblk(int64_t T) { return T <= 16 ? 1 : (int)((T + 15) / 16); }
 
 struct GemmChoice {
     int variant;
@@ -397,7 +398,8 @@ DecodeGeom decode_geom(int64_t T, int32_t K, int32_t N, int64_t ext_rows_bound) 
 // throughout (28 vs 43 us, 63 vs 93 us at 128 rows).
 bool decode_path_cheaper(int64_t T, int32_t K, int32_t N) {
     const double w_mb = 2.0e-6 * (double)K * (double)N;
-    const double p_mb = 1.024e-3 * (double)((N + 15) / 16) * (double)((K / 8 + 63) / 64) * (double)decode_tblk(T);
+    const int tblk = T <= 32 ? decode_tblk(T) : 2 * (int)((T + 31) / 32);  // (the fit's own measure of the rows)
+    const double p_mb = 1.024e-3 * (double)((N + 15) / 16) * (double)((K / 8 + 63) / 64) * (double)tblk;
     const double t_decode = 8.0 + (w_mb + 2.0 * p_mb) / 3.6;
     const double t_tiled = 15.0 + std::max(29.0 * (double)K / 4096.0, w_mb / 3.0 + 6.0);
     return t_decode <= 1.08 * t_tiled;
