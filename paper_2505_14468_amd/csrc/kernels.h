@@ -78,15 +78,18 @@ namespace lora {
     } while (0)
 #endif
 
-// Launch with or without a timer.
-template <typename F, typename... Args>
-inline hipError_t launch_kernel(F kernel, dim3 grid, dim3 block, size_t smem, hipStream_t stream, const KernelTimer *timer,
-                                Args... args) {
-    if (timer != nullptr)
-        hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)smem, stream, timer->start, timer->stop, 0, args...);
-    else
-        hipLaunchKernelGGL(kernel, grid, block, smem, stream, args...);
-    return hipGetLastError();
+// Launch with or without a timer.  The status is the launch's own: hipGetLastError() behind a <<<>>> launch would also report
+// an error that some earlier HIP call of this thread left behind, for a kernel that was enqueued all the same.
+template <typename... P>
+inline hipError_t launch_kernel_as(const void *kernel, dim3 grid, dim3 block, size_t smem, hipStream_t stream, const KernelTimer *timer, P... args) {
+    void *ptrs[] = {&args...};
+    if (timer != nullptr) return hipExtLaunchKernel(kernel, grid, block, ptrs, smem, stream, timer->start, timer->stop, 0);
+    return hipLaunchKernel(kernel, grid, block, ptrs, smem, stream);
+}
+template <typename... P, typename... Args>
+inline hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, size_t smem, hipStream_t stream, const KernelTimer *timer,
+                                const Args &...args) {
+    return launch_kernel_as<P...>(reinterpret_cast<const void *>(kernel), grid, block, smem, stream, timer, args...);
 }
 
 // Enqueues the segment builder (one or two kernels).  `fuse_fill`: the single

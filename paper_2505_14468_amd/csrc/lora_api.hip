@@ -66,7 +66,8 @@ struct lora_ctx {
     // pinned tables that plan_apply_kernel reads in place, and the words in which it reports having read them
     int32_t *tables = nullptr;
     uint32_t *table_done = nullptr;
-    uint32_t table_ticket[kTableSlots] = {};
+    uint32_t table_ticket[kTableSlots] = {};  // what the slot's word reads when its table is free
+    uint32_t last_ticket = 0;
     int table_next = 0;
     std::vector<int32_t> key_rows, key_seg;  // scratch of lora_plan()
     std::mutex ring_mutex;  // guards everything above
@@ -1130,14 +1131,14 @@ int lora_plan(lora_ctx *ctx, const int32_t *req_adapter, const int32_t *req_ntok
         PlanTable t;
         t.data = ctx->tables + (size_t)slot * kPlanTableInts;
         t.done = ctx->table_done + slot;
-        t.ticket = ctx->table_ticket[slot] + 1;
+        t.ticket = ++ctx->last_ticket;  // (no two launches share one, whatever became of them)
         t.n_req = n_req;
         t.n_seg = n_seg;
         build_table(req_adapter, req_ntok, adapter_rank, n_adapters, a, ctx->key_rows, ctx->key_seg, ctx->tables + (size_t)slot * kPlanTableInts, &t);
         KernelTimer timer;
         const bool timed = next_timer(ctx, kProfPlanSegments, &timer);
         LORA_HIP(launch_plan_apply(a, t, stream, timed ? &timer : nullptr));
-        ctx->table_ticket[slot] = t.ticket;  // (only now: a launch that failed reports nothing)
+        ctx->table_ticket[slot] = t.ticket;  // (only now: a launch that failed enqueued nothing and will report nothing)
         ctx->table_next = (slot + 1) % kTableSlots;
         fill_plan(a, out);
     } else {

@@ -37,3 +37,29 @@ def test_more_plans_in_flight_than_tables():
         got, ref = pl.to_host(c), plan_reference(ids.astype(np.int32), L.astype(np.int32), ranks.astype(np.int32))
         for k in ("perm", "row_seg", "seg_adapter", "seg_indptr", "seg_rank", "seg_ext"):
             assert np.array_equal(got[k], ref[k]), k
+
+
+def test_pending_error_of_another_call():
+    """A HIP call refused before lora_plan() (an argument error, nothing on the GPU) says nothing about the plan's launch: plans
+    of different sizes queued behind other work all come out right."""
+    import torch
+    from gpu_common import B, ctx, plan_reference, rt
+    c = ctx()
+    hip = B.lib()  # (its own HIP runtime: dependencies of the library are searched too)
+    rng = np.random.default_rng(4)
+    ranks = rng.choice([8, 16, 32], 9).astype(np.int32)
+    batches = [(rng.integers(-1, 9, n).astype(np.int32), rng.integers(0, 5, n).astype(np.int32)) for n in (400, 3, 64, 1, 200, 7)]
+    bufs = [torch.empty(B.lora_plan_bytes(len(i), int(L.sum()), 9, 32), dtype=torch.uint8, device=c.device) for i, L in batches]
+    torch.cuda.synchronize()
+    st = torch.cuda.current_stream().cuda_stream
+    x = torch.randn(8192, 8192, device=c.device)
+    x @ x
+    structs = []
+    for (ids, L), buf in zip(batches, bufs):
+        assert hip.hipSetDevice(1 << 20) != 0
+        structs.append(B.lora_plan(c.handle, ids, L, ranks, 32, int(L.sum()), buf.data_ptr(), buf.numel(), st))
+    hip.hipGetLastError()  # (torch would blame its next call)
+    for (ids, L), buf, struct in zip(batches, bufs, structs):
+        got, ref = rt.Plan(struct, buf).to_host(c), plan_reference(ids, L, ranks)
+        for k in ("perm", "row_seg", "seg_adapter", "seg_indptr", "seg_rank", "seg_ext"):
+            assert np.array_equal(got[k], ref[k]), k
