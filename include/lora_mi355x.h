@@ -195,8 +195,9 @@ size_t lora_plan_bytes(int32_t n_req, int64_t T, int32_t n_adapters, int32_t r_m
  * freed on return; up to 2048 requests and 16384 rows: a sorted table that the
  * kernel reads in place, else the arrays) and builds every T-sized array on the
  * device, in plan_buf (DEVICE, 256-byte aligned, >= lora_plan_bytes()).
- * Asynchronous on `stream`; may block only when the pinned memory is in use (16
- * plans in flight; 4 larger ones).  T == 0 is valid.  Errors: as lora_plan_validate, plus WORKSPACE_TOO_SMALL, ALIGNMENT, HIP. */
+ * Asynchronous on `stream`; may block only when the pinned memory is in use: with
+ * 16 plans in flight for 20 ms at most (the plan is then made as for a larger
+ * batch), with 4 larger ones until the oldest has been copied.  T == 0 is valid.  Errors: as lora_plan_validate, plus WORKSPACE_TOO_SMALL, ALIGNMENT, HIP. */
 int lora_plan(lora_ctx *ctx, const int32_t *req_adapter, const int32_t *req_ntok, int32_t n_req,
               const int32_t *adapter_rank, int32_t n_adapters, int32_t r_max, int64_t T_expected,
               void *plan_buf, size_t plan_buf_bytes, lora_stream_t stream, lora_plan_t *out);

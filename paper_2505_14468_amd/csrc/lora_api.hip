@@ -345,11 +345,23 @@ void build_table(const int32_t *req_adapter, const int32_t *req_ntok, const int3
     t->n_units = units;
 }
 
-// Waits until the kernel that was given slot `i`'s table has read it (it stands in a stream, so it will).
-void wait_table(const lora_ctx *ctx, int i) {
+// Most time lora_plan() waits for a table: several times what the layers of most plans take on the GPU, so that a host that
+// runs ahead of it finds one.  Past that the upload takes over, whose events the runtime can report errors on.
+constexpr auto kTableWait = std::chrono::milliseconds(20);
+
+bool table_free(const lora_ctx *ctx, int i) { return __atomic_load_n(ctx->table_done + i, __ATOMIC_ACQUIRE) == ctx->table_ticket[i]; }
+
+// A slot whose last table has been read, the next one in turn if possible; -1 if there is none within the time above.
+int take_table(const lora_ctx *ctx) {
     const auto t0 = std::chrono::steady_clock::now();
-    while (__atomic_load_n(ctx->table_done + i, __ATOMIC_ACQUIRE) != ctx->table_ticket[i]) {
-        if (std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(1))
+    for (;;) {
+        for (int k = 0; k < kTableSlots; ++k) {
+            const int i = (ctx->table_next + k) % kTableSlots;
+            if (table_free(ctx, i)) return i;
+        }
+        const auto waited = std::chrono::steady_clock::now() - t0;
+        if (waited >= kTableWait) return -1;
+        if (waited < std::chrono::milliseconds(1))
             std::this_thread::yield();
         else
             std::this_thread::sleep_for(std::chrono::microseconds(50));
@@ -1055,9 +1067,12 @@ int lora_ctx_destroy(lora_ctx *ctx) {
             (void)hipEventDestroy(ctx->ring_event[i]);
         }
     }
-    for (int i = 0; i < kTableSlots; ++i) wait_table(ctx, i);
+    // (tables that a kernel may still read: freed only once the device is known to be through with them)
+    bool idle = true;
+    for (int i = 0; i < kTableSlots; ++i) idle = idle && table_free(ctx, i);
+    if (!idle) idle = hipDeviceSynchronize() == hipSuccess;
     if (ctx->ring) (void)hipHostFree(ctx->ring);
-    (void)hipHostFree(ctx->tables);
+    if (idle) (void)hipHostFree(ctx->tables);
     free_profiler(ctx);
     delete ctx;
     return LORA_OK;
@@ -1123,25 +1138,29 @@ int lora_plan(lora_ctx *ctx, const int32_t *req_adapter, const int32_t *req_ntok
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     LORA_HIP(hipStreamIsCapturing(stream, &capturing));
     // The host's table for the batches one workgroup can serve; the arrays themselves and the device's own builders for
-    // larger ones, and under stream capture (nothing runs that would report the table read).
+    // larger ones, under stream capture (nothing runs that would report the table read) and while every table waits to be read.
+    bool built = false;
     if (n_req <= kApplyReq && T_expected <= kApplyRows && ext_total <= 8 * kApplyRows && capturing == hipStreamCaptureStatusNone) {
         std::lock_guard<std::mutex> lock(ctx->ring_mutex);
-        const int slot = ctx->table_next;
-        wait_table(ctx, slot);
-        PlanTable t;
-        t.data = ctx->tables + (size_t)slot * kPlanTableInts;
-        t.done = ctx->table_done + slot;
-        t.ticket = ++ctx->last_ticket;  // (no two launches share one, whatever became of them)
-        t.n_req = n_req;
-        t.n_seg = n_seg;
-        build_table(req_adapter, req_ntok, adapter_rank, n_adapters, a, ctx->key_rows, ctx->key_seg, ctx->tables + (size_t)slot * kPlanTableInts, &t);
-        KernelTimer timer;
-        const bool timed = next_timer(ctx, kProfPlanSegments, &timer);
-        LORA_HIP(launch_plan_apply(a, t, stream, timed ? &timer : nullptr));
-        ctx->table_ticket[slot] = t.ticket;  // (only now: a launch that failed enqueued nothing and will report nothing)
-        ctx->table_next = (slot + 1) % kTableSlots;
-        fill_plan(a, out);
-    } else {
+        const int slot = take_table(ctx);
+        if (slot >= 0) {
+            PlanTable t;
+            t.data = ctx->tables + (size_t)slot * kPlanTableInts;
+            t.done = ctx->table_done + slot;
+            t.ticket = ++ctx->last_ticket;  // (no two launches share one, whatever became of them)
+            t.n_req = n_req;
+            t.n_seg = n_seg;
+            build_table(req_adapter, req_ntok, adapter_rank, n_adapters, a, ctx->key_rows, ctx->key_seg, ctx->tables + (size_t)slot * kPlanTableInts, &t);
+            KernelTimer timer;
+            const bool timed = next_timer(ctx, kProfPlanSegments, &timer);
+            LORA_HIP(launch_plan_apply(a, t, stream, timed ? &timer : nullptr));
+            ctx->table_ticket[slot] = t.ticket;  // (only now: a launch that failed enqueued nothing and will report nothing)
+            ctx->table_next = (slot + 1) % kTableSlots;
+            fill_plan(a, out);
+            built = true;
+        }
+    }
+    if (!built) {
         const size_t n_ints = 2 * (size_t)n_req + (size_t)n_adapters;
         if (n_ints > 0) {
             std::lock_guard<std::mutex> lock(ctx->ring_mutex);

@@ -24,7 +24,8 @@ std::map<const void *, std::string> &names() {
 std::vector<Launch> launches;
 hipError_t pending = hipSuccess;       // what hipGetLastError() has to say
 hipError_t launch_error = hipSuccess;  // what a launch returns (nothing is enqueued then)
-hipError_t sync_error = hipSuccess;    // what waiting for an event returns
+hipError_t sync_error = hipSuccess;    // what waiting for an event or the device returns
+hipError_t copy_error = hipSuccess;    // what an asynchronous copy returns
 bool capturing = false;
 long event_waits = 0;
 
@@ -61,7 +62,7 @@ extern "C" {
 // ---- what the tests steer and read ----
 void fake_reset() {
     launches.clear();
-    pending = launch_error = sync_error = hipSuccess;
+    pending = launch_error = sync_error = copy_error = hipSuccess;
     capturing = false;
     event_waits = 0;
 }
@@ -69,6 +70,7 @@ void fake_set(const char *what, int v) {
     if (!strcmp(what, "pending")) pending = (hipError_t)v;
     if (!strcmp(what, "launch_error")) launch_error = (hipError_t)v;
     if (!strcmp(what, "sync_error")) sync_error = (hipError_t)v;
+    if (!strcmp(what, "copy_error")) copy_error = (hipError_t)v;
     if (!strcmp(what, "capturing")) capturing = v != 0;
 }
 int fake_launches() { return (int)launches.size(); }
@@ -145,7 +147,7 @@ hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
     memcpy(d, s, n);
     return hipSuccess;
 }
-hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }  // (queued, never run)
+hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t) { return fail(copy_error); }  // (queued, never run)
 hipError_t hipGetSymbolAddress(void **p, const void *) {
     *p = (void *)(uintptr_t)0x7f0000000000ull;  // (an address nothing else has; kernels do not run here)
     return hipSuccess;
@@ -157,6 +159,7 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) {
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return fail(sync_error); }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
     *e = reinterpret_cast<hipEvent_t>(malloc(8));
     return hipSuccess;
@@ -169,7 +172,7 @@ hipError_t hipEventDestroy(hipEvent_t e) {
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) {
     ++event_waits;
-    return sync_error == hipSuccess ? hipSuccess : fail(sync_error);
+    return fail(sync_error);
 }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) {
     *ms = 0.f;
