@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include <map>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -27,6 +28,7 @@ hipError_t launch_error = hipSuccess;  // what a launch returns (nothing is enqu
 hipError_t sync_error = hipSuccess;    // what waiting for an event or the device returns
 hipError_t copy_error = hipSuccess;    // what an asynchronous copy returns
 bool capturing = false;
+size_t largest_new = ~(size_t)0;  // a larger operator new throws
 long event_waits = 0;
 
 hipError_t fail(hipError_t e) {
@@ -57,6 +59,14 @@ Config config;
 
 }  // namespace
 
+void *operator new(size_t n) {
+    void *p = n <= largest_new ? malloc(n ? n : 1) : nullptr;
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
+
 extern "C" {
 
 // ---- what the tests steer and read ----
@@ -71,6 +81,7 @@ void fake_set(const char *what, int v) {
     if (!strcmp(what, "launch_error")) launch_error = (hipError_t)v;
     if (!strcmp(what, "sync_error")) sync_error = (hipError_t)v;
     if (!strcmp(what, "copy_error")) copy_error = (hipError_t)v;
+    if (!strcmp(what, "largest_new")) largest_new = (size_t)v;
     if (!strcmp(what, "capturing")) capturing = v != 0;
 }
 int fake_launches() { return (int)launches.size(); }

@@ -46,6 +46,12 @@ def tables():
     return out
 
 
+def read_table(i):
+    """What the plan kernel of launch `i` does first: its word receives its ticket."""
+    a = F.fake_arg1(i)
+    C.c_uint32.from_address(C.c_uint64.from_address(a + 8).value).value = C.c_uint32.from_address(a + 16).value
+
+
 def make_plan(ids, ntok, ranks, r_max=None, raw=False):
     ids, ntok, ranks = (np.asarray(v, np.int32) for v in (ids, ntok, ranks))
     r_max = int(ranks.max()) if r_max is None else r_max

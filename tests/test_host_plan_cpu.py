@@ -58,14 +58,57 @@ def test_plan_kernels_that_never_run(fake):
 def test_tables_are_taken_again_when_they_have_been_read(fake):
     """Every table but one is read: the plans go on through the tables and leave that one alone."""
     fake_hip.run(fake, """
-        def read(i):  # what the kernel does: the launch's word receives its ticket
-            a = F.fake_arg1(i)
-            C.c_uint32.from_address(C.c_uint64.from_address(a + 8).value).value = C.c_uint32.from_address(a + 16).value
         for i in range(100):
             make_plan([0, 1], [1, 2], [8, 16])
             if i != 3:
-                read(i)
+                read_table(i)
         seen = [a for a, _ in tables()]
         assert len(seen) == 100 and seen.count(seen[3]) == 1
         assert len({t for _, t in tables()}) == 100
+    """)
+
+
+def test_no_exception_leaves_lora_plan(fake):
+    """Memory for a thousand counters is refused: a status comes back, or the plan is made without; nothing is thrown."""
+    fake_hip.run(fake, """
+        say("largest_new", 2048)
+        status = make_plan([0, 1], [1, 2], [8] * 1000, raw=True)
+        say("largest_new", 1 << 30)
+        assert status in (B.LORA_OK, B.LORA_ERR_INVALID_ARG), status
+        assert make_plan([0, 1], [1, 2], [8] * 1000, raw=True) == B.LORA_OK
+    """)
+
+
+def test_host_table_against_the_reference(fake):
+    """Every request- and segment-level entry of the pinned table, for slots at the edges of the host's bit words, unused slots
+    between, requests without rows and without adapter, batches one after another in the same scratch."""
+    fake_hip.run(fake, """
+        from oracle import plan_reference
+        rng = np.random.default_rng(11)
+        for n_ad in (1, 63, 64, 65, 200, 65536):
+            for R in (0, 1, 5, 300):
+                edge = [v for v in (0, 62, 63, 64, 127, 128, 65535) if v < n_ad]
+                ids = np.where(rng.random(R) < 0.5, rng.choice(edge, R), rng.integers(-1, n_ad, R)).astype(np.int32)
+                L = rng.integers(0, 4, R).astype(np.int32)
+                ranks = rng.choice([8, 16, 64], n_ad).astype(np.int32)
+                F.fake_reset()
+                plan = make_plan(ids, L, ranks, r_max=64)
+                ref = plan_reference(ids, L, ranks)
+                S = len(ref["seg_adapter"])
+                read_table(0)
+                tab = np.ctypeslib.as_array((C.c_int32 * (3 * R + 5 * S + 4)).from_address(tables()[0][0]))
+                at = 3 * R + 1
+                tok = np.concatenate([[0], np.cumsum(L)])
+                assert np.array_equal(tab[: R + 1], tok)
+                slot_of = np.empty(int(L.sum()), int)
+                slot_of[ref["perm"]] = np.arange(len(slot_of))
+                full = np.flatnonzero(L)
+                assert np.array_equal(tab[R + 1 : 2 * R + 1][full], slot_of[tok[full]])
+                assert np.array_equal(tab[2 * R + 1 : at][full], ref["row_seg"][slot_of[tok[full]]])
+                for name, n in (("seg_adapter", S), ("seg_indptr", S + 1), ("seg_rank", S), ("seg_ext", S + 1)):
+                    assert np.array_equal(tab[at : at + n], ref[name]), (n_ad, R, name)
+                    at += n
+                rows = np.diff(ref["seg_indptr"])
+                units = np.where(ref["seg_adapter"] >= 0, -(-rows // plan.unit_rows), 0)
+                assert np.array_equal(tab[at : at + S + 1], np.concatenate([[0], np.cumsum(units)]))
     """)
