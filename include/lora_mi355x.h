@@ -100,7 +100,9 @@ typedef struct lora_adapter_table_t {
  * Segment table ("plan"): token rows grouped by adapter.  Plain data, filled by
  * lora_plan*(): device pointers into the caller's plan_buf plus host copies of
  * the sizes.  Valid until plan_buf is freed or reused; one plan serves every
- * projection and layer of the same batch.
+ * projection and layer of the same batch.  Calls captured into a graph on such
+ * a plan may be replayed after lora_plan*() has filled the same plan_buf for
+ * another batch with the same n_req, T, n_adapters and r_max.
  *
  * Row order: rows are sorted stably by adapter id (ascending; rows without an
  * adapter last).  "slot" = position in that order.
@@ -110,8 +112,8 @@ typedef struct lora_plan_t {
     int32_t n_req;
     int32_t n_adapters;
     int32_t r_max;          /* row stride of the intermediate V, >= every used rank         */
-    int32_t seg_cap;        /* most segments: entries of the seg_* arrays (lora_plan: in use) */
-    int32_t ext_cap;        /* most records of ext_rec (lora_plan: in use)                  */
+    int32_t seg_cap;        /* most segments of the batch (lora_plan: those in use)         */
+    int32_t ext_cap;        /* most records of ext_rec (lora_plan: those in use)            */
     int32_t magic;
     int32_t unit_rows;      /* most rows of a work unit: 64, or 16 in a plan of few rows and segments */
     const int32_t *perm;        /* device [T]        slot -> row index of X / Y             */

@@ -93,8 +93,8 @@ __global__ __launch_bounds__(MAXW * 64) void decode_stream_kernel(DecodeArgs p0)
 
     // ---- this wave's block of 16 weight rows: extension blocks (rows of the used A_a) first, then W0's ----
     const int nrec = p.A != nullptr ? p.plan.scalars[kScExtTotal] >> 3 : 0;  // records of 8 ranks
-    const bool is_ext = blk < p.nbe_cap;
-    const bool valid = is_ext ? blk * 2 < nrec : blk - p.nbe_cap < p.nbw;
+    const bool is_ext = blk < p.nbe;
+    const bool valid = is_ext ? blk * 2 < nrec : blk - p.nbe < p.nbw;
     const int wr = lane >> 3, wc = lane & 7;  // load slot: row wr + 8 i of the block, chunk wc of a 128-byte stage
     int4 rec[2] = {make_int4(-1, 0, 0, 0), make_int4(-1, 0, 0, 0)};
     const void *a_guess = nullptr;  // entry `lane` of the table of A pointers, read in the records' round trip
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(MAXW * 64) void decode_stream_kernel(DecodeArgs p0)
     } else {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {  // rows past N are clamped: they only feed partial sums that are never read
-            const int n = min(max(blk - p.nbe_cap, 0) * 16 + wr + 8 * i, p.N - 1);
+            const int n = min(max(blk - p.nbe, 0) * 16 + wr + 8 * i, p.N - 1);
             rowok[i] = true;
             rowp[i] = static_cast<const char *>(p.W) + (int64_t)n * p.ldw * (int64_t)sizeof(E);
         }
@@ -219,7 +219,8 @@ __global__ __launch_bounds__(MAXW * 64) void decode_stream_kernel(DecodeArgs p0)
     LORA_TS(p.trace, 3);  // stages consumed (MFMAs may still run)
     // acc[tb][e] = D[weight row blk * 16 + lg * 4 + e][token tb * 16 + li]: one contiguous KiB per 16-row token block, in it
     // 64 bytes (the block's 16 weight rows) per token
-    float4 *P4 = reinterpret_cast<float4 *>(p.P) + ((int64_t)(blk * p.ks + slice) * TBLK) * 64 + li * 4 + lg;
+    const int pblk = is_ext ? blk : blk + (p.nbe_cap - p.nbe);
+    float4 *P4 = reinterpret_cast<float4 *>(p.P) + ((int64_t)(pblk * p.ks + slice) * TBLK) * 64 + li * 4 + lg;
 #pragma unroll
     for (int tb = 0; tb < TBLK; ++tb)
         if (!MASKED || (keep >> tb & 1u)) P4[tb * 64] = make_float4(acc[tb][0], acc[tb][1], acc[tb][2], acc[tb][3]);
@@ -586,7 +587,7 @@ hipError_t init_stream() {
 // Lays the projections of a launch out in the two grids; returns the totals.
 void layout_sets(DecodeArgs &a, long *blocks_out, long *cols_out) {
     if (a.n_sets <= 0) {
-        *blocks_out = (long)a.nbe_cap + a.nbw;
+        *blocks_out = (long)a.nbe + a.nbw;
         *cols_out = a.nbw;
         return;
     }
@@ -594,7 +595,7 @@ void layout_sets(DecodeArgs &a, long *blocks_out, long *cols_out) {
     for (int i = 0; i < a.n_sets; ++i) {
         a.set[i].blk0 = (int32_t)blk;
         a.set[i].cb0 = (int32_t)cb;
-        blk += (long)a.nbe_cap + a.set[i].nbw;
+        blk += (long)a.nbe + a.set[i].nbw;
         cb += a.set[i].nbw;
     }
     *blocks_out = blk;
@@ -648,7 +649,7 @@ hipError_t launch_reduce_t(const DecodeArgs &a, hipStream_t stream, const Kernel
 }
 
 bool decode_args_ok(const DecodeArgs &a, int tblk) {
-    if (!(a.T > (tblk - 1) * 16 && a.T <= tblk * 16 && a.K > 0 && (a.K & 7) == 0 && a.nbe_cap >= 0 && a.X != nullptr &&
+    if (!(a.T > (tblk - 1) * 16 && a.T <= tblk * 16 && a.K > 0 && (a.K & 7) == 0 && a.nbe >= 0 && a.nbe <= a.nbe_cap && a.X != nullptr &&
           a.ks == (a.K / 8 + kDsSliceChunks - 1) / kDsSliceChunks && a.n_sets >= 0 && a.n_sets <= kMaxGemmSets))
         return false;
     if (a.n_sets == 0) return a.N > 0 && a.nbw == (a.N + 15) / 16 && a.P != nullptr && a.W != nullptr && a.Y != nullptr;

@@ -277,7 +277,8 @@ struct DecodeArgs {
     int32_t r_max;         // the plan's largest rank
     int32_t n_adapters;    // entries of the A / B / scale tables
     int32_t nbw;           // blocks of 16 rows of W0: ceil(N / 16)
-    int32_t nbe_cap;       // upper bound of the blocks of 16 extension rows (rows of the used A_a), which come first
+    int32_t nbe_cap;       // most blocks of 16 extension rows (rows of the used A_a) of any batch of the plan's sizes; they come first in P
+    int32_t nbe;           // those the grid has room for (at most nbe_cap)
     int32_t ks;            // slices of 512 along K
     int32_t waves;         // waves (= 16-row blocks) per workgroup of the streaming kernel
     long long *trace = nullptr;  // phase stamps (trace builds only)

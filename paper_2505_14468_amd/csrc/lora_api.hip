@@ -647,10 +647,25 @@ bool has_adapters(const lora_plan_t *plan, const lora_linear_desc *d) {
     return d->tbl != nullptr && plan->n_adapters > 0 && plan->r_max > 0;
 }
 
-// Upper bound of the plan's work units: sum over the adapter segments of ceil(rows / unit_rows).
-int64_t max_units_of(const lora_plan_t *plan) {
-    const int64_t segs = std::min<int64_t>(std::min<int64_t>(plan->n_adapters, plan->n_req), std::min<int64_t>(plan->T, plan->seg_cap));
-    return plan->T / plan->unit_rows + segs;
+// What the launches' grids have room for: work units -- sum over the adapter segments of ceil(rows / unit_rows) -- and ranks in
+// use, each by an upper bound.  Under stream capture it holds for every batch of the plan's sizes, because a captured launch may
+// be replayed after plan_buf has been filled for another one (nothing but grids depends on these bounds: workspace offsets
+// follow the sizes alone, and a captured stage may follow an eager one).  An eager launch is for this plan, of which
+// lora_plan() knows what it uses: no surplus workgroups (73 requests, a 7B decoder layer, 100 slots of up to rank 64: 237 -> 229 us).
+struct PlanBounds {
+    int64_t units, ext_rows;
+};
+PlanBounds bounds_of(const lora_plan_t *plan, hipStream_t stream) {
+    int64_t segs = std::min<int64_t>(std::min<int64_t>(plan->n_adapters, plan->n_req), plan->T);
+    int64_t ext_rows = segs * plan->r_max;
+    if (plan->seg_cap < segs || 8 * (int64_t)plan->ext_cap < ext_rows) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone) {
+            segs = std::min<int64_t>(segs, plan->seg_cap);
+            ext_rows = std::min<int64_t>(ext_rows, 8 * (int64_t)plan->ext_cap);
+        }
+    }
+    return PlanBounds{plan->T / plan->unit_rows + segs, ext_rows};
 }
 
 // Decode path: when the reduction's own expand -- every row gathers its adapter's B_a for the workgroup's 16 columns,
@@ -667,13 +682,13 @@ bool decode_adapters_heavy(const lora_ctx *ctx, const lora_plan_t *plan, const l
 
 // The two launches of the decode path share one argument block.  n > 1: several projections of the same X, their
 // blocks of weight rows side by side in the first launch's grid and their column blocks in the second's.
-DecodeArgs decode_args(const lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *const *descs, int n, const GemmChoice &c) {
+DecodeArgs decode_args(const lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, const lora_linear_desc *const *descs, int n,
+                       const GemmChoice &c) {
     const lora_linear_desc *d = descs[0];
     bool any_ad = false;
     for (int i = 0; i < n; ++i) any_ad = any_ad || has_adapters(plan, descs[i]);
-    // ranks the batch can use at most: one adapter per request, per slot, per row; those in use where the host built the plan
+    // ranks that a batch of these sizes can use at most: one adapter per request, per slot, per row
     const int64_t segs = std::min<int64_t>(std::min<int64_t>(plan->n_req, plan->n_adapters), plan->T);
-    const int64_t ext_rows = std::min<int64_t>(segs * plan->r_max, 8 * (int64_t)plan->ext_cap);
     DecodeArgs a;
     a.plan = view_of(plan);
     a.X = d->X;
@@ -686,7 +701,7 @@ DecodeArgs decode_args(const lora_ctx *ctx, const lora_plan_t *plan, const lora_
     for (int i = 0; i < n; ++i) {
         const lora_linear_desc *di = descs[i];
         const WorkspaceLayout w = workspace_layout(plan->T, di->K, di->N, plan->r_max, di->dtype);
-        const DecodeGeom g = decode_geom(plan->T, di->K, di->N, any_ad ? ext_rows : 0);
+        const DecodeGeom g = decode_geom(plan->T, di->K, di->N, any_ad ? segs * plan->r_max : 0);
         const bool ad = has_adapters(plan, di);
         DecodeSet &st = a.set[i];
         st.W = di->W0;
@@ -702,8 +717,9 @@ DecodeArgs decode_args(const lora_ctx *ctx, const lora_plan_t *plan, const lora_
         st.n_adapters = ad ? di->tbl->n_adapters : 0;
         st.blk0 = st.cb0 = st.fb0 = 0;
         a.nbe_cap = g.nbe_cap;
+        a.nbe = any_ad ? (int32_t)((pb.ext_rows + 15) / 16) : 0;
         a.ks = g.ks;
-        nblk += (long)g.nbe_cap + g.nbw;
+        nblk += (long)a.nbe + g.nbw;
     }
     const DecodeSet &s0 = a.set[0];  // (one projection: the launch's own fields)
     a.W = s0.W;
@@ -735,8 +751,8 @@ DecodeArgs decode_args(const lora_ctx *ctx, const lora_plan_t *plan, const lora_
 
 // The second launch of the decode path: sums the slices, adds V B_a, stores Y.  Projections with much adapter work go
 // through the finishing kernel, the others through the reduction: one launch of each at most.
-int do_decode_second(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *const *descs, int n, const DecodeArgs &a,
-                     const GemmChoice &c, hipStream_t stream) {
+int do_decode_second(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, const lora_linear_desc *const *descs, int n,
+                     const DecodeArgs &a, const GemmChoice &c, hipStream_t stream) {
     DecodeArgs part[2] = {a, a};  // [0] reduction, [1] finishing kernel
     int cnt[2] = {0, 0};
     for (int i = 0; i < n; ++i) {
@@ -751,29 +767,29 @@ int do_decode_second(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_d
         if (k == 0)
             LORA_HIP(launch_decode_reduce(part[k], c.tblk, stream, timed ? &timer : nullptr));
         else
-            LORA_HIP(launch_decode_finish(part[k], c.tblk, (int)max_units_of(plan), stream, timed ? &timer : nullptr));
+            LORA_HIP(launch_decode_finish(part[k], c.tblk, (int)pb.units, stream, timed ? &timer : nullptr));
     }
     return LORA_OK;
 }
 
-int do_decode(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *const *descs, int n, const GemmChoice &c,
-              hipStream_t stream) {
-    const DecodeArgs a = decode_args(ctx, plan, descs, n, c);
+int do_decode(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, const lora_linear_desc *const *descs, int n,
+              const GemmChoice &c, hipStream_t stream) {
+    const DecodeArgs a = decode_args(ctx, plan, pb, descs, n, c);
     KernelTimer t1;
     const bool timed1 = next_timer(ctx, kProfShrink, &t1);
     LORA_HIP(launch_decode_stream(a, c.tblk, stream, timed1 ? &t1 : nullptr));  // streams W0 and the used A_a against X
-    return do_decode_second(ctx, plan, descs, n, a, c, stream);
+    return do_decode_second(ctx, plan, pb, descs, n, a, c, stream);
 }
 
 // (multi: several projections of the same X that go through one launch)
-int do_shrink(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *d, hipStream_t stream,
+int do_shrink(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, const lora_linear_desc *d, hipStream_t stream,
               const lora_linear_desc *const *multi = nullptr, int n_multi = 0) {
     if (n_multi == 0) {
         const GemmChoice c = choose_gemm(ctx, plan->T, d->K, d->N, d->dtype);
         if (c.variant == kGemmDecode) {  // decode-sized: the first launch streams W0 and the used A_a against X
             KernelTimer timer;
             const bool timed = next_timer(ctx, kProfShrink, &timer);
-            LORA_HIP(launch_decode_stream(decode_args(ctx, plan, &d, 1, c), c.tblk, stream, timed ? &timer : nullptr));
+            LORA_HIP(launch_decode_stream(decode_args(ctx, plan, pb, &d, 1, c), c.tblk, stream, timed ? &timer : nullptr));
             return LORA_OK;
         }
     }
@@ -804,8 +820,7 @@ int do_shrink(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *d,
         a.set[i].n_adapters = adi ? di->tbl->n_adapters : 0;
         a.set[i].pad_ = 0;
     }
-    // units <= sum over segments of ceil(rows / unit_rows) <= T / unit_rows + number of adapter segments
-    a.max_units = ad ? (int32_t)max_units_of(plan) : 0;
+    a.max_units = ad ? (int32_t)pb.units : 0;
     // With few units (decode-sized batches) a unit's ranks are dealt to several workgroups: every A_a
     // is streamed once either way, and it takes most of the chip to stream them at HBM speed.
     const int64_t wide_groups = (plan->r_max + kShrinkRanks - 1) / kShrinkRanks;
@@ -840,7 +855,7 @@ int do_shrink(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *d,
 // (collect: several projections in one launch -- the expand kernel's arguments are gathered there, not launched)
 // (all_in_d: the whole adapter term through the expand kernel -- the caller has checked the workspace -- for a GEMM
 // that adds nothing itself)
-int prepare_set(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *d, int variant, hipStream_t stream,
+int prepare_set(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, const lora_linear_desc *d, int variant, hipStream_t stream,
                 const KernelTimer *expand_timer, GemmSet *out, bool *split_out, ExpandArgs *collect = nullptr,
                 bool all_in_d = false) {
     const WorkspaceLayout w = workspace_layout(plan->T, d->K, d->N, plan->r_max, d->dtype);
@@ -870,7 +885,7 @@ int prepare_set(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *
         e.ldd = (int64_t)w.ldd;
         e.r_max = plan->r_max;
         e.N = d->N;
-        e.max_units = (int32_t)max_units_of(plan);  // as for the shrink grid
+        e.max_units = (int32_t)pb.units;  // as for the shrink grid
         e.unit_rows = plan->unit_rows;
         e.col_groups = 0;
         // The tiled GEMM keeps the long segments' term to itself (an extension stage per 64 ranks of each such segment
@@ -904,10 +919,10 @@ int prepare_set(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *
     return LORA_OK;
 }
 
-int do_gemm(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *d, hipStream_t stream) {
+int do_gemm(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, const lora_linear_desc *d, hipStream_t stream) {
     GemmChoice c = choose_gemm(ctx, plan->T, d->K, d->N, d->dtype);
     if (c.variant == kGemmDecode)
-        return do_decode_second(ctx, plan, &d, 1, decode_args(ctx, plan, &d, 1, c), c, stream);
+        return do_decode_second(ctx, plan, pb, &d, 1, decode_args(ctx, plan, pb, &d, 1, c), c, stream);
     KernelTimer timer, etimer;
     const bool timed = next_timer(ctx, kProfGemm, &timer);
     const WorkspaceLayout w = workspace_layout(plan->T, d->K, d->N, plan->r_max, d->dtype);
@@ -918,7 +933,7 @@ int do_gemm(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *d, h
     if (sk.s > 1) c.variant = sk.variant;
     GemmSet g;
     bool split = false;
-    const int rc = prepare_set(ctx, plan, d, c.variant, stream, timed ? &etimer : nullptr, &g, &split, nullptr, sk.s > 1);
+    const int rc = prepare_set(ctx, plan, pb, d, c.variant, stream, timed ? &etimer : nullptr, &g, &split, nullptr, sk.s > 1);
     if (rc != LORA_OK) return rc;
     if (sk.s > 1) {  // partial products per stretch of K, then one launch that sums them, adds the adapter term and rounds
         GemmArgs a;
@@ -997,8 +1012,8 @@ int multi_kind(const lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_d
     return 1;
 }
 
-int do_gemm_multi(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *const *descs, int n, const GemmChoice &c,
-                  hipStream_t stream) {
+int do_gemm_multi(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, const lora_linear_desc *const *descs, int n,
+                  const GemmChoice &c, hipStream_t stream) {
     GemmArgs a;
     a.plan = view_of(plan);
     a.X = descs[0]->X;
@@ -1022,7 +1037,7 @@ int do_gemm_multi(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc
     e.n_sets = 0;
     for (int i = 0; i < n; ++i) {
         bool split = false;
-        const int rc = prepare_set(ctx, plan, descs[i], c.variant, stream, nullptr, &a.set[i], &split, &e);
+        const int rc = prepare_set(ctx, plan, pb, descs[i], c.variant, stream, nullptr, &a.set[i], &split, &e);
         if (rc != LORA_OK) return rc;
     }
     if (e.n_sets > 0) {  // one launch for every projection that takes it
@@ -1213,7 +1228,7 @@ int lora_plan(lora_ctx *ctx, const int32_t *req_adapter, const int32_t *req_ntok
         rc = build_plan(ctx, a, stream, out);
         if (rc != LORA_OK) return rc;
     }
-    // (the host knows what the batch uses: launches that are sized by these bounds get no surplus workgroups)
+    // (the host knows what the batch uses: see bounds_of)
     out->seg_cap = n_seg;
     out->ext_cap = (int32_t)(ext_total >> 3);
     return LORA_OK;
@@ -1263,7 +1278,8 @@ int lora_shrink(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *
     if (plan->T == 0) return LORA_OK;
     DeviceGuard guard(ctx->device);
     if (guard.err != hipSuccess) return hip_fail(guard.err);
-    return do_shrink(ctx, plan, desc, static_cast<hipStream_t>(stream));
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    return do_shrink(ctx, plan, bounds_of(plan, s), desc, s);
 }
 
 int lora_gemm_expand(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *desc, lora_stream_t stream) {
@@ -1273,7 +1289,7 @@ int lora_gemm_expand(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_d
     DeviceGuard guard(ctx->device);
     if (guard.err != hipSuccess) return hip_fail(guard.err);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    return do_gemm(ctx, plan, desc, s);
+    return do_gemm(ctx, plan, bounds_of(plan, s), desc, s);
 }
 
 int lora_linear(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *desc, lora_stream_t stream) {
@@ -1283,9 +1299,10 @@ int lora_linear(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *
     DeviceGuard guard(ctx->device);
     if (guard.err != hipSuccess) return hip_fail(guard.err);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    rc = do_shrink(ctx, plan, desc, s);
+    const PlanBounds pb = bounds_of(plan, s);
+    rc = do_shrink(ctx, plan, pb, desc, s);
     if (rc != LORA_OK) return rc;
-    return do_gemm(ctx, plan, desc, s);
+    return do_gemm(ctx, plan, pb, desc, s);
 }
 
 int lora_linear_static(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *desc, lora_stream_t stream) {
@@ -1306,9 +1323,10 @@ int lora_linear_static(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear
     DeviceGuard guard(ctx->device);
     if (guard.err != hipSuccess) return hip_fail(guard.err);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    rc = do_shrink(ctx, plan, &d, s);
+    const PlanBounds pb = bounds_of(plan, s);
+    rc = do_shrink(ctx, plan, pb, &d, s);
     if (rc != LORA_OK) return rc;
-    return do_gemm(ctx, plan, &d, s);
+    return do_gemm(ctx, plan, pb, &d, s);
 }
 
 int lora_linear_multi(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *const *descs, int32_t n,
@@ -1329,20 +1347,21 @@ int lora_linear_multi(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_
     DeviceGuard guard(ctx->device);
     if (guard.err != hipSuccess) return hip_fail(guard.err);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    const PlanBounds pb = bounds_of(plan, s);
     GemmChoice c;
     const int kind = n == 1 ? 0 : multi_kind(ctx, plan, descs, n, &c);
     if (kind == 0) {  // one after the other
         for (int i = 0; i < n; ++i) {
-            int rc = do_shrink(ctx, plan, descs[i], s);
-            if (rc == LORA_OK) rc = do_gemm(ctx, plan, descs[i], s);
+            int rc = do_shrink(ctx, plan, pb, descs[i], s);
+            if (rc == LORA_OK) rc = do_gemm(ctx, plan, pb, descs[i], s);
             if (rc != LORA_OK) return rc;
         }
         return LORA_OK;
     }
-    if (kind == 2) return do_decode(ctx, plan, descs, n, c, s);
-    const int rc = do_shrink(ctx, plan, descs[0], s, descs, n);  // one launch: the single projection's grid once per projection
+    if (kind == 2) return do_decode(ctx, plan, pb, descs, n, c, s);
+    const int rc = do_shrink(ctx, plan, pb, descs[0], s, descs, n);  // one launch: the single projection's grid once per projection
     if (rc != LORA_OK) return rc;
-    return do_gemm_multi(ctx, plan, descs, n, c, s);
+    return do_gemm_multi(ctx, plan, pb, descs, n, c, s);
 }
 
 int lora_profile_begin(lora_ctx *ctx, int max_launches) {

@@ -86,3 +86,62 @@ def test_captured_step_replays_bit_exact(case):
             assert torch.equal(g_bufs[1][q].view(torch.int16), e_bufs[1][q].view(torch.int16)), (case, trial, q)
         assert float(g_bufs[1][0].float().abs().max()) > 0
     reset_options()
+
+
+@pytest.mark.parametrize("case", ["decode", "decode_much_adapter_work", "prefill"])
+def test_captured_layers_follow_a_plan_rebuilt_by_lora_plan(case):
+    """Only the layers are captured, on a plan of one small adapter; lora_plan() then fills the same buffer, outside the graph,
+    for batches of the same sizes that use every adapter.  Each replay gives what eager calls on that plan give."""
+    from gpu_common import B, ctx, reset_options, rt
+    reset_options()
+    c = ctx()
+    dev = c.device
+    K, N, T = 520, 1544, 64 if case != "prefill" else 300
+    n_ad, r = 24, 128 if case == "decode_much_adapter_work" else 16
+    ranks = np.full(n_ad, r, np.int32)
+    ranks[0] = 8
+    wl = make_custom(seed=971, dtype="bf16", K=K, N=N, ranks=ranks, scales=np.linspace(0.5, 2.0, n_ad), req_adapter=np.zeros(T, int),
+                     req_ntok=np.ones(T, int), name=f"replan_{case}")
+    X, W0, table = rt.upload_workload(wl, 0, dev)
+    rng = np.random.default_rng(8)
+    batches = [np.zeros(T, int), rng.integers(-1, n_ad, T), np.arange(T) % n_ad, np.full(T, -1)]
+    buf = torch.empty(B.lora_plan_bytes(T, T, n_ad, r), dtype=torch.uint8, device=dev)
+    pl = rt.plan(c, batches[0], np.ones(T, int), ranks, r, buf=buf)
+    Y, Ym, Ys = (torch.zeros((T, N), dtype=X.dtype, device=dev) for _ in range(3))
+    ws = [rt.workspace(T, K, N, r, X.dtype, dev) for _ in range(3)]
+    d = [rt.linear_desc(pl, X, W0, y, table, w) for y, w in zip((Y, Ym, Ys), ws)]
+    side = torch.cuda.Stream()
+
+    def layers():
+        st = torch.cuda.current_stream().cuda_stream
+        B.lora_linear(c.handle, pl.struct, d[0], st)
+        B.lora_linear_multi(c.handle, pl.struct, [d[1], d[2]], st)
+
+    def staged(first):  # the first stage eagerly, the second from its own graph
+        st = torch.cuda.current_stream().cuda_stream
+        (B.lora_shrink if first else B.lora_gemm_expand)(c.handle, pl.struct, d[0], st)
+
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        layers()
+    side.synchronize()
+    graph, second = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        layers()
+    with torch.cuda.graph(second, stream=side):
+        staged(False)
+    for ids in batches[1:] + batches[:1]:
+        now = rt.plan(c, ids, np.ones(T, int), ranks, r, buf=buf)
+        for y in (Y, Ym, Ys):
+            y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        want = rt.linear(c, now, X, W0, table)
+        for y in (Y, Ym, Ys):
+            assert torch.equal(y.view(torch.int16), want.view(torch.int16)), (case, ids[:8])
+        Y.fill_(float("nan"))
+        B.lora_shrink(c.handle, now.struct, d[0], torch.cuda.current_stream().cuda_stream)
+        second.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y.view(torch.int16), want.view(torch.int16)), (case, ids[:8])
+    reset_options()
