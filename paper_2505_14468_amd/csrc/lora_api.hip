@@ -828,11 +828,13 @@ int do_shrink(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, cons
     // (every rank block of a unit reads the unit's rows of X again: only worth it while X is small)
     const bool small_x = plan->T <= 256;
     // A unit of at most 16 rows reads little of X beside its ranks' rows of A_a, so its ranks are dealt out as finely as keeps
-    // one workgroup per CU (365 rows on 14 adapters of rank 16 and 32, K = 11008: 32 workgroups, 23.4 us, as one block of
-    // 32 ranks, 15-16 us as blocks of 8).
+    // one workgroup per CU, the workgroups of all projections counted (365 rows on 14 adapters of rank 16 and 32, K = 11008: 32
+    // workgroups, 23.4 us, as one block of 32 ranks, 15-16 us as blocks of 8; 700 rows on 16 adapters of rank 16, three
+    // projections of 4096 -> 4096: the layer 110 us with 354 workgroups, two blocks of 8 ranks each, 105 with 177).
     int fine = 0;
+    const int64_t unit_sets = (int64_t)a.max_units * std::max(n_multi, 1);
     if (plan->unit_rows == kShrinkRowsSmall)
-        for (int rb = 32; rb >= 8 && a.max_units * (((int64_t)plan->r_max + rb - 1) / rb) <= (int64_t)ctx->num_cu; rb /= 2) fine = rb;
+        for (int rb = 32; rb >= 8 && unit_sets * (((int64_t)plan->r_max + rb - 1) / rb) <= (int64_t)ctx->num_cu; rb /= 2) fine = rb;
     int rank_block = !ad                                                  ? kShrinkRanks
                      : !small_x ? (fine > 0 ? fine : a.max_units * wide_groups < (int64_t)ctx->num_cu && plan->r_max > 32 ? 32 : kShrinkRanks)
                      : a.max_units * mid_groups < 2 * (int64_t)ctx->num_cu  ? 8

@@ -40,3 +40,28 @@ def test_captured_launches_have_room_for_every_batch_of_the_same_sizes(fake, T, 
         area = lambda launches: sum(g[0] * g[1] * g[2] for _, g, _ in launches)
         assert all(area(e) <= area(c) for e, c in zip(grids(one), captured))
     """)
+
+
+@pytest.mark.parametrize("T,rank,sets,block", [(700, 16, 1, 8), (700, 16, 3, 16), (400, 64, 1, 16), (400, 64, 3, 32), (1216, 16, 2, 16)])
+def test_shrink_rank_blocks_count_every_projection(fake, T, rank, sets, block):
+    """Above 256 rows a unit's ranks are dealt out while the launch, all its projections together, has at most a workgroup per CU."""
+    fake_hip.run(fake, f"""
+        T, rank, sets, block = {T}, {rank}, {sets}, {block}
+        plan = make_plan(np.arange(16), np.diff(np.linspace(0, T, 17).astype(int)), np.full(16, rank))
+        assert plan.unit_rows == 16
+        d = [make_desc(plan, 4096, 4096) for _ in range(sets)]
+        for v in d:
+            v.X = d[0].X
+
+        def shrink():
+            F.fake_reset()
+            B.lora_linear_multi(ctx, plan, d, 0)
+            return [l for l in launched() if "shrink_kernel" in l[0]]
+
+        chosen = shrink()
+        assert len(chosen) == 1
+        B.lora_ctx_set_option(ctx, "shrink_rank_block", block)
+        assert chosen == shrink()
+        B.lora_ctx_set_option(ctx, "shrink_rank_block", 8)
+        assert (chosen == shrink()) == (block == 8)
+    """)
