@@ -166,10 +166,11 @@ int lora_ctx_destroy(lora_ctx *ctx);
  * the decode path), "plan_variant" (1: never the one-lane-per-request
  * plan kernels), "plan_fused_rows" (most rows for which one workgroup builds
  * the whole plan), "expand_split" (0 / 1: adapter term always computed inside
- * the GEMM / by the separate expand kernel whenever the workspace has room
- * for it), "gemm_split_k" (0: never split the tiled GEMM along K),
+ * the GEMM or the decode path's reduction / by the separate expand kernel or the
+ * decode path's finishing kernel whenever the workspace has room for the term), "gemm_split_k" (0: never split the tiled GEMM along K),
  * "shrink_rank_block" (8 / 16 / 32 / 64).  value < 0 restores the
- * built-in choice.  Results never depend on them beyond fp32 summation order.
+ * built-in choice.  Results never depend on them beyond fp32 summation order
+ * and, for "expand_split" on the decode path, the rounding of V to bf16.
  * Not thread-safe against concurrent calls on the same ctx.  Errors:
  * INVALID_ARG for an unknown name or a value the option does not take. */
 int lora_ctx_set_option(lora_ctx *ctx, const char *name, int value);
@@ -240,9 +241,11 @@ size_t lora_linear_workspace_bytes(int64_t T, int32_t K, int32_t N, int32_t r_ma
  * above plus room for the adapter term in fp32 ([T, N]; bf16 batches of any
  * size, fp32 ones of more than 128 rows).  Batches of many small segments
  * then compute that term in a weight-streaming kernel of its own and the GEMM
- * adds it before the single rounding of Y; with a smaller
- * workspace the term is computed inside the GEMM (same
- * result within the rounding of the intermediate V and fp32 summation order).  For batches of 129 to
+ * adds it before the single rounding of Y, and decode-sized bf16 batches with
+ * much adapter work stream every used B_a once against V in bf16; with a
+ * smaller workspace the term is computed inside the GEMM, or the decode path's
+ * reduction with V in fp32 (same result within the rounding of the
+ * intermediate V and fp32 summation order).  For batches of 129 to
  * 1024 rows whose output tiles would leave most of the chip idle (and larger
  * ones with K >= 10240 into few columns) it also has
  * room for the fp32 partial outputs of a GEMM split along K (2 to 8 copies
@@ -266,8 +269,8 @@ int lora_shrink(lora_ctx *ctx, const lora_plan_t *plan, const lora_linear_desc *
  * X) taken from the workspace as lora_shrink() left them for the same plan,
  * desc->X and K (decode-sized bf16 batches: sums the partial sums lora_shrink()
  * left, adds V B_a in fp32 -- V never rounded -- and stores Y; with much
- * adapter work V is rounded to bf16 and the launch streams every used B_a
- * once, work unit by work unit).  Otherwise two forms, same result up
+ * adapter work and a workspace of the preferred size V is rounded to bf16 and
+ * the launch streams every used B_a once, work unit by work unit).  Otherwise two forms, same result up
  * to fp32 summation order: the expand
  * as extra K-steps of the GEMM's own MFMA loop (always, with a workspace of the
  * minimal size; and for segments of 64 rows and more up to rank 64), or -- with

@@ -52,3 +52,31 @@ def test_one_call_with_projections_of_both_kinds():
         got = rt.bits_from_tensor(outs[q])
         assert np.array_equal(got, rt.bits_from_tensor(rt.linear(c, pl, up[0][0], u[1], u[2])))
         check_against_oracle(wl, to_f64(got), p=q)
+
+
+def test_v_is_not_rounded_with_a_workspace_below_the_preferred_size():
+    """Much adapter work and a minimal workspace: with small integers every sum is exact in fp32 while V needs more bits than bf16
+    has (|V| up to several hundred), so Y is the exact result rounded once, bit for bit."""
+    import torch
+    from gpu_common import ctx, reset_options, rt
+    from oracle import oracle_workload
+    from workloads import bf16_bits_from_f32
+    reset_options()
+    c = ctx()
+    T, K, N = 64, 520, 1544
+    wl = make_custom(seed=3200, dtype="bf16", K=K, N=N, ranks=(128,) * 64, scales=(1.0,) * 64, req_adapter=np.arange(T),
+                     req_ntok=np.ones(T, np.int64), name="finish_minimal", integer_valued=True)
+    want = bf16_bits_from_f32(oracle_workload(wl).astype(np.float32))
+    X, W0, table = rt.upload_workload(wl, 0, c.device)
+    pl = rt.plan(c, wl.req_adapter, wl.req_ntok, wl.ranks)
+    ws = [rt.workspace(T, K, N, pl.r_max, X.dtype, c.device, minimal=True) for _ in range(2)]
+    Ys = [torch.empty((T, N), dtype=X.dtype, device=c.device) for _ in range(2)]
+    rt.linear(c, pl, X, W0, table, Y=Ys[0], ws=ws[0])
+    assert np.array_equal(rt.bits_from_tensor(Ys[0]), want)
+    d = [rt.linear_desc(pl, X, W0, y, table, w) for y, w in zip(Ys, ws)]
+    for y in Ys:
+        y.fill_(float("nan"))
+    rt.B.lora_linear_multi(c.handle, pl.struct, d, torch.cuda.current_stream().cuda_stream)
+    for y in Ys:
+        assert np.array_equal(rt.bits_from_tensor(y), want)
+    reset_options()

@@ -65,3 +65,27 @@ def test_shrink_rank_blocks_count_every_projection(fake, T, rank, sets, block):
         B.lora_ctx_set_option(ctx, "shrink_rank_block", 8)
         assert (chosen == shrink()) == (block == 8)
     """)
+
+
+def test_finishing_kernel_only_with_a_workspace_of_the_preferred_size(fake):
+    """The decode path's finishing kernel rounds V to bf16; calls with less workspace keep the reduction, whose V is fp32."""
+    fake_hip.run(fake, """
+        plan = make_plan(np.arange(64), np.ones(64, int), np.full(64, 128))
+        K, N = 520, 1544
+        pref = B.lora_linear_workspace_bytes_preferred(64, K, N, 128, 1)
+        least = B.lora_linear_workspace_bytes(64, K, N, 128, 1)
+        assert least < pref
+
+        def second(calls):
+            F.fake_reset()
+            calls()
+            return ["finish" if "decode_finish" in l[0] else "reduce" for l in launched() if "decode_stream" not in l[0]]
+
+        for size, want in ((pref, "finish"), (pref - 1, "reduce"), (least, "reduce")):
+            d = make_desc(plan, K, N, ws_bytes=size)
+            assert second(lambda: B.lora_linear(ctx, plan, d, 0)) == [want]
+            assert second(lambda: B.lora_gemm_expand(ctx, plan, d, 0)) == [want]
+        both = [make_desc(plan, K, N, ws_bytes=least), make_desc(plan, K, N, ws_bytes=pref)]
+        both[1].X = both[0].X
+        assert second(lambda: B.lora_linear_multi(ctx, plan, both, 0)) == ["reduce", "finish"]
+    """)
