@@ -511,10 +511,14 @@ struct WorkspaceLayout {
 struct SplitK {
     int s, k_chunk, variant;
 };
-SplitK choose_split_k(int64_t T, int32_t K, int32_t N, int32_t dtype) {
+// (room: bytes for the partial outputs.  A workspace kept for another shape may have room for some: fewer stretches still beat
+// none when K is long -- 13824 -> 5120, 160 rows: 64 us per layer with six, 66 with five, 73 with three, 109 unsplit; 11008 -> 4096, 300
+// rows: 77 with two, 99 unsplit -- and lose below 8192 -- 4096 -> 4096, 256 rows: 37-39 with three and two, 32 unsplit)
+SplitK choose_split_k(int64_t T, int32_t K, int32_t N, int32_t dtype, size_t room = SIZE_MAX) {
     SplitK r{1, 0, kGemmTile128x128};
     if (T <= kDecodeMaxRows) return r;  // (the decode path, or a batch too small to matter)
     const int stage = dtype == LORA_DTYPE_BF16 ? 64 : 32;
+    const size_t one = (size_t)T * align_up((size_t)N, 8) * sizeof(float);  // bytes of one partial output
     int64_t s = 0;
     if (T <= 1024 && dtype == LORA_DTYPE_BF16) {
         // Mid-sized batches.  As many stretches of K as fit one round of at most one workgroup per CU, on 128x128 or on
@@ -531,7 +535,8 @@ SplitK choose_split_k(int64_t T, int32_t K, int32_t N, int32_t dtype) {
             if (v && (K < 4096 || (K < 8192 && T > 384))) continue;
             const int64_t tiles = ((T + bm - 1) / bm) * (((int64_t)N + 127) / 128);
             if (tiles > 96 && K < 4096) continue;
-            const int64_t sv = std::min<int64_t>(std::min<int64_t>(256 / tiles, 8), K / (16 * stage));  // (256: the part's CUs)
+            int64_t sv = std::min<int64_t>(std::min<int64_t>(256 / tiles, 8), K / (16 * stage));  // (256: the part's CUs)
+            if (K >= 8192) sv = std::min<int64_t>(sv, (int64_t)std::min<size_t>(room / one, 8));
             if (sv < 2) continue;
             const double cost = (v ? 0.45 : 0.36) * (double)((K / stage + sv - 1) / sv) + (double)sv * (double)T * (double)N * 1.6e-6;
             if (s < 2 || cost < best) {
@@ -560,7 +565,7 @@ SplitK choose_split_k(int64_t T, int32_t K, int32_t N, int32_t dtype) {
     if (s < 2) return SplitK{1, 0, kGemmTile128x128};
     r.k_chunk = (int)(((K + s - 1) / s + stage - 1) / stage * stage);
     r.s = (K + r.k_chunk - 1) / r.k_chunk;
-    if (r.s < 2) r = SplitK{1, 0, kGemmTile128x128};
+    if (r.s < 2 || (size_t)r.s * one > room) r = SplitK{1, 0, kGemmTile128x128};
     return r;
 }
 
@@ -874,7 +879,7 @@ int prepare_set(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, co
     g.B = ad ? d->tbl->B : nullptr;
     g.N = d->N;
     bool split = false;
-    if (ad && w.d_bytes > 0 && d->workspace_bytes >= w.total_preferred) {
+    if (ad && w.d_bytes > 0 && (all_in_d || d->workspace_bytes >= w.total_preferred)) {
         const int64_t segs = plan->n_adapters < plan->n_req ? plan->n_adapters : plan->n_req;  // upper bound
         split = segs > 0 && plan->T / segs < 64;
         if (ctx->opt_expand_split >= 0) split = ctx->opt_expand_split == 1;
@@ -930,9 +935,9 @@ int do_gemm(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, const 
     KernelTimer timer, etimer;
     const bool timed = next_timer(ctx, kProfGemm, &timer);
     const WorkspaceLayout w = workspace_layout(plan->T, d->K, d->N, plan->r_max, d->dtype);
-    SplitK sk = choose_split_k(plan->T, d->K, d->N, d->dtype);
+    SplitK sk = choose_split_k(plan->T, d->K, d->N, d->dtype, d->workspace_bytes > w.sk_off ? d->workspace_bytes - w.sk_off : 0);
     if (ctx->opt_gemm_split_k == 0 || (ctx->opt_gemm_variant >= 0 && ctx->opt_gemm_variant != sk.variant) ||
-        d->workspace_bytes < w.total_preferred || (has_adapters(plan, d) && w.d_bytes == 0))
+        (has_adapters(plan, d) && w.d_bytes == 0))
         sk = SplitK{1, 0, kGemmTile128x128};
     if (sk.s > 1) c.variant = sk.variant;
     GemmSet g;

@@ -63,3 +63,28 @@ def test_adapters(T, expand_split):
     ctx().set_option("expand_split", expand_split)
     check_against_oracle(wl, gpu_linear(wl))
     reset_options()
+
+
+@pytest.mark.parametrize("T,K,N", [(150, 8264, 4097), (250, 8200, 2816), (129, 4104, 1000)])
+def test_fewer_stretches_in_a_smaller_workspace(T, K, N):
+    """A workspace with room for some of the partial outputs only, down to none: exact sums rounded once, whatever the split."""
+    from gpu_common import B, ctx, reset_options, rt
+    import torch
+    from oracle import oracle_workload
+    from workloads import bf16_bits_from_f32
+    reset_options()
+    c = ctx()
+    ids, lens = _batch(T + K, T)
+    wl = make_custom(seed=900 + T, dtype="bf16", K=K, N=N, ranks=RANKS, scales=(0.5, 0.25, 1.0, 0.125, 2.0), req_adapter=np.full_like(ids, -1),
+                     req_ntok=lens, name=f"fewer_{T}_{K}_{N}", integer_valued=True)
+    want = bf16_bits_from_f32(oracle_workload(wl).astype(np.float32))
+    name = B.lora_gemm_kernel_name(c.handle, T, K, N, 1)
+    assert "splitk" in name
+    X, W0, table = rt.upload_workload(wl, 0, c.device)
+    pl = rt.plan(c, wl.req_adapter, wl.req_ntok, wl.ranks)
+    size = B.lora_linear_workspace_bytes_preferred(T, K, N, pl.r_max, 1)
+    one = T * ((N + 7) // 8 * 8) * 4
+    for less in range(int(name.rpartition("splitk")[2]) + 1):
+        ws = torch.empty(size - less * one, dtype=torch.uint8, device=c.device)
+        Y = rt.linear(c, pl, X, W0, table, ws=ws)
+        assert np.array_equal(rt.bits_from_tensor(Y), want), less

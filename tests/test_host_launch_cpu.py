@@ -89,3 +89,41 @@ def test_finishing_kernel_only_with_a_workspace_of_the_preferred_size(fake):
         both[1].X = both[0].X
         assert second(lambda: B.lora_linear_multi(ctx, plan, both, 0)) == ["reduce", "finish"]
     """)
+
+
+@pytest.mark.parametrize("K,N", [(11008, 4096), (4096, 4096), (13824, 5120)])
+@pytest.mark.parametrize("kept", [768, 1024, 2048, "static"])
+def test_kept_workspace_is_used_for_what_it_has_room_for(fake, K, N, kept):
+    """A workspace kept for a larger batch (or the static one): the split along K takes as many stretches as there is room for
+    behind the adapter term, at most as many as with a workspace of the preferred size, and below K = 8192 those or none."""
+    fake_hip.run(fake, f"""
+        K, N, kept = {K}, {N}, {kept!r}
+        size = (32 << 20) if kept == "static" else B.lora_linear_workspace_bytes_preferred(kept, K, N, 16, 1)
+        seen = set()
+        for T in (160, 256, 300, 385, 450, 512, 576, 640, 700, 768, 1000):
+            plan = make_plan(np.arange(16), np.diff(np.linspace(0, T, 17).astype(int)), np.full(16, 16))
+            term = T * N * 4
+            before = (B.lora_linear_workspace_bytes(T, K, N, 16, 1) + 255) // 256 * 256
+            F.fake_reset()
+            if kept == "static":
+                d = make_desc(plan, K, N, ws_bytes=0)
+                B.lora_linear_static(ctx, plan, d, 0)
+            elif before > size:
+                continue
+            else:
+                B.lora_linear(ctx, plan, make_desc(plan, K, N, ws_bytes=size), 0)
+            names = [l[0] for l in launched()]
+            tile = [l for l in launched() if "gemm_tile_kernel" in l[0]]
+            assert len(tile) == 1
+            got = tile[0][1][1]
+            best = B.lora_gemm_kernel_name(ctx, T, K, N, 1).rpartition("splitk")
+            most = int(best[2]) if best[1] else 1
+            room = max(size - before - term, 0) // term
+            if K < 8192 and room < most:
+                room = 0
+            assert got <= max(min(most, room), 1) and (got > 1) == (most > 1 and room > 1), (T, got, most, room)
+            assert any("splitk_reduce" in n for n in names) == (got > 1)
+            assert any("expand_kernel" in n for n in names) == (got > 1 or size >= B.lora_linear_workspace_bytes_preferred(T, K, N, 16, 1))
+            seen.add((got > 1, got < most))
+        assert seen
+    """)
