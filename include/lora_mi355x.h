@@ -163,9 +163,10 @@ int lora_ctx_destroy(lora_ctx *ctx);
  * 4 the decode path (bf16, up to 128 rows), 5 256x256 on 4 waves,
  * 9 128x192, 10 256x192, 11 256x224), "decode_waves" (waves per workgroup of
  * the decode path's streaming kernel: 8..12), "decode_max_rows" (0: never
- * the decode path), "plan_variant" (1: never the one-lane-per-request
- * plan kernels), "plan_fused_rows" (most rows for which one workgroup builds
- * the whole plan), "expand_split" (0 / 1: adapter term always computed inside
+ * the decode path), "plan_variant" (the device's plan builders, also where
+ * lora_plan() would hand it a table: 0: picked by size, 1: never the
+ * one-lane-per-request kernels), "plan_fused_rows" (the same builders: most
+ * rows for which one workgroup builds the whole plan), "expand_split" (0 / 1: adapter term always computed inside
  * the GEMM or the decode path's reduction / by the separate expand kernel or the
  * decode path's finishing kernel whenever the workspace has room for the term), "gemm_split_k" (0: never split the tiled GEMM along K),
  * "shrink_rank_block" (8 / 16 / 32 / 64).  value < 0 restores the

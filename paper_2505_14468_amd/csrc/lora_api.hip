@@ -1195,9 +1195,11 @@ int lora_plan(lora_ctx *ctx, const int32_t *req_adapter, const int32_t *req_ntok
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     LORA_HIP(hipStreamIsCapturing(stream, &capturing));
     // The host's table for the batches one workgroup can serve; the arrays themselves and the device's own builders for
-    // larger ones, under stream capture (nothing runs that would report the table read) and while every table waits to be read.
+    // larger ones, under stream capture (nothing runs that would report the table read), while every table waits to be read, and
+    // when an option asks for one of those builders.
     bool built = false;
-    if (n_req <= kApplyReq && T_expected <= kApplyRows && ext_total <= 8 * kApplyRows && capturing == hipStreamCaptureStatusNone) {
+    const bool asked = ctx->opt_plan_variant >= 0 || ctx->opt_plan_fused_rows >= 0;
+    if (!asked && n_req <= kApplyReq && T_expected <= kApplyRows && ext_total <= 8 * kApplyRows && capturing == hipStreamCaptureStatusNone) {
         std::lock_guard<std::mutex> lock(ctx->ring_mutex);
         const int slot = take_table(ctx);
         if (slot >= 0) {

@@ -17,6 +17,18 @@ def test_plan_from_host_arrays_at_the_edges(R, T, n_ad):
     _check_plan(ids, L, rng.choice([8, 16, 64], n_ad), False)
 
 
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("R", [1, 64, 65, 128, 300])
+def test_host_arrays_through_the_device_s_builders(R, variant):
+    """The upload and the builders behind it, which larger batches and stream capture take: mixed keys, and the same key in every
+    lane of a wave."""
+    rng = np.random.default_rng(R)
+    ranks = rng.choice([8, 16, 64], 50)
+    _check_plan(rng.integers(-1, 50, R), rng.integers(0, 4, R), ranks, False, plan_variant=variant)
+    _check_plan(np.full(R, 7), np.ones(R, int), ranks, False, plan_variant=variant)
+    _check_plan(np.full(R, -1), np.ones(R, int), ranks, False, plan_variant=variant)
+
+
 def test_rank_axis_longer_than_one_workgroup_serves():
     _check_plan(np.arange(300), np.ones(300, int), np.full(300, 512), False)      # 19200 records: beyond the table's limit
     _check_plan(np.arange(256), np.ones(256, int), np.full(256, 512), False)      # 16384: at it

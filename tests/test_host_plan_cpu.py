@@ -112,3 +112,26 @@ def test_host_table_against_the_reference(fake):
                 units = np.where(ref["seg_adapter"] >= 0, -(-rows // plan.unit_rows), 0)
                 assert np.array_equal(tab[at : at + S + 1], np.concatenate([[0], np.cumsum(units)]))
     """)
+
+
+def test_options_and_capture_reach_the_device_s_builders(fake):
+    """lora_plan() with "plan_variant" or "plan_fused_rows" set, or under stream capture, uploads the arrays and launches the builders
+    that lora_plan_device() launches; otherwise the table's kernel."""
+    fake_hip.run(fake, """
+        def kernels(R, option=None, value=-1, capturing=0):
+            F.fake_reset()
+            if option:
+                B.lora_ctx_set_option(ctx, option, value)
+            say("capturing", capturing)
+            make_plan(np.arange(R) % 7, np.ones(R, int), np.full(7, 8))
+            if option:
+                B.lora_ctx_set_option(ctx, option, -1)
+            return [next(k for k in ("apply", "tiny", "mid", "small", "segments", "fill") if f"plan_{k}_kernel" in l[0]) for l in launched()]
+
+        for R, by_size in ((5, "tiny"), (64, "tiny"), (100, "mid"), (300, "small")):
+            assert kernels(R) == ["apply"]
+            assert kernels(R, "plan_variant", 0) == [by_size] == kernels(R, capturing=1)
+            assert kernels(R, "plan_variant", 1) == ["small"]
+            assert "apply" not in kernels(R, "plan_fused_rows", 0) and kernels(R, "plan_fused_rows", 0)[-1] == "fill"
+            assert kernels(R) == ["apply"]
+    """)
