@@ -161,19 +161,20 @@ int lora_ctx_destroy(lora_ctx *ctx);
 /* Overrides of the built-in kernel choices, for tests and measurements:
  * "gemm_variant" (0 tile 128x128, 1 256x128, 3 64x64,
  * 4 the decode path (bf16, up to 128 rows), 5 256x256 on 4 waves,
- * 9 128x192, 10 256x192, 11 256x224), "decode_waves" (waves per workgroup of
- * the decode path's streaming kernel: 8..12), "decode_max_rows" (0: never
- * the decode path), "plan_variant" (the device's plan builders, also where
- * lora_plan() would hand it a table: 0: picked by size, 1: never the
+ * 9 128x192, 10 256x192, 11 256x224, 12 192x128), "decode_waves" (waves per
+ * workgroup of the decode path's streaming kernel: 8..12), "decode_max_rows"
+ * (0: never the decode path), "plan_variant" (the device's plan builders, also
+ * where lora_plan() would hand it a table: 0: picked by size, 1: never the
  * one-lane-per-request kernels), "plan_fused_rows" (the same builders: most
- * rows for which one workgroup builds the whole plan), "expand_split" (0 / 1: adapter term always computed inside
- * the GEMM or the decode path's reduction / by the separate expand kernel or the
- * decode path's finishing kernel whenever the workspace has room for the term), "gemm_split_k" (0: never split the tiled GEMM along K),
- * "shrink_rank_block" (8 / 16 / 32 / 64).  value < 0 restores the
- * built-in choice.  Results never depend on them beyond fp32 summation order
- * and, for "expand_split" on the decode path, the rounding of V to bf16.
- * Not thread-safe against concurrent calls on the same ctx.  Errors:
- * INVALID_ARG for an unknown name or a value the option does not take. */
+ * rows for which one workgroup builds the whole plan), "expand_split" (0 / 1:
+ * adapter term always computed inside the GEMM or the decode path's reduction /
+ * by the separate expand kernel or the decode path's finishing kernel with
+ * every workspace of the preferred size), "gemm_split_k" (0: never split the
+ * tiled GEMM along K), "shrink_rank_block" (8 / 16 / 32 / 64).  value < 0
+ * restores the built-in choice.  Results never depend on them beyond fp32
+ * summation order and, for "expand_split" on the decode path, the rounding of
+ * V to bf16.  Not thread-safe against concurrent calls on the same ctx.
+ * Errors: INVALID_ARG for an unknown name or a value the option does not take. */
 int lora_ctx_set_option(lora_ctx *ctx, const char *name, int value);
 
 /* ---- step a1: segment / indptr builder ---------------------------------- */

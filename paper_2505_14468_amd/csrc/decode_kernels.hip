@@ -508,7 +508,7 @@ __device__ __forceinline__ void finish_unit(const DecodeArgs &p, const __bf16 *B
 }
 
 template <int TBLK>
-__global__ __launch_bounds__(kFinWaves * 64, 4) void decode_finish_kernel(DecodeArgs p0, int units_cap, int bare_cap) {
+__global__ __launch_bounds__(kFinWaves * 64, 4) void decode_finish_kernel(DecodeArgs p0, int units_cap) {
     typedef __bf16 E;
     __shared__ __attribute__((aligned(16))) chunk_t vs[kFinRows * (kMaxRank / 8 + 1)];
     __shared__ __attribute__((aligned(16))) float tile[kFinRows * kFinTile];
@@ -570,7 +570,7 @@ hipError_t launch_finish_t(const DecodeArgs &a0, int units_cap, hipStream_t stre
         grid = (long)(units_cap + bare_cap) * ((a.N + kFinCols - 1) / kFinCols);
     }
     if (grid <= 0) return hipSuccess;
-    return launch_kernel(decode_finish_kernel<TBLK>, dim3((unsigned)grid), dim3(kFinWaves * 64), 0, stream, timer, a, units_cap, bare_cap);
+    return launch_kernel(decode_finish_kernel<TBLK>, dim3((unsigned)grid), dim3(kFinWaves * 64), 0, stream, timer, a, units_cap);
 }
 
 template <int TBLK, int MAXW>

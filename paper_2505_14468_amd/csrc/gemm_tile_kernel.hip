@@ -596,6 +596,10 @@ hipError_t init_tile() {
     }
     return e;
 }
+// fp32 is split along K on 128x128 and 256x256 tiles only.
+template <typename E>
+constexpr bool kSplit192 = sizeof(E) == 2;
+
 template <typename E>
 hipError_t init_tiles() {
     hipError_t e = init_tile<E, 64, 64, 2, 2>();
@@ -605,7 +609,7 @@ hipError_t init_tiles() {
     if (e == hipSuccess) e = init_tile<E, 128, 192, 2, 2>();
     if (e == hipSuccess) e = init_tile<E, 256, 192, 2, 2>();
     if (e == hipSuccess) e = init_tile<E, 256, 224, 4, 1>();
-    if (e == hipSuccess) e = init_tile<E, 192, 128, 2, 2, true>();
+    if (e == hipSuccess) e = init_tile<E, 192, 128, 2, 2, kSplit192<E>>();
     return e;
 }
 
@@ -627,7 +631,7 @@ hipError_t launch_variant(const GemmArgs &a, int variant, hipStream_t stream, co
         case kGemmTile256x224:
             return launch_tile<E, 256, 224, 4, 1>(a, stream, timer);
         case kGemmTile192x128:
-            return launch_tile<E, 192, 128, 2, 2, true>(a, stream, timer);
+            return launch_tile<E, 192, 128, 2, 2, kSplit192<E>>(a, stream, timer);
         default:
             return hipErrorInvalidValue;
     }
