@@ -28,7 +28,7 @@ def test_captured_step_replays_bit_exact(case):
         L = [70, 1, 9, 64, 90, 33, 1, 17]
         K = 2312
         assert "splitk" in B.lora_gemm_kernel_name(c.handle, sum(L), K, Ns[0], 1)
-    else:  # 64 one-token requests on adapters of rank 128: V, expand kernel and the adding launch behind the stream
+    else:  # 64 one-token requests on adapters of rank 128: the finishing kernel behind the stream
         ids = [i % 8 for i in range(64)]
         L = [1] * 64
         K, Ns, ranks = 520, (1544, 1536), (128,) * 8

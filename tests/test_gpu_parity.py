@@ -639,9 +639,9 @@ def test_strided_inputs_and_adapter_eviction():
 
 
 @pytest.mark.parametrize("T", [5, 40, 100, 128])
-def test_decode_path_adapter_term_through_the_expand_kernel(T):
-    """Decode-sized batches with much adapter work: V reduced by a launch of its own, the term by the expand kernel,
-    added by the reduction -- against the oracle and against the reduction's own expand, forced either way."""
+def test_decode_path_adapter_term_through_the_finishing_kernel(T):
+    """Decode-sized batches with much adapter work: V, adapter term and sum by the finishing kernel, work unit by work
+    unit -- against the oracle and against the reduction's own expand, forced either way."""
     from gpu_common import ctx, gpu_linear, check_against_oracle, reset_options, TOL
     reset_options()
     rng = np.random.default_rng(40 + T)
@@ -674,7 +674,7 @@ def test_largest_rank_and_eviction_on_every_path(T, K, heavy):
     reset_options()
     c = ctx()
     if heavy:
-        c.set_option("expand_split", 1)  # (decode path: the adapter term through the expand kernel)
+        c.set_option("expand_split", 1)  # (decode path: the finishing kernel)
     rng = np.random.default_rng(T)
     ranks = (512, 8, 256, 16)
     lens = [1, 2, 3, 1]  # every adapter in use

@@ -19,17 +19,16 @@ def _batch(seed, T):
 
 
 # (rows: one tile, its edges, several with a ragged last one; columns: less than a tile, a multiple, ragged)
-@pytest.mark.parametrize("T,K,N,split", [(191, 520, 100, False), (193, 1000, 256, False), (700, 1000, 300, False),
-                                         (150, 8264, 4097, True), (385, 8200, 2816, True), (577, 8264, 4000, True)])
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+# (the split along K of this tile is bf16's alone)
+@pytest.mark.parametrize("T,K,N,split,dtype", [(191, 520, 100, False, "bf16"), (193, 1000, 256, False, "bf16"), (700, 1000, 300, False, "bf16"),
+                                               (191, 520, 100, False, "f32"), (193, 1000, 256, False, "f32"), (700, 1000, 300, False, "f32"),
+                                               (150, 8264, 4097, True, "bf16"), (385, 8200, 2816, True, "bf16"), (577, 8264, 4000, True, "bf16")])
 def test_integer_inputs_are_exact(T, K, N, split, dtype):
     """Integers small enough that every partial sum is exact in fp32, in any order: fp32 results are the oracle's bit for
     bit; bf16 ones, on requests without adapters (no rounded V), are the exact sums rounded once."""
     from gpu_common import B, ctx, gpu_linear, reset_options
     from oracle import oracle_workload
     from workloads import bf16_bits_from_f32, f32_from_bf16_bits
-    if split and dtype == "f32":
-        pytest.skip("fp32 splits along K on 128x128 tiles")
     reset_options()
     ids, lens = _batch(T + K, T)
     if dtype == "bf16":
