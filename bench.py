@@ -12,8 +12,9 @@ The default run times ALL FIVE workload configurations (configuration 3 as its s
 projections, plus the decoder layer as one step with one plan, with and without the fused
 q/k/v and gate/up calls, and a 32-layer loop on one plan) and prints ONE JSON line: the
 headline fields describe the largest one (configuration 2, the prefill-shaped MLP
-up-projection; ``--steps`` / ``--warmup`` apply to it), ``per_config`` holds every
-configuration's step time, step time with the plan amortised over the 7 x 32 layer calls
+up-projection; ``--steps`` / ``--warmup`` apply to it), ``per_config`` lists every
+configuration's main figures.  ``--detail PATH`` writes everything: every configuration's
+step time, step time with the plan amortised over the 7 x 32 layer calls
 of a model step, per-kernel microseconds (HIP event pairs around every launch, in a second
 pass over the same steps), the roofline of the dominant kernel and of each other kernel,
 whole-call algorithmic bytes over time, the adapter path's GB/s, parity against the
@@ -521,6 +522,7 @@ def main():
                          "(one function's own batch, the regime of the paper's section 6)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--option", action="append", default=[], help="tuning override name=value (lora_ctx_set_option)")
+    ap.add_argument("--detail", metavar="PATH", help="default run: write everything measured to this file (JSON)")
     ap.add_argument("--library-gemm", action="store_true",
                     help="time the vendor library's plain bf16 GEMM and lora_linear without adapters at the base shapes of configurations 2-4 and exit")
     ap.add_argument("--calibrate-copy", action="store_true",
@@ -586,13 +588,13 @@ def main():
             if idx == 1:
                 r["three_projections_of_the_same_activations"] = run_fused_copies(ctx, mods, wl, 3, 200, 40)
             per_config.append(dict(index=idx, **r))
-            sys.stderr.write(f"bench: config {idx} done at {time.perf_counter() - t_start:.0f} s\n")
+            sys.stderr.write(f"config {idx}: {time.perf_counter() - t_start:.0f} s\n")
             continue
         projs = []
         for p in range(len(wl.projections)):  # the oracle's leg on the first projection only (the others have the same shape classes)
             r = run_projection(ctx, mods, wl, idx, p, steps, warmup, cpu_s if p == 0 else 0.0, options)
             projs.append(r)
-            sys.stderr.write(f"bench: config 3 projection {p} done at {time.perf_counter() - t_start:.0f} s\n")
+            sys.stderr.write(f"config 3.{p}: {time.perf_counter() - t_start:.0f} s\n")
         layer = run_layer(ctx, mods, wl, 30, 8, fuse=False)
         layer_fused = run_layer(ctx, mods, wl, 30, 8, fuse=True)
         model = run_layer(ctx, mods, wl, 3, 1, fuse=True, n_layers=32)
@@ -605,19 +607,33 @@ def main():
             "model_32_layers_one_plan_fused": model,
             "roofline": projs[0]["roofline"], "cpu_baseline": projs[0]["cpu_baseline"],
             "parity_max_err_over_rms": projs[0]["parity_max_err_over_rms"]})
-        sys.stderr.write(f"bench: config 3 done at {time.perf_counter() - t_start:.0f} s\n")
-    head = per_config[HEADLINE]
-    out = dict(common)
-    for k in ("value", "unit", "steps", "warmup", "ms_per_step", "dtype", "config", "roofline", "cpu_baseline", "ms_per_layer",
-              "ms_per_step_plan_amortised", "kernel_us", "whole_call", "adapter_path", "parity_max_err_over_rms"):
-        out[k] = head[k]
-    out["per_config"] = per_config
-    out["batch_size_sweep_config1_shape"] = run_batch_sweep(ctx, mods, options)
-    out["adapter_heavy_decode"] = run_adapter_heavy_decode(ctx, mods, options)
-    out["schedulers"] = run_schedulers(np)
-    out["targets"] = {"prefill (configs 2, 3)": ">= 0.60 of bf16 MFMA peak", "decode / adapter-heavy (configs 1, 4)": ">= 0.70 of HBM peak (whole_call.frac_of_hbm_peak)"}
-    print(json.dumps(out))
+        sys.stderr.write(f"config 3: {time.perf_counter() - t_start:.0f} s\n")
+    detail = dict(common, per_config=per_config, batch_size_sweep_config1_shape=run_batch_sweep(ctx, mods, options),
+                  adapter_heavy_decode=run_adapter_heavy_decode(ctx, mods, options), schedulers=run_schedulers(np),
+                  targets={"prefill (configs 2, 3)": ">= 0.60 of bf16 MFMA peak",
+                           "decode / adapter-heavy (configs 1, 4)": ">= 0.70 of HBM peak (whole_call.frac_of_hbm_peak)"})
+    if args.detail:
+        with open(args.detail, "w") as f:
+            json.dump(detail, f, indent=1)
+    print(headline(detail))
     ctx.close()
+
+
+def headline(detail):
+    """The default run's one line, short enough to be kept whole by whoever records the end of the output (the whole of
+    ``detail`` is ten times as long): the headline configuration's figures and, for every configuration, value, step and
+    layer time, the dominant kernel's fraction of its roofline and parity."""
+    per_config = detail["per_config"]
+    head = per_config[HEADLINE]
+    out = {k: v for k, v in detail.items() if k in ("metric", "n_gpus", "higher_is_better", "scaling", "vs_baseline", "data")}
+    for k in ("value", "unit", "steps", "warmup", "ms_per_step", "dtype", "config", "cpu_baseline", "ms_per_layer", "parity_max_err_over_rms"):
+        out[k] = head[k]
+    out["roofline"] = {k: v for k, v in head["roofline"].items() if k != "traffic_source"}
+    out["per_config"] = {
+        "columns": ["value", "ms_per_step", "ms_per_layer", "roofline frac", "parity"],
+        **{str(c["index"]): [c["value"], c.get("ms_per_step"), c.get("ms_per_layer", c.get("ms_per_layer_sum_of_seven")), c["roofline"]["frac"],
+                             float(f"{c['parity_max_err_over_rms']:.2e}")] for c in per_config}}
+    return json.dumps(out)
 
 
 if __name__ == "__main__":
