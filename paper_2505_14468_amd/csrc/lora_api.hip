@@ -652,6 +652,15 @@ bool has_adapters(const lora_plan_t *plan, const lora_linear_desc *d) {
     return d->tbl != nullptr && plan->n_adapters > 0 && plan->r_max > 0;
 }
 
+// Whether work on the stream is being captured; yes also where the runtime does not say (the legacy stream, for one, while a stream
+// that synchronises with it is captured): the calls then do what is right under capture, and report what HIP says to that.
+bool is_capturing(hipStream_t stream) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // What the launches' grids have room for: work units -- sum over the adapter segments of ceil(rows / unit_rows) -- and ranks in
 // use, each by an upper bound.  Under stream capture it holds for every batch of the plan's sizes, because a captured launch may
 // be replayed after plan_buf has been filled for another one (nothing but grids depends on these bounds: workspace offsets
@@ -663,12 +672,9 @@ struct PlanBounds {
 PlanBounds bounds_of(const lora_plan_t *plan, hipStream_t stream) {
     int64_t segs = std::min<int64_t>(std::min<int64_t>(plan->n_adapters, plan->n_req), plan->T);
     int64_t ext_rows = segs * plan->r_max;
-    if (plan->seg_cap < segs || 8 * (int64_t)plan->ext_cap < ext_rows) {
-        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone) {
-            segs = std::min<int64_t>(segs, plan->seg_cap);
-            ext_rows = std::min<int64_t>(ext_rows, 8 * (int64_t)plan->ext_cap);
-        }
+    if ((plan->seg_cap < segs || 8 * (int64_t)plan->ext_cap < ext_rows) && !is_capturing(stream)) {
+        segs = std::min<int64_t>(segs, plan->seg_cap);
+        ext_rows = std::min<int64_t>(ext_rows, 8 * (int64_t)plan->ext_cap);
     }
     return PlanBounds{plan->T / plan->unit_rows + segs, ext_rows};
 }
@@ -1192,14 +1198,12 @@ int lora_plan(lora_ctx *ctx, const int32_t *req_adapter, const int32_t *req_ntok
     int32_t *base = static_cast<int32_t *>(plan_buf);
     int32_t *staged = base + L.staged;
     const PlanBuildArgs a = plan_args(ctx, staged, staged + n_req, staged + 2 * (size_t)n_req, n_req, n_adapters, r_max, T_expected, L, base);
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    LORA_HIP(hipStreamIsCapturing(stream, &capturing));
     // The host's table for the batches one workgroup can serve; the arrays themselves and the device's own builders for
     // larger ones, under stream capture (nothing runs that would report the table read), while every table waits to be read, and
     // when an option asks for one of those builders.
     bool built = false;
     const bool asked = ctx->opt_plan_variant >= 0 || ctx->opt_plan_fused_rows >= 0;
-    if (!asked && n_req <= kApplyReq && T_expected <= kApplyRows && ext_total <= 8 * kApplyRows && capturing == hipStreamCaptureStatusNone) {
+    if (!asked && n_req <= kApplyReq && T_expected <= kApplyRows && ext_total <= 8 * kApplyRows && !is_capturing(stream)) {
         std::lock_guard<std::mutex> lock(ctx->ring_mutex);
         const int slot = take_table(ctx);
         if (slot >= 0) {

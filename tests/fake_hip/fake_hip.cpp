@@ -27,6 +27,7 @@ hipError_t pending = hipSuccess;       // what hipGetLastError() has to say
 hipError_t launch_error = hipSuccess;  // what a launch returns (nothing is enqueued then)
 hipError_t sync_error = hipSuccess;    // what waiting for an event or the device returns
 hipError_t copy_error = hipSuccess;    // what an asynchronous copy returns
+hipError_t status_error = hipSuccess;  // what asking for a stream's capture status returns
 bool capturing = false;
 size_t largest_new = ~(size_t)0;  // a larger operator new throws
 long event_waits = 0;
@@ -72,7 +73,7 @@ extern "C" {
 // ---- what the tests steer and read ----
 void fake_reset() {
     launches.clear();
-    pending = launch_error = sync_error = copy_error = hipSuccess;
+    pending = launch_error = sync_error = copy_error = status_error = hipSuccess;
     capturing = false;
     event_waits = 0;
 }
@@ -81,6 +82,7 @@ void fake_set(const char *what, int v) {
     if (!strcmp(what, "launch_error")) launch_error = (hipError_t)v;
     if (!strcmp(what, "sync_error")) sync_error = (hipError_t)v;
     if (!strcmp(what, "copy_error")) copy_error = (hipError_t)v;
+    if (!strcmp(what, "status_error")) status_error = (hipError_t)v;
     if (!strcmp(what, "largest_new")) largest_new = (size_t)v;
     if (!strcmp(what, "capturing")) capturing = v != 0;
 }
@@ -167,7 +169,7 @@ hipError_t hipGetSymbolAddress(void **p, const void *) {
 // ---- streams, events ----
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) {
     *s = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
-    return hipSuccess;
+    return fail(status_error);
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return fail(sync_error); }

@@ -114,6 +114,18 @@ def test_host_table_against_the_reference(fake):
     """)
 
 
+def test_stream_whose_capture_status_is_not_told(fake):
+    """The runtime refuses to say (the legacy stream while another thread captures): the calls go on as under capture and leave no
+    error behind."""
+    fake_hip.run(fake, """
+        say("status_error", 906)
+        plan = make_plan([0, 1, 1], [1, 2, 3], np.full(9, 8))
+        B.lora_linear(ctx, plan, make_desc(plan, 512, 512), 0)
+        assert "plan_tiny" in launched()[0][0] and F.fake_launches() == 3
+        assert F.hipGetLastError() == 0
+    """)
+
+
 def test_options_and_capture_reach_the_device_s_builders(fake):
     """lora_plan() with "plan_variant" or "plan_fused_rows" set, or under stream capture, uploads the arrays and launches the builders
     that lora_plan_device() launches; otherwise the table's kernel."""
