@@ -432,9 +432,11 @@ DecodeGeom decode_geom(int64_t T, int32_t K, int32_t N, int64_t ext_rows_bound) 
 // outputs the partial tiles of the K slices (T x N x 4 bytes per slice, written and read) outgrow the weights.
 // Both sides are fits to measured layer times in microseconds (bf16, with adapters): the decode path moves its bytes
 // at ~3.6 TB/s behind ~8 us of fixed cost; the tiled path (64x64 tiles, shrink and expand launches ~15 us) is bound
-// by its chain of K stages or by the weights at ~3 TB/s.  4096 -> 11008: decode up to 96 rows (52.8 vs 55.4 us), tiled
-// from 112 (56.4 vs 59.8); 5120 -> 13824: tiled from 72 rows (65 vs 73 us); 4096 -> 4096 and 11008 -> 4096: decode
-// throughout (28 vs 43 us, 63 vs 93 us at 128 rows).
+// by its chain of K stages or by the weights at ~3 TB/s.  The fit is older than the kernels for odd numbers of blocks and
+// counts rows by pairs of blocks, as those it was made on did; today it errs towards tiles by up to 6 us at a few sizes:
+// 4096 -> 11008: decode up to 96 rows (45 vs 52 us), tiled from 97 (52 vs 47; 54.6 vs 55.6 at 128); 5120 -> 13824: tiled from 65
+// rows (63 vs 57; 64 vs 60 at 72, even at 80, 74 vs 86 at 128); 4096 -> 4096 and 11008 -> 4096: decode throughout (23 vs 37 us,
+// 53 vs 84 us at 128 rows).
 bool decode_path_cheaper(int64_t T, int32_t K, int32_t N) {
     const double w_mb = 2.0e-6 * (double)K * (double)N;
     const int tblk = T <= 32 ? decode_tblk(T) : 2 * (int)((T + 31) / 32);  // (the fit's own measure of the rows)
