@@ -51,6 +51,27 @@ def test_more_plans_in_flight_than_tables():
             assert np.array_equal(got[k], ref[k]), k
 
 
+def test_plans_behind_a_stream_that_stays_busy():
+    """The stream is busy for longer than lora_plan() waits for a table: the plans beyond the sixteenth are uploaded instead."""
+    import torch
+    from gpu_common import ctx, plan_reference, rt
+    c = ctx()
+    rng = np.random.default_rng(6)
+    ranks = rng.choice([8, 16, 32], 9)
+    batches = [(rng.integers(-1, 9, 30 + i), rng.integers(0, 4, 30 + i)) for i in range(19)]
+    x = torch.randn(8192, 8192, device=c.device)
+    torch.cuda.synchronize()
+    for _ in range(100):  # (fp32, ~9 ms each)
+        y = x @ x
+    plans = [rt.plan(c, ids, L, ranks) for ids, L in batches]
+    busy = not torch.cuda.current_stream().query()
+    for (ids, L), pl in zip(batches, plans):
+        got, ref = pl.to_host(c), plan_reference(ids.astype(np.int32), L.astype(np.int32), ranks.astype(np.int32))
+        for k in ("perm", "row_seg", "seg_adapter", "seg_indptr", "seg_rank", "seg_ext"):
+            assert np.array_equal(got[k], ref[k]), k
+    assert busy and bool(torch.isfinite(y).all())
+
+
 def test_pending_error_of_another_call():
     """A HIP call refused before lora_plan() (an argument error, nothing on the GPU) says nothing about the plan's launch: plans
     of different sizes queued behind other work all come out right."""

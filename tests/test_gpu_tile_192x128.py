@@ -87,3 +87,23 @@ def test_fewer_stretches_in_a_smaller_workspace(T, K, N):
         ws = torch.empty(size - less * one, dtype=torch.uint8, device=c.device)
         Y = rt.linear(c, pl, X, W0, table, ws=ws)
         assert np.array_equal(rt.bits_from_tensor(Y), want), less
+
+
+def test_fewer_stretches_with_adapters():
+    """The same with the adapter term, whose room lies in front of the partial outputs, against the oracle."""
+    from gpu_common import B, check_against_oracle, ctx, reset_options, rt
+    import torch
+    from workloads import to_f64
+    reset_options()
+    c = ctx()
+    T, K, N = 150, 8264, 1200
+    ids, lens = _batch(T, T)
+    wl = make_custom(seed=950, dtype="bf16", K=K, N=N, ranks=RANKS, scales=(0.5, 0.25, 1.0, 0.125, 2.0), req_adapter=ids, req_ntok=lens,
+                     name="fewer_adapters")
+    most = int(B.lora_gemm_kernel_name(c.handle, T, K, N, 1).rpartition("splitk")[2])
+    X, W0, table = rt.upload_workload(wl, 0, c.device)
+    pl = rt.plan(c, wl.req_adapter, wl.req_ntok, wl.ranks)
+    size = B.lora_linear_workspace_bytes_preferred(T, K, N, pl.r_max, 1)
+    for less in range(most + 2):
+        ws = torch.full((size - less * T * N * 4,), 255, dtype=torch.uint8, device=c.device)
+        check_against_oracle(wl, to_f64(rt.bits_from_tensor(rt.linear(c, pl, X, W0, table, ws=ws))))
