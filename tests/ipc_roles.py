@@ -44,7 +44,7 @@ def holder(d, n_clients):
     torch.cuda.synchronize()
     handle = B.lora_backbone_export(0, ptr)
     with open(os.path.join(d, "handle.tmp"), "w") as f:
-        json.dump({"handle": handle.hex(), "bytes": int(bits.nbytes)}, f)
+        json.dump({"handle": handle.hex(), "bytes": int(bits.nbytes), "clients": n_clients}, f)
     os.replace(os.path.join(d, "handle.tmp"), os.path.join(d, "handle.json"))
     print("holder: exported", flush=True)
     t0 = time.time()
@@ -59,6 +59,17 @@ def holder(d, n_clients):
         json.dump({"unchanged": same}, f)
     print("holder: done, W0 unchanged:", same, flush=True)
     return 0 if same else 1
+
+
+def step(d, what, name, others):
+    """Say that client `name` (None: nobody) has come to `what`, and wait until all of `others` have."""
+    if name is not None:
+        open(os.path.join(d, f"{what}_{name}"), "w").close()
+    t0 = time.time()
+    while not all(os.path.exists(os.path.join(d, f"{what}_{o}")) for o in others):
+        if time.time() - t0 > 120:
+            raise RuntimeError(f"waited for {what}")
+        time.sleep(0.01)
 
 
 def client(d, name):
@@ -76,11 +87,16 @@ def client(d, name):
     info = json.load(open(os.path.join(d, "handle.json")))
     ctx = rt.Context(0)
     torch.cuda.synchronize()
+    # What is free on the device counts every process's allocations, so nobody else allocates between the two readings: all
+    # clients are set up first, then they open the handle one after the other, then they go on together.
+    step(d, "ready", name, [str(i) for i in range(info["clients"])])
+    step(d, "opened", None, [str(i) for i in range(int(name))])
     free0, _ = torch.cuda.mem_get_info()
     t1 = time.perf_counter()
     ptr = B.lora_backbone_open(0, bytes.fromhex(info["handle"]))
     open_ms = (time.perf_counter() - t1) * 1e3
     free1, _ = torch.cuda.mem_get_info()
+    step(d, "opened", name, [str(i) for i in range(info["clients"])])
     W0 = torch.as_tensor(_Raw(ptr, (N, K)), device="cuda").view(torch.bfloat16)  # zero-copy: the holder's memory
     assert W0.data_ptr() == ptr
     rng = np.random.default_rng(int(name) + 1)
