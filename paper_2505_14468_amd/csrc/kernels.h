@@ -220,12 +220,13 @@ enum GemmVariant {
     // (6, 7, 8: not in use)
     kGemmTile128x192 = 9,    // 128 rows x 192 columns on 4 waves (fills the chip where 256x128 leaves CUs idle)
     kGemmTile256x192 = 10,   // 256 x 192 on 4 waves (a tile count just below a whole number of rounds where 256x256 is just above)
-    kGemmTile256x224 = 11,   // 256 x 224 on 4 waves of 64 x 224 (likewise)
+    kGemmTile256x224 = 11,   // 256 x 224 on 4 waves of 128 x 112 (likewise)
     kGemmTile192x128 = 12,   // 192 x 128 on 4 waves (1500 rows x 4096 columns: 256 tiles, one whole round)
     kGemmVariantCount
 };
 
 hipError_t launch_gemm_tile(const GemmArgs &a, int dtype, int variant, hipStream_t stream, const KernelTimer *timer);
+hipError_t launch_gemm_tile_f32(const GemmArgs &a, int variant, hipStream_t stream, const KernelTimer *timer);
 
 // Y[row, :] = sum over s (in order) of P[s][row, :]  +  D[row, :] for rows with an adapter (D null: none), rounded once.
 struct SplitReduceArgs {
@@ -294,6 +295,7 @@ hipError_t launch_decode_finish(const DecodeArgs &a, int tblk, int units_cap, hi
 
 // Dynamic-LDS grants of every kernel instantiation, for the current device (context creation).
 hipError_t init_gemm_tile_kernels();
+hipError_t init_gemm_tile_f32();
 hipError_t init_shrink_kernels();
 hipError_t init_expand_kernels();
 
