@@ -8,11 +8,10 @@
 // than W0 in such a batch -- arrive through a two-deep, latency-bound pipeline.  Here the same work
 // is a weight-streaming problem laid out like the shrink:
 //
-//   * a workgroup = one work unit of the plan's list (<= 64 rows of one segment, <= 16 in small plans) x 1024 output columns
-//     (long enough a stream of B_a to pay for the unit's set-up: work list, row map, V);
+//   * a workgroup = one work unit of the plan's list (<= 64 rows of one segment, <= 16 in small plans) x 256 output columns;
 //   * the unit's rows of V (<= 64 x r, a few KB) are staged in LDS once; as MFMA operand they are
 //     read from there, so global loads carry B_a only;
-//   * each of the 8 waves walks 16-column blocks; MFMA 16x16x32 with the 16 output columns as M
+//   * each of the 2 waves walks 16-column blocks; MFMA 16x16x32 with the 16 output columns as M
 //     (operand rows = rows of B_a, contiguous along the rank) and 16 token rows as N; four groups
 //     of loads (16 KB per wave) are in flight while one is multiplied, across block boundaries;
 //   * steps come in pairs that share one 128-byte piece of every B_a row (step 2m takes the even
@@ -28,9 +27,14 @@
 namespace lora {
 namespace {
 
-constexpr int kExWaves = 8;
-constexpr int kExBlocksPerWave = 8;                               // 16-column blocks per wave
-constexpr int kExCols = kExWaves * kExBlocksPerWave * 16;         // output columns per workgroup
+// Workgroups of two waves: a unit is a chain of four dependent round trips (work list -> row map and adapter -> V and B_a ->
+// stores) with a short stream in the middle, and what one CU gets through is how many of them run side by side.  1024, 512 and
+// 256 columns a workgroup (eight, four, two waves): 1216 rows on 100 adapters of rank 8 to 64, gate and up 37.3 / 31.0 / 28.1 us,
+// one 4096 -> 4096 16.6 / 15.0 / 14.2; 1500 one-token requests 18.8 / 17.0 / 16.0; 365 rows 7.9 / 5.8 / 5.6; 2048 rows on some 170
+// adapters of rank 128, 5120 -> 13824 (714 MB of B_a and D) 170 / 163 / 164.
+constexpr int kExWaves = 2;
+constexpr int kExBlocksPerWave = 8;                        // 16-column blocks per wave
+constexpr int kExCols = kExWaves * kExBlocksPerWave * 16;  // output columns per workgroup
 constexpr int kExGroup = 4;                                       // MFMA steps per load group
 constexpr int kExRing = 4;                                        // load groups in flight per wave
 constexpr int kExPad = 1;                                         // chunks of padding per staged row of V
@@ -149,7 +153,7 @@ __device__ __forceinline__ void expand_unit(const ExpandArgs &p, const E *Ba, in
     }
 }
 
-// The common shapes -- a whole group of 1024 columns, rank <= 128 (bf16) -- with every index a compile-time constant:
+// The common shapes -- a whole group of 256 columns, rank <= 128 (bf16) -- with every index a compile-time constant:
 // S MFMA steps per 16-column block (2: at most 8 chunks of rank, 4: at most 16), the B_a loads of RING blocks in flight
 // per wave (all 8: everything is requested before the first MFMA), the results of all 8 blocks kept in
 // registers and stored after the last load has been consumed.  Loads and stores are counted by one in-order
@@ -167,11 +171,12 @@ __device__ __forceinline__ void expand_unit_whole(const ExpandArgs &p, const E *
     chunk_t *vs = reinterpret_cast<chunk_t *>(smem);
     const E *V = static_cast<const E *>(p.V);
 
-    // ---- the unit's rows of V: two chunks per thread at most (64 rows x 16 chunks), requested first ----
-    chunk_t vreg[2];
-    int vdst[2];
+    // ---- the unit's rows of V (at most 16 TB rows x 4 S chunks), requested first ----
+    constexpr int VL = (TB * 16 * 4 * S + kExWaves * 64 - 1) / (kExWaves * 64);
+    chunk_t vreg[VL];
+    int vdst[VL];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < VL; ++u) {
         const int e = tid + u * (kExWaves * 64);
         const bool ok = e < nrows * rchunks;
         const int t = ok ? e / rchunks : 0, c = ok ? e - t * rchunks : 0;
@@ -199,7 +204,7 @@ __device__ __forceinline__ void expand_unit_whole(const ExpandArgs &p, const E *
     for (int i = 0; i < RING; ++i) load_block(i, ring[i]);
     LORA_TS(p.trace, 2);
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < VL; ++u)
         if (vdst[u] >= 0) vs[vdst[u]] = vreg[u];
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // LDS only: the B_a loads stay in flight
     LORA_TS(p.trace, 3);  // V staged
@@ -235,9 +240,9 @@ __device__ __forceinline__ void expand_unit_whole(const ExpandArgs &p, const E *
 }
 
 // SMALL: every unit of the plan has at most 16 rows.  That instantiation keeps a quarter of the accumulators and
-// half the loads in flight, fits 128 registers (4 waves per SIMD), and two workgroups share a CU: a unit of a few
+// half the loads in flight, fits 128 registers (4 waves per SIMD): twice as many workgroups share a CU, and a unit of a few
 // rows is a chain of dependent round trips (work list, row map and adapter table, operands) more than it is a
-// stream, and one workgroup's chain overlaps the other's loads.
+// stream, and one workgroup's chain overlaps the others' loads.
 template <typename E, bool SMALL>
 __global__ __launch_bounds__(kExWaves * 64, SMALL ? 4 : 2) void expand_kernel(ExpandArgs p0) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
