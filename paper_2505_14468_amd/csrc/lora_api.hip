@@ -858,6 +858,11 @@ int do_shrink(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, cons
     if (ctx->opt_shrink_rank_block > 0) rank_block = ctx->opt_shrink_rank_block;
     a.rank_block = rank_block;
     a.rank_groups = ad ? (plan->r_max + rank_block - 1) / rank_block : 1;
+    // Workgroups of four waves, two per CU, when there are more than that many: one's chain of dependent loads rides on the
+    // other's stream (three projections of 4096 -> 4096, 1216 rows, 100 adapters of rank 8 to 64, 1008 workgroups: 31.2 -> 25.4 us;
+    // gate and up, 672: 24.1 -> 20.3).  Fewer workgroups stay at eight waves: a unit's stream is what lasts then (336
+    // workgroups, K = 4096: 13.5 us against 17.3; K = 11008: 25 against 37).
+    a.waves = (int64_t)a.max_units * a.rank_groups * std::max(n_multi, 1) > 2 * (int64_t)ctx->num_cu ? 4 : 8;
     a.xlds_bytes = ad && plan->T <= 256 ? 64 * 1024 : 0;  // small batches: units of a few rows, one workgroup per CU is plenty
     KernelTimer timer;
     const bool timed = next_timer(ctx, kProfShrink, &timer);

@@ -23,21 +23,20 @@
 namespace lora {
 namespace {
 
-constexpr int kShWaves = 8;
-constexpr int kRedBytes = 16 * 64 * 16;           // serial reduction buffer (large units): [16 tiles][64 lanes] float4
-constexpr int kPartBytes = kShWaves * 4 * 1024;   // per-wave partial tiles (units of at most 4 MFMA tiles)
-constexpr int kStageBytes = kShWaves * 2048;       // per-wave buffers that turn loaded lines into MFMA operands
+constexpr int kRedBytes = 16 * 64 * 16;  // serial reduction buffer (large units): [16 tiles][64 lanes] float4
+constexpr int part_bytes(int waves) { return waves * 4 * 1024; }  // per-wave partial tiles (units of at most 4 MFMA tiles)
+constexpr int stage_bytes(int waves) { return waves * 2048; }     // per-wave buffers that turn loaded lines into MFMA operands
 constexpr int kXldsBytes = 64 * 1024;             // rows of X staged in LDS (units of a few rows)
 constexpr int kXldsPad = 4;                       // chunks of padding per staged row: rows fall into different banks
 constexpr int kXldsRows = 4;                      // at most this many rows are staged ...
 constexpr int kXldsChunks = 2;                    // ... of at most this many chunks per thread (K <= 8192 in bf16)
 
 // Dynamic LDS of the kernel: [reduction area][operand buffers][X staging area (only when launched with it)].
-constexpr int kShSmemBase = kRedBytes > kPartBytes ? kRedBytes : kPartBytes;
+constexpr int reduction_bytes(int waves) { return kRedBytes > part_bytes(waves) ? kRedBytes : part_bytes(waves); }
 
 // (AH: the unit's block of ranks has at most 8 of them -- one load instruction per stage of A_a covers it; the
 // upper half of the MFMA tile then multiplies stale LDS contents into accumulator rows that are never stored)
-template <typename E, int TB, int JB, bool AH = false>
+template <typename E, int WAVES, int TB, int JB, bool AH = false>
 __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, float scale, int slot0, int nrows, int j0,
                                             int nj, const int (&prow)[4][2], unsigned char *smem) {
     static_assert(!AH || JB == 1, "half blocks of ranks: one block only");
@@ -56,9 +55,9 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
 
     // A unit of a few rows (decode) keeps its rows of X in LDS, shared by the waves: as MFMA operand a row
     // is wanted by every lane group of every wave.
-    const bool xlds = TB == 1 && p.xlds_bytes > 0 && nrows <= kXldsRows && kchunks <= kXldsChunks * kShWaves * 64 &&
+    const bool xlds = TB == 1 && p.xlds_bytes > 0 && nrows <= kXldsRows && kchunks <= kXldsChunks * WAVES * 64 &&
                       (int64_t)nrows * (kchunks + kXldsPad) * 16 <= p.xlds_bytes;
-    chunk_t *xs = reinterpret_cast<chunk_t *>(smem + kShSmemBase + kStageBytes);
+    chunk_t *xs = reinterpret_cast<chunk_t *>(smem + reduction_bytes(WAVES) + stage_bytes(WAVES));
     const int xstride = kchunks + kXldsPad;
 
     // Operand loads.  An MFMA operand wants "row lane % 16, 16 bytes of k" per lane; read like that from a
@@ -85,7 +84,7 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
         for (int tb = 0; tb < TB; ++tb)
             xrow[tb][i] = reinterpret_cast<const char *>(p.X) + ((int64_t)prow[tb][i] * p.ldx + wc * CE) * (int64_t)sizeof(E);
     }
-    chunk_t *buf = reinterpret_cast<chunk_t *>(smem + kShSmemBase) + wave * 128;
+    chunk_t *buf = reinterpret_cast<chunk_t *>(smem + reduction_bytes(WAVES)) + wave * 128;
     const int rsrc = li * 8, rswz = (li >> 1) & 7;
     const chunk_t *xsrow = xs + min(li, nrows - 1) * xstride + lg;
 
@@ -98,7 +97,7 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
     // This wave's share of the stages along K.  Whole stages are dealt to the waves; a last partial one
     // (K not a multiple of the 128-byte piece) goes to the last wave, masked.
     const int full = kchunks >> 3;
-    const int sg0 = (int)((int64_t)full * wave / kShWaves), sg1 = (int)((int64_t)full * (wave + 1) / kShWaves);
+    const int sg0 = (int)((int64_t)full * wave / WAVES), sg1 = (int)((int64_t)full * (wave + 1) / WAVES);
 
     // Stages past the wave's range are skipped (a uniform branch), not loaded and dropped: the address
     // unit's time is what this kernel runs out of.
@@ -172,7 +171,7 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
                 const E *src = static_cast<const E *>(p.X) + (int64_t)row * p.ldx;
 #pragma unroll
                 for (int u = 0; u < kXldsChunks; ++u) {
-                    const int c = tid + u * (kShWaves * 64);
+                    const int c = tid + u * (WAVES * 64);
                     if (c < kchunks) xr[t][u] = load_chunk(src + (int64_t)c * CE);
                 }
             }
@@ -194,7 +193,7 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
             if (t < nrows) {
 #pragma unroll
                 for (int u = 0; u < kXldsChunks; ++u) {
-                    const int c = tid + u * (kShWaves * 64);
+                    const int c = tid + u * (WAVES * 64);
                     if (c < kchunks) xs[t * xstride + c] = xr[t][u];
                 }
             }
@@ -214,7 +213,7 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
 #pragma unroll
     for (int q = 0; q < RS; ++q)
         if (g0 + q < sg1) mma_stage(g0 + q, ring[q], 0, std::integral_constant<int, 0>{}, false);
-    if ((kchunks & 7) != 0 && wave == kShWaves - 1) {  // the partial stage: chunks past K are zeros
+    if ((kchunks & 7) != 0 && wave == WAVES - 1) {  // the partial stage: chunks past K are zeros
         const bool ok = full * 8 + wc < kchunks;
         const int sb = ok ? full * 128 : -(wc * 16);  // dropped loads read the start of the row
         StageRegs f;
@@ -231,7 +230,7 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
     }
 
     LORA_TS(p.trace, 5);  // K loop done (first wave)
-    LORA_TS_WAVE(p.trace, 7, kShWaves - 1);  // (last wave)
+    LORA_TS_WAVE(p.trace, 7, WAVES - 1);  // (last wave)
     // Sum the per-wave partial tiles in wave order (fixed order -> deterministic), scale, store.
     // acc[tb][jb][e] holds D[j = jb*16 + lg*4 + e][t = tb*16 + li].
     E *V = static_cast<E *>(p.V);
@@ -247,13 +246,13 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
 #pragma unroll
                 for (int e = 0; e < 4; ++e) part[wave * TILE + (tb * 16 + li) * (JB * 16) + jb * 16 + lg * 4 + e] = acc[tb][jb][e];
         __syncthreads();
-        for (int e = tid; e < nrows * jchunks; e += kShWaves * 64) {
+        for (int e = tid; e < nrows * jchunks; e += WAVES * 64) {
             const int t = e / jchunks, jc = e - t * jchunks;
             float sum[CE];
 #pragma unroll
             for (int q = 0; q < CE; ++q) sum[q] = 0.f;
 #pragma unroll
-            for (int w = 0; w < kShWaves; ++w) {
+            for (int w = 0; w < WAVES; ++w) {
                 const float *src = &part[w * TILE + t * (JB * 16) + jc * CE];
 #pragma unroll
                 for (int q = 0; q < CE; ++q) sum[q] += src[q];
@@ -266,7 +265,7 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
         // large tiles (long K loops behind them): one wave after the other adds into one buffer, every lane into
         // its own 16-byte slot of every tile -- [tile][lane] float4: one conflict-free LDS read and write per tile
         float4 *red = reinterpret_cast<float4 *>(smem);
-        for (int w = 0; w < kShWaves; ++w) {
+        for (int w = 0; w < WAVES; ++w) {
             if (wave == w) {
 #pragma unroll
                 for (int tb = 0; tb < TB; ++tb)
@@ -287,7 +286,7 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
             __syncthreads();
         }
         // element (t, j) of the unit sits in tile (t / 16, j / 16), lane t % 16 + 16 * (j % 16 / 4), component j % 4
-        for (int e = tid; e < nrows * jchunks; e += kShWaves * 64) {
+        for (int e = tid; e < nrows * jchunks; e += WAVES * 64) {
             const int t = e / jchunks, jc = e - t * jchunks;
             float src[CE];
 #pragma unroll
@@ -306,8 +305,8 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
     }
 }
 
-template <typename E>
-__global__ __launch_bounds__(kShWaves * 64) void shrink_kernel(ShrinkArgs p0) {
+template <typename E, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 2) void shrink_kernel(ShrinkArgs p0) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x;
     LORA_TS(p0.trace, 0);
@@ -399,7 +398,7 @@ __global__ __launch_bounds__(kShWaves * 64) void shrink_kernel(ShrinkArgs p0) {
     if (Aa == nullptr) {  // slot emptied after the plan was built: flag it, contribute nothing
         E *V = static_cast<E *>(p.V);
         if (tid == 0) atomicMin(&p.plan.scalars[kScEvicted], kErrNotResident);
-        for (int e = tid; e < nrows * nj; e += kShWaves * 64) {
+        for (int e = tid; e < nrows * nj; e += WAVES * 64) {
             const int t = e / nj, j = e - t * nj;
             V[(int64_t)p.plan.perm[slot0 + t] * p.r_max + j0 + j] = Elem<E>::from_f32(0.f);
         }
@@ -409,20 +408,20 @@ __global__ __launch_bounds__(kShWaves * 64) void shrink_kernel(ShrinkArgs p0) {
     // unit shape -> instantiation (all branches are uniform over the workgroup)
     if (nrows <= 16) {
         if (nj <= 8)
-            shrink_unit<E, 1, 1, true>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
+            shrink_unit<E, WAVES, 1, 1, true>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
         else if (nj <= 16)
-            shrink_unit<E, 1, 1>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
+            shrink_unit<E, WAVES, 1, 1>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
         else if (nj <= 32)
-            shrink_unit<E, 1, 2>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
+            shrink_unit<E, WAVES, 1, 2>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
         else
-            shrink_unit<E, 1, 4>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
+            shrink_unit<E, WAVES, 1, 4>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
     } else {
         if (nj <= 16)
-            shrink_unit<E, 4, 1>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
+            shrink_unit<E, WAVES, 4, 1>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
         else if (nj <= 32)
-            shrink_unit<E, 4, 2>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
+            shrink_unit<E, WAVES, 4, 2>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
         else
-            shrink_unit<E, 4, 4>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
+            shrink_unit<E, WAVES, 4, 4>(p, Aa, scale, slot0, nrows, j0, nj, prow, smem);
     }
     LORA_TS(p.trace, 6);
 }
@@ -430,30 +429,41 @@ __global__ __launch_bounds__(kShWaves * 64) void shrink_kernel(ShrinkArgs p0) {
 }  // namespace
 
 // (more than the default 64 KB of dynamic LDS: granted per kernel and device before the first launch)
+template <typename E, int WAVES>
+static hipError_t init_shrink() {
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(shrink_kernel<E, WAVES>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               reduction_bytes(WAVES) + stage_bytes(WAVES) + kXldsBytes);
+}
 hipError_t init_shrink_kernels() {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(shrink_kernel<__bf16>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kShSmemBase + kStageBytes + kXldsBytes);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(shrink_kernel<float>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                kShSmemBase + kStageBytes + kXldsBytes);
+    hipError_t e = init_shrink<__bf16, 8>();
+    if (e == hipSuccess) e = init_shrink<float, 8>();
+    if (e == hipSuccess) e = init_shrink<__bf16, 4>();
+    if (e == hipSuccess) e = init_shrink<float, 4>();
     return e;
+}
+
+template <typename E, int WAVES>
+static hipError_t launch_waves(const ShrinkArgs &a, long grid, hipStream_t stream, const KernelTimer *timer) {
+    const size_t smem = (size_t)reduction_bytes(WAVES) + stage_bytes(WAVES) + (size_t)a.xlds_bytes;
+    return launch_kernel(shrink_kernel<E, WAVES>, dim3((unsigned)grid), dim3(WAVES * 64), smem, stream, timer, a);
 }
 
 hipError_t launch_shrink(const ShrinkArgs &a, int dtype, hipStream_t stream, const KernelTimer *timer) {
     const long grid = (long)((a.max_units + 7) / 8 * 8) * a.rank_groups * (a.n_sets > 0 ? a.n_sets : 1);
     if (grid <= 0) return hipSuccess;
     if (a.xlds_bytes != 0 && a.xlds_bytes != kXldsBytes) return hipErrorInvalidValue;
-    const size_t smem = (size_t)kShSmemBase + kStageBytes + (size_t)a.xlds_bytes;
+    const auto launch = [&](const ShrinkArgs &b) {
+        if (b.waves == 4) return dtype == 1 ? launch_waves<__bf16, 4>(b, grid, stream, timer) : launch_waves<float, 4>(b, grid, stream, timer);
+        return dtype == 1 ? launch_waves<__bf16, 8>(b, grid, stream, timer) : launch_waves<float, 8>(b, grid, stream, timer);
+    };
 #ifdef LORA_TRACE
     return trace_launch("shrink", grid, [&](long long *buf) {
         ShrinkArgs b = a;
         b.trace = buf;
-        if (dtype == 1) return launch_kernel(shrink_kernel<__bf16>, dim3((unsigned)grid), dim3(kShWaves * 64), smem, stream, timer, b);
-        return launch_kernel(shrink_kernel<float>, dim3((unsigned)grid), dim3(kShWaves * 64), smem, stream, timer, b);
+        return launch(b);
     });
 #else
-    if (dtype == 1) return launch_kernel(shrink_kernel<__bf16>, dim3((unsigned)grid), dim3(kShWaves * 64), smem, stream, timer, a);
-    return launch_kernel(shrink_kernel<float>, dim3((unsigned)grid), dim3(kShWaves * 64), smem, stream, timer, a);
+    return launch(a);
 #endif
 }
 
