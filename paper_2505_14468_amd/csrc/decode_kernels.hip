@@ -374,7 +374,7 @@ __global__ __launch_bounds__(TBLK * 64) void decode_reduce_kernel(DecodeArgs p0)
     LORA_TS(p.trace, 3);
 }
 
-constexpr int kFinWaves = 8;
+constexpr int kFinWaves = 4;  // (8 waves, 512 columns: 22.1 us where 4 take 21.6, 36.7 / 35.7, 59.5 / 58.3; 2: 25.3, 39.2, 61.4)
 constexpr int kFinBlocks = 4;                            // 16-column blocks per wave
 constexpr int kFinCols = kFinWaves * kFinBlocks * 16;    // output columns per workgroup
 constexpr int kFinTile = kFinCols + 4;                   // floats per row of the staged adapter term (4 of padding)
@@ -382,14 +382,14 @@ constexpr int kFinRows = kShrinkRowsSmall;               // most rows of a work 
 
 // Second launch for batches with much adapter work.  The reduction above gathers B_a row by row (T x r x N elements,
 // 16 bytes at a time) and every one of its workgroups re-reduces V; here a workgroup = one work unit of the plan (at
-// most 16 rows of one adapter) x 512 output columns: V of the unit's rows from their extension partial tiles (slices in
+// most 16 rows of one adapter) x 256 output columns: V of the unit's rows from their extension partial tiles (slices in
 // order, scaled, rounded to bf16 as the shrink kernel's V is), V B_a on the matrix cores with B_a streamed once, then
 // the base product's partial tiles of the same rows and columns in slice order, and Y is stored.  Rows without an
 // adapter come in units of their own behind the adapters'.  Everything after the streaming launch is this one launch:
 // as V, adapter term (fp32 through memory) and sum in a launch each, 64 rows on 64 adapters of rank 128 at
 // 5120 -> 13824 took 75.8 us, here 60.5.
 // Bound by the stream of B_a behind a chain of four dependent reads (unit -> rows, pointer -> B_a, partial tiles), so
-// two workgroups share a CU (128 registers) and B_a is requested before everything that takes longer to address.
+// four workgroups share a CU (128 registers) and B_a is requested before everything that takes longer to address.
 template <int TBLK, int S>
 __device__ __forceinline__ void finish_unit(const DecodeArgs &p, const __bf16 *Ba, float sc, int r, int slot0, int nrows, int n00,
                                             chunk_t *vs, float *tile) {
