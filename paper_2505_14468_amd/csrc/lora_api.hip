@@ -469,6 +469,13 @@ GemmChoice choose_gemm_sets(const lora_ctx *ctx, int64_t T, int32_t K, const int
     // (192x128: 1500 rows on 4096 -> 4096 in fp32 481 -> 368 us per layer, in bf16 65 -> 62; 1300 rows on 5120 -> 13824 221 -> 205)
     // Time model: rounds of one tile per CU, a tile costing its area over its MFMA efficiency (measured per
     // round at K = 4096: 256x256 104 us, 256x224 100 us, 256x192 88 us, 256x128 64 us, 128x192 51 us, 128x128 34 us, all on 4 waves).
+    // Since then every round has become shorter (256x256 107 us where the same kernel took 116, 256x192 78, 128x192 46, 128x128 33.5,
+    // one part), the order is the same but for 128x128 in bf16 on long contraction axes, which holds twice the operand traffic
+    // per flop against the power: 0.72 instead of 0.77 takes 256x192 in its place where the two were close -- 1380 rows 5120 ->
+    // 13824 214 -> 173 us, 1764 rows 4096 -> 11008 162 -> 138, 868 rows 4096 -> 22016 166 -> 149, 3830 rows 5120 -> 5120 175 -> 161 --
+    // but not below K = 4096, where the larger tile's start and end weigh more (3184 rows 2048 -> 6000: 73 and 77; 6413 rows 1024
+    // -> 3000: 43 and 48).  At 0.68 it would also give way to 128x192, which loses (556 rows 4096 -> 22016: 125 and 133).
+    const double eff128 = dtype == LORA_DTYPE_BF16 && K >= 4096 ? 0.72 : 0.77;
     struct Cand {
         int variant, bm, bn;
         double eff;
@@ -479,7 +486,7 @@ GemmChoice choose_gemm_sets(const lora_ctx *ctx, int64_t T, int32_t K, const int
                           {kGemmTile256x192, 256, 192, 0.89},
                           {kGemmTile128x192, 128, 192, 0.77},
                           {kGemmTile192x128, 192, 128, 0.77},
-                          {kGemmTile128x128, 128, 128, 0.77},
+                          {kGemmTile128x128, 128, 128, eff128},
                           {kGemmTile64x64, 64, 64, 0.45}};
     double best = 0.0;
     bool have = false;
