@@ -672,8 +672,9 @@ bool is_capturing(hipStream_t stream) {
 
 // What the launches' grids have room for: work units -- sum over the adapter segments of ceil(rows / unit_rows) -- and ranks in
 // use, each by an upper bound.  Under stream capture it holds for every batch of the plan's sizes, because a captured launch may
-// be replayed after plan_buf has been filled for another one (nothing but grids depends on these bounds: workspace offsets
-// follow the sizes alone, and a captured stage may follow an eager one).  An eager launch is for this plan, of which
+// be replayed after plan_buf has been filled for another one.  Nothing but grids, and what they imply for the shape of the
+// shrink's workgroups, depends on these bounds, and no result does: workspace offsets follow the sizes alone, a captured stage
+// may follow an eager one, and V's sums are cut the same way in every shape.  An eager launch is for this plan, of which
 // lora_plan() knows what it uses: no surplus workgroups (73 requests, a 7B decoder layer, 100 slots of up to rank 64: 237 -> 229 us).
 struct PlanBounds {
     int64_t units, ext_rows;
@@ -869,7 +870,9 @@ int do_shrink(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, cons
     // other's stream (three projections of 4096 -> 4096, 1216 rows, 100 adapters of rank 8 to 64, 1008 workgroups: 31.2 -> 25.4 us;
     // gate and up, 672: 24.1 -> 20.3).  Fewer workgroups stay at eight waves: a unit's stream is what lasts then (336
     // workgroups, K = 4096: 13.5 us against 17.3; K = 11008: 25 against 37).
-    a.waves = (int64_t)a.max_units * a.rank_groups * std::max(n_multi, 1) > 2 * (int64_t)ctx->num_cu ? 4 : 8;
+    // (four waves take two of a unit's eight slices of K each: from one stage of 128 bytes per slice on)
+    const bool long_k = (int64_t)d->K * (d->dtype == LORA_DTYPE_BF16 ? 2 : 4) >= 8 * 128;
+    a.waves = long_k && (int64_t)a.max_units * a.rank_groups * std::max(n_multi, 1) > 2 * (int64_t)ctx->num_cu ? 4 : 8;
     a.xlds_bytes = ad && plan->T <= 256 ? 64 * 1024 : 0;  // small batches: units of a few rows, one workgroup per CU is plenty
     KernelTimer timer;
     const bool timed = next_timer(ctx, kProfShrink, &timer);

@@ -3,8 +3,9 @@
 //
 // One workgroup = one work unit = (segment, block of <= 64 of its rows, group of <= 64 ranks).
 // The unit list is part of the plan; the grid is an upper bound and surplus workgroups
-// leave at once.  Inside a unit the 8 waves split the contraction axis K between
-// them; each wave runs 16x16 MFMA tiles with the adapter rows (ranks) as the MFMA M dimension
+// leave at once.  Inside a unit the contraction axis K is cut into eight slices, whatever the number of
+// waves: eight waves take one each, four take slices w and w + 4, one after the other.  A slice is
+// multiplied by itself -- 16x16 MFMA tiles with the adapter rows (ranks) as the MFMA M dimension
 // and the token rows as the N dimension.  A_a is [r, K] and X is [T, K], both contiguous along
 // K: a wave loads a stage (128 bytes of every row, two MFMA steps) of a 16-row block as two
 // instructions of 8 rows x 128 bytes -- whole cache lines -- and turns it into MFMA operand
@@ -14,8 +15,10 @@
 // the latency and bandwidth of streaming A_a once.  The unit's shape picks the instantiation
 // (1 or 4 token blocks, 1 / 2 / 4 rank blocks) so that small units spend their registers on
 // loads in flight rather than on empty tiles.
-// The per-wave partial tiles are summed through LDS in wave order, so the result is
+// The slices' partial tiles are summed through LDS in slice order, so the result is
 // deterministic, scaled by s_a in fp32 and stored once (bf16 or fp32), in original row order.
+// It is the same, bit for bit, with four waves and with eight: the host chooses between them by the size of the
+// grid, and the same batch comes with other grids eagerly, under capture and beside other projections.
 #include <type_traits>
 
 #include "kernels.h"
@@ -23,16 +26,17 @@
 namespace lora {
 namespace {
 
-constexpr int kRedBytes = 16 * 64 * 16;  // serial reduction buffer (large units): [16 tiles][64 lanes] float4
-constexpr int part_bytes(int waves) { return waves * 4 * 1024; }  // per-wave partial tiles (units of at most 4 MFMA tiles)
-constexpr int stage_bytes(int waves) { return waves * 2048; }     // per-wave buffers that turn loaded lines into MFMA operands
+constexpr int kSlices = 8;                        // of the contraction axis
+constexpr int kRedBytes = 16 * 64 * 16;           // serial reduction buffer (large units): [16 tiles][64 lanes] float4
+constexpr int kPartBytes = kSlices * 4 * 1024;    // the slices' partial tiles (units of at most 4 MFMA tiles)
+constexpr int stage_bytes(int waves) { return waves * 2048; }  // per-wave buffers that turn loaded lines into MFMA operands
 constexpr int kXldsBytes = 64 * 1024;             // rows of X staged in LDS (units of a few rows)
 constexpr int kXldsPad = 4;                       // chunks of padding per staged row: rows fall into different banks
 constexpr int kXldsRows = 4;                      // at most this many rows are staged ...
 constexpr int kXldsChunks = 2;                    // ... of at most this many chunks per thread (K <= 8192 in bf16)
 
 // Dynamic LDS of the kernel: [reduction area][operand buffers][X staging area (only when launched with it)].
-constexpr int reduction_bytes(int waves) { return kRedBytes > part_bytes(waves) ? kRedBytes : part_bytes(waves); }
+constexpr int kReductionBytes = kRedBytes > kPartBytes ? kRedBytes : kPartBytes;
 
 // (AH: the unit's block of ranks has at most 8 of them -- one load instruction per stage of A_a covers it; the
 // upper half of the MFMA tile then multiplies stale LDS contents into accumulator rows that are never stored)
@@ -40,6 +44,7 @@ template <typename E, int WAVES, int TB, int JB, bool AH = false>
 __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, float scale, int slot0, int nrows, int j0,
                                             int nj, const int (&prow)[4][2], unsigned char *smem) {
     static_assert(!AH || JB == 1, "half blocks of ranks: one block only");
+    constexpr int PASSES = kSlices / WAVES;  // slices per wave
     constexpr int AI = AH ? 1 : 2;  // load instructions per stage and 16-rank block of A_a
     constexpr int CE = Elem<E>::CE;
     constexpr int LPS = TB + JB;
@@ -57,7 +62,7 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
     // is wanted by every lane group of every wave.
     const bool xlds = TB == 1 && p.xlds_bytes > 0 && nrows <= kXldsRows && kchunks <= kXldsChunks * WAVES * 64 &&
                       (int64_t)nrows * (kchunks + kXldsPad) * 16 <= p.xlds_bytes;
-    chunk_t *xs = reinterpret_cast<chunk_t *>(smem + reduction_bytes(WAVES) + stage_bytes(WAVES));
+    chunk_t *xs = reinterpret_cast<chunk_t *>(smem + kReductionBytes + stage_bytes(WAVES));
     const int xstride = kchunks + kXldsPad;
 
     // Operand loads.  An MFMA operand wants "row lane % 16, 16 bytes of k" per lane; read like that from a
@@ -84,7 +89,7 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
         for (int tb = 0; tb < TB; ++tb)
             xrow[tb][i] = reinterpret_cast<const char *>(p.X) + ((int64_t)prow[tb][i] * p.ldx + wc * CE) * (int64_t)sizeof(E);
     }
-    chunk_t *buf = reinterpret_cast<chunk_t *>(smem + reduction_bytes(WAVES)) + wave * 128;
+    chunk_t *buf = reinterpret_cast<chunk_t *>(smem + kReductionBytes) + wave * 128;
     const int rsrc = li * 8, rswz = (li >> 1) & 7;
     const chunk_t *xsrow = xs + min(li, nrows - 1) * xstride + lg;
 
@@ -94,10 +99,11 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
 #pragma unroll
         for (int jb = 0; jb < JB; ++jb) acc[tb][jb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    // This wave's share of the stages along K.  Whole stages are dealt to the waves; a last partial one
-    // (K not a multiple of the 128-byte piece) goes to the last wave, masked.
+    // Whole stages along K are dealt to the slices; a last partial one (K not a multiple of the 128-byte piece) goes to
+    // the last slice, masked.  sg0, sg1: this wave's current slice.
     const int full = kchunks >> 3;
-    const int sg0 = (int)((int64_t)full * wave / WAVES), sg1 = (int)((int64_t)full * (wave + 1) / WAVES);
+    auto slice_begin = [&](int slice) { return (int)((int64_t)full * slice / kSlices); };
+    int sg0 = slice_begin(wave), sg1 = slice_begin(wave + 1);
 
     // Stages past the wave's range are skipped (a uniform branch), not loaded and dropped: the address
     // unit's time is what this kernel runs out of.
@@ -200,51 +206,110 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
         __syncthreads();  // the staged rows are complete (uniform over the workgroup)
     }
     LORA_TS(p.trace, 4);  // rows staged
-    int g0 = sg0;
-    for (; g0 + 2 * RS <= sg1; g0 += RS) {  // every stage here has its refill stage inside the wave's range
+    // One slice of K into acc, from a primed ring.  LAST: the wave's last one; otherwise the ring is primed for stages n0 .. n1 - 1,
+    // the next slice's, as it empties, so that the sums of this one cover their way (the host sees to it that no slice is
+    // empty: a load behind a branch could not be counted).
+    auto run_slice = [&](int slice, auto last, int n0, int n1) __attribute__((always_inline)) {
+        constexpr bool LAST = decltype(last)::value;
+        int g0 = sg0;
+        for (; g0 + 2 * RS <= sg1; g0 += RS) {  // every stage here has its refill stage inside the slice
 #pragma unroll
-        for (int q = 0; q < RS; ++q) mma_stage(g0 + q, ring[q], g0 + q + RS, std::integral_constant<int, 1>{}, false);
-    }
-    if (g0 + RS < sg1) {  // the last ring-ful with refills: some of them
-#pragma unroll
-        for (int q = 0; q < RS; ++q) mma_stage(g0 + q, ring[q], g0 + q + RS, std::integral_constant<int, 2>{}, false);
-        g0 += RS;
-    }
-#pragma unroll
-    for (int q = 0; q < RS; ++q)
-        if (g0 + q < sg1) mma_stage(g0 + q, ring[q], 0, std::integral_constant<int, 0>{}, false);
-    if ((kchunks & 7) != 0 && wave == WAVES - 1) {  // the partial stage: chunks past K are zeros
-        const bool ok = full * 8 + wc < kchunks;
-        const int sb = ok ? full * 128 : -(wc * 16);  // dropped loads read the start of the row
-        StageRegs f;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            if (!xlds) {
-#pragma unroll
-                for (int tb = 0; tb < TB; ++tb) f.x[tb][i] = keep_if(ok, load_chunk(xrow[tb][i] + sb));
-            }
-#pragma unroll
-            for (int jb = 0; jb < JB; ++jb) f.a[jb][i] = keep_if(ok, load_chunk(Ab + ((int64_t)aoff[jb][i] + sb)));
+            for (int q = 0; q < RS; ++q) mma_stage(g0 + q, ring[q], g0 + q + RS, std::integral_constant<int, 1>{}, false);
         }
-        mma_stage(full, f, 0, std::integral_constant<int, 0>{}, true);
+        if (g0 + RS < sg1) {  // the last ring-ful with refills: some of them
+#pragma unroll
+            for (int q = 0; q < RS; ++q) mma_stage(g0 + q, ring[q], g0 + q + RS, std::integral_constant<int, 2>{}, false);
+            g0 += RS;
+        }
+#pragma unroll
+        for (int q = 0; q < RS; ++q) {
+            if (g0 + q < sg1) mma_stage(g0 + q, ring[q], 0, std::integral_constant<int, 0>{}, false);
+            if constexpr (!LAST) {
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb) load_x(min(n0 + q, n1 - 1), tb, ring[q]);
+#pragma unroll
+                for (int jb = 0; jb < JB; ++jb) load_a(min(n0 + q, n1 - 1), jb, ring[q]);
+            }
+        }
+        if (LAST && (kchunks & 7) != 0 && slice == kSlices - 1) {  // the partial stage: chunks past K are zeros
+            const bool ok = full * 8 + wc < kchunks;
+            const int sb = ok ? full * 128 : -(wc * 16);  // dropped loads read the start of the row
+            StageRegs f;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                if (!xlds) {
+#pragma unroll
+                    for (int tb = 0; tb < TB; ++tb) f.x[tb][i] = keep_if(ok, load_chunk(xrow[tb][i] + sb));
+                }
+#pragma unroll
+                for (int jb = 0; jb < JB; ++jb) f.a[jb][i] = keep_if(ok, load_chunk(Ab + ((int64_t)aoff[jb][i] + sb)));
+            }
+            mma_stage(full, f, 0, std::integral_constant<int, 0>{}, true);
+        }
+    };
+
+    // What a slice leaves in acc (acc[tb][jb][e] holds D[j = jb*16 + lg*4 + e][t = tb*16 + li]) goes to LDS.
+    constexpr bool SMALL_TILE = TB * JB <= 4;
+    constexpr int TILE = TB * JB * 256;  // floats per slice (small tiles); element (t, j) at t * (JB*16) + j
+    float *part = reinterpret_cast<float *>(smem);
+    float4 *red = reinterpret_cast<float4 *>(smem);
+    auto put_slice = [&](int pass) __attribute__((always_inline)) {
+        if constexpr (SMALL_TILE) {  // every slice's partial tile is kept by itself
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+                for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        part[(pass * WAVES + wave) * TILE + (tb * 16 + li) * (JB * 16) + jb * 16 + lg * 4 + e] = acc[tb][jb][e];
+        } else {
+            // large tiles (long K loops behind them): one wave after the other adds into one buffer, every lane into
+            // its own 16-byte slot of every tile -- [tile][lane] float4: one conflict-free LDS read and write per tile
+            for (int w = 0; w < WAVES; ++w) {
+                if (wave == w) {
+#pragma unroll
+                    for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+                        for (int jb = 0; jb < JB; ++jb) {
+                            float4 *dst = &red[(tb * JB + jb) * 64 + lane];
+                            float4 v = make_float4(acc[tb][jb][0], acc[tb][jb][1], acc[tb][jb][2], acc[tb][jb][3]);
+                            if (pass != 0 || w != 0) {
+                                const float4 o = *dst;
+                                v.x += o.x;
+                                v.y += o.y;
+                                v.z += o.z;
+                                v.w += o.w;
+                            }
+                            *dst = v;
+                        }
+                }
+                __syncthreads();
+            }
+        }
+    };
+    if constexpr (PASSES == 1) {
+        run_slice(wave, std::true_type{}, 0, 0);
+    } else {
+        static_assert(PASSES == 2, "one slice or two per wave");
+        const int n0 = slice_begin(wave + WAVES), n1 = slice_begin(wave + WAVES + 1);
+        run_slice(wave, std::false_type{}, n0, n1);
+        put_slice(0);
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+            for (int jb = 0; jb < JB; ++jb) acc[tb][jb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        sg0 = n0;
+        sg1 = n1;
+        run_slice(wave + WAVES, std::true_type{}, 0, 0);
     }
 
     LORA_TS(p.trace, 5);  // K loop done (first wave)
     LORA_TS_WAVE(p.trace, 7, WAVES - 1);  // (last wave)
-    // Sum the per-wave partial tiles in wave order (fixed order -> deterministic), scale, store.
-    // acc[tb][jb][e] holds D[j = jb*16 + lg*4 + e][t = tb*16 + li].
+    // Sum the slices in order (fixed order -> deterministic), scale, store.
+    put_slice(PASSES - 1);
     E *V = static_cast<E *>(p.V);
     const int jchunks = nj / CE;  // ranks are multiples of 8
-    if constexpr (TB * JB <= 4) {
-        // small tiles: every wave parks its partial tile, then each thread sums one output over the waves
-        float *part = reinterpret_cast<float *>(smem);
-        constexpr int TILE = TB * JB * 256;  // floats per wave; element (t, j) at t * (JB*16) + j
-#pragma unroll
-        for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-            for (int jb = 0; jb < JB; ++jb)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) part[wave * TILE + (tb * 16 + li) * (JB * 16) + jb * 16 + lg * 4 + e] = acc[tb][jb][e];
+    if constexpr (SMALL_TILE) {  // each thread sums one output over the slices
         __syncthreads();
         for (int e = tid; e < nrows * jchunks; e += WAVES * 64) {
             const int t = e / jchunks, jc = e - t * jchunks;
@@ -252,7 +317,7 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
 #pragma unroll
             for (int q = 0; q < CE; ++q) sum[q] = 0.f;
 #pragma unroll
-            for (int w = 0; w < WAVES; ++w) {
+            for (int w = 0; w < kSlices; ++w) {
                 const float *src = &part[w * TILE + t * (JB * 16) + jc * CE];
 #pragma unroll
                 for (int q = 0; q < CE; ++q) sum[q] += src[q];
@@ -262,29 +327,6 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
             if constexpr (CE == 8) store4(dst + 4, scale * sum[4], scale * sum[5], scale * sum[6], scale * sum[7]);
         }
     } else {
-        // large tiles (long K loops behind them): one wave after the other adds into one buffer, every lane into
-        // its own 16-byte slot of every tile -- [tile][lane] float4: one conflict-free LDS read and write per tile
-        float4 *red = reinterpret_cast<float4 *>(smem);
-        for (int w = 0; w < WAVES; ++w) {
-            if (wave == w) {
-#pragma unroll
-                for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-                    for (int jb = 0; jb < JB; ++jb) {
-                        float4 *dst = &red[(tb * JB + jb) * 64 + lane];
-                        float4 v = make_float4(acc[tb][jb][0], acc[tb][jb][1], acc[tb][jb][2], acc[tb][jb][3]);
-                        if (w != 0) {
-                            const float4 o = *dst;
-                            v.x += o.x;
-                            v.y += o.y;
-                            v.z += o.z;
-                            v.w += o.w;
-                        }
-                        *dst = v;
-                    }
-            }
-            __syncthreads();
-        }
         // element (t, j) of the unit sits in tile (t / 16, j / 16), lane t % 16 + 16 * (j % 16 / 4), component j % 4
         for (int e = tid; e < nrows * jchunks; e += WAVES * 64) {
             const int t = e / jchunks, jc = e - t * jchunks;
@@ -432,7 +474,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void shrink_kernel(ShrinkArgs p0) {
 template <typename E, int WAVES>
 static hipError_t init_shrink() {
     return hipFuncSetAttribute(reinterpret_cast<const void *>(shrink_kernel<E, WAVES>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               reduction_bytes(WAVES) + stage_bytes(WAVES) + kXldsBytes);
+                               kReductionBytes + stage_bytes(WAVES) + kXldsBytes);
 }
 hipError_t init_shrink_kernels() {
     hipError_t e = init_shrink<__bf16, 8>();
@@ -444,7 +486,8 @@ hipError_t init_shrink_kernels() {
 
 template <typename E, int WAVES>
 static hipError_t launch_waves(const ShrinkArgs &a, long grid, hipStream_t stream, const KernelTimer *timer) {
-    const size_t smem = (size_t)reduction_bytes(WAVES) + stage_bytes(WAVES) + (size_t)a.xlds_bytes;
+    if (WAVES < kSlices && a.K < kSlices * 8 * Elem<E>::CE) return hipErrorInvalidValue;  // (an empty slice)
+    const size_t smem = (size_t)kReductionBytes + stage_bytes(WAVES) + (size_t)a.xlds_bytes;
     return launch_kernel(shrink_kernel<E, WAVES>, dim3((unsigned)grid), dim3(WAVES * 64), smem, stream, timer, a);
 }
 

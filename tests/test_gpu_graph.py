@@ -145,3 +145,43 @@ def test_captured_layers_follow_a_plan_rebuilt_by_lora_plan(case):
         torch.cuda.synchronize()
         assert torch.equal(Y.view(torch.int16), want.view(torch.int16)), (case, ids[:8])
     reset_options()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("used", [60, 1000])
+def test_results_do_not_depend_on_the_grids_bound(dtype, used):
+    """1000 slots, some or all of them in use: the shrink has a few workgroups or more than 512 by what lora_plan() knows, and more
+    than 512 by the sizes.  Eagerly, alone and beside two other projections, on a plan built on the device, and replayed: the
+    same bits."""
+    from gpu_common import B, ctx, reset_options, rt
+    reset_options()
+    c = ctx()
+    dev = c.device
+    K, N, T, n_ad, r = 1032, 264, 1500, 1000, 64
+    rng = np.random.default_rng(used)
+    ranks = rng.choice([8, 16, 40, 64], n_ad).astype(np.int32)
+    wl = make_custom(seed=972, dtype=dtype, K=K, N=N, ranks=ranks, scales=np.linspace(0.5, 2.0, n_ad), req_adapter=np.arange(T) % used,
+                     req_ntok=np.ones(T, int), name=f"bound_{dtype}_{used}")
+    X, W0, table = rt.upload_workload(wl, 0, dev)
+    ids, ones = np.ascontiguousarray(wl.req_adapter).astype(np.int32), np.ones(T, np.int32)
+    bits = lambda y: y.view(torch.int16 if dtype == "bf16" else torch.int32)
+    pl = rt.plan(c, ids, ones, ranks, r)
+    want = rt.linear(c, pl, X, W0, table)
+    for y in rt.linear_multi(c, pl, X, [(W0, table)] * 3):
+        assert torch.equal(bits(y), bits(want))
+    dpl = rt.plan_device(c, *(torch.from_numpy(v).to(dev) for v in (ids, ones, ranks)), r, T)
+    assert torch.equal(bits(rt.linear(c, dpl, X, W0, table)), bits(want))
+    Y = torch.zeros((T, N), dtype=X.dtype, device=dev)
+    ws = rt.workspace(T, K, N, r, X.dtype, dev)
+    d = rt.linear_desc(pl, X, W0, Y, table, ws)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        B.lora_linear(c.handle, pl.struct, d, torch.cuda.current_stream().cuda_stream)
+    for _ in range(3):
+        Y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(bits(Y), bits(want))
+    reset_options()
