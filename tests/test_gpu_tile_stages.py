@@ -80,3 +80,23 @@ def test_extension_behind_the_stages(variant, dtype):
         bound = unit * (np.abs(want) + term_v) * 1.01 + (K + max(RANKS)) * 2.0 ** -24 * terms
         assert (np.abs(gpu_linear(wl) - want) <= bound).all(), K
     reset_options()
+
+
+@pytest.mark.parametrize("dtype,short", [("bf16", 64), ("bf16", 130), ("f32", 32), ("f32", 65)])
+@pytest.mark.parametrize("variant", sorted(TILES))
+def test_long_segment_behind_table_batches_without_a_column(variant, dtype, short):
+    """One-row requests on adapters of rank 64, whose term comes from the expand kernel, in front of a long segment, whose term the
+    GEMM computes: the first batches of the tile's column table (512 columns each) have none in use.  K of whole stages, so
+    that the loads past its end are still on their way when the extension begins."""
+    from gpu_common import check_against_oracle, ctx, gpu_linear, reset_options
+    reset_options()
+    ctx().set_option("gemm_variant", variant)
+    ctx().set_option("gemm_split_k", 0)
+    ctx().set_option("expand_split", 1)
+    bm, bn = TILES[variant]
+    for K in (64, 128, 320):
+        lens = np.r_[np.ones(short, int), max(2 * bm, 130)]
+        wl = make_custom(seed=K + short, dtype=dtype, K=K, N=bn + 9, ranks=np.full(short + 1, 64), scales=np.full(short + 1, 0.5),
+                         req_adapter=np.arange(short + 1), req_ntok=lens, name=f"late_columns_{variant}_{dtype}_{short}_{K}")
+        check_against_oracle(wl, gpu_linear(wl))
+    reset_options()
