@@ -126,7 +126,7 @@ struct ShrinkArgs {
     int32_t rank_block;    // ranks per workgroup: 8 or 16 (few units: spread them over the chip) or kShrinkRanks
     int32_t rank_groups;   // ceil(r_max / rank_block)
     int32_t max_units;     // upper bound of work units (shrink grid = max_units * rank_groups)
-    int32_t waves = 8;     // per workgroup: 8 (one workgroup per CU) or 4 (two; K of at least 8 stages).  V is the same bit for bit
+    int32_t waves = 8;     // per workgroup: 8 (one workgroup per CU) or 4 (two; K of at least 8 stages, no staging of X).  V is the same bit for bit
     int32_t xlds_bytes;    // LDS for staging the X rows of small units: 0 or 64 KiB (decode-sized batches)
     long long *trace = nullptr;  // phase stamps (trace builds only)
     int32_t n_sets = 0;    // > 0: the projections of the launch (A, scale, V, n_adapters above are then unused)

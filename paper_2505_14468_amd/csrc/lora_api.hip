@@ -872,8 +872,9 @@ int do_shrink(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, cons
     // workgroups, K = 4096: 13.5 us against 17.3; K = 11008: 25 against 37).
     // (four waves take two of a unit's eight slices of K each: from one stage of 128 bytes per slice on)
     const bool long_k = (int64_t)d->K * (d->dtype == LORA_DTYPE_BF16 ? 2 : 4) >= 8 * 128;
-    a.waves = long_k && (int64_t)a.max_units * a.rank_groups * std::max(n_multi, 1) > 2 * (int64_t)ctx->num_cu ? 4 : 8;
-    a.xlds_bytes = ad && plan->T <= 256 ? 64 * 1024 : 0;  // small batches: units of a few rows, one workgroup per CU is plenty
+    // With X staged in LDS (small batches: units of a few rows) there is room for one workgroup per CU of either kind.
+    a.xlds_bytes = ad && plan->T <= 256 ? 64 * 1024 : 0;
+    a.waves = long_k && a.xlds_bytes == 0 && (int64_t)a.max_units * a.rank_groups * std::max(n_multi, 1) > 2 * (int64_t)ctx->num_cu ? 4 : 8;
     KernelTimer timer;
     const bool timed = next_timer(ctx, kProfShrink, &timer);
     LORA_HIP(launch_shrink(a, d->dtype, stream, timed ? &timer : nullptr));

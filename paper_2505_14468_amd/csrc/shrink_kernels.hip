@@ -34,6 +34,7 @@ constexpr int kXldsBytes = 64 * 1024;             // rows of X staged in LDS (un
 constexpr int kXldsPad = 4;                       // chunks of padding per staged row: rows fall into different banks
 constexpr int kXldsRows = 4;                      // at most this many rows are staged ...
 constexpr int kXldsChunks = 2;                    // ... of at most this many chunks per thread (K <= 8192 in bf16)
+constexpr int kXldsWaves = 8;                     // by workgroups of this many waves only: with the staging area one fits a CU
 
 // Dynamic LDS of the kernel: [reduction area][operand buffers][X staging area (only when launched with it)].
 constexpr int kReductionBytes = kRedBytes > kPartBytes ? kRedBytes : kPartBytes;
@@ -60,7 +61,7 @@ __device__ __forceinline__ void shrink_unit(const ShrinkArgs &p, const E *Aa, fl
 
     // A unit of a few rows (decode) keeps its rows of X in LDS, shared by the waves: as MFMA operand a row
     // is wanted by every lane group of every wave.
-    const bool xlds = TB == 1 && p.xlds_bytes > 0 && nrows <= kXldsRows && kchunks <= kXldsChunks * WAVES * 64 &&
+    const bool xlds = TB == 1 && WAVES == kXldsWaves && p.xlds_bytes > 0 && nrows <= kXldsRows && kchunks <= kXldsChunks * WAVES * 64 &&
                       (int64_t)nrows * (kchunks + kXldsPad) * 16 <= p.xlds_bytes;
     chunk_t *xs = reinterpret_cast<chunk_t *>(smem + kReductionBytes + stage_bytes(WAVES));
     const int xstride = kchunks + kXldsPad;
@@ -474,7 +475,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void shrink_kernel(ShrinkArgs p0) {
 template <typename E, int WAVES>
 static hipError_t init_shrink() {
     return hipFuncSetAttribute(reinterpret_cast<const void *>(shrink_kernel<E, WAVES>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               kReductionBytes + stage_bytes(WAVES) + kXldsBytes);
+                               kReductionBytes + stage_bytes(WAVES) + (WAVES == kXldsWaves ? kXldsBytes : 0));
 }
 hipError_t init_shrink_kernels() {
     hipError_t e = init_shrink<__bf16, 8>();
@@ -486,6 +487,7 @@ hipError_t init_shrink_kernels() {
 
 template <typename E, int WAVES>
 static hipError_t launch_waves(const ShrinkArgs &a, long grid, hipStream_t stream, const KernelTimer *timer) {
+    if (WAVES != kXldsWaves && a.xlds_bytes != 0) return hipErrorInvalidValue;
     if (WAVES < kSlices && a.K < kSlices * 8 * Elem<E>::CE) return hipErrorInvalidValue;  // (an empty slice)
     const size_t smem = (size_t)kReductionBytes + stage_bytes(WAVES) + (size_t)a.xlds_bytes;
     return launch_kernel(shrink_kernel<E, WAVES>, dim3((unsigned)grid), dim3(WAVES * 64), smem, stream, timer, a);

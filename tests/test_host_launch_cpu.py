@@ -67,6 +67,26 @@ def test_shrink_rank_blocks_count_every_projection(fake, T, rank, sets, block):
     """)
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("T,n_ad,K,waves", [(200, 100, 4096, 8), (200, 100, 5120, 8), (256, 250, 11008, 8), (257, 250, 4096, 4),
+                                            (1500, 600, 4096, 4), (600, 20, 4096, 8), (1500, 600, 136, 8), (1500, 600, 512, 4)])
+def test_shrink_waves_of_a_workgroup(fake, T, n_ad, K, waves, dtype):
+    """Four waves only where two such workgroups fit a CU (no staging of X, which batches of at most 256 rows have), the grid
+    has more than two per CU, and K has a stage for each of the eight slices."""
+    fake_hip.run(fake, f"""
+        T, n_ad, K, waves, dtype = {T}, {n_ad}, {K}, {waves}, {dtype}
+        plan = make_plan(np.arange(T) % n_ad, np.ones(T, int), np.full(n_ad, 64))
+        B.lora_ctx_set_option(ctx, "gemm_variant", 0)  # (tiles at decode sizes too)
+        d = [make_desc(plan, K, 264, dtype) for _ in range(3)]
+        for v in d:
+            v.X = d[0].X
+        F.fake_reset()
+        B.lora_linear_multi(ctx, plan, d, 0)
+        blocks = [b for name, _, b in launched() if "shrink_kernel" in name]
+        assert blocks == [(64 * waves, 1, 1)], blocks
+    """)
+
+
 def test_finishing_kernel_only_with_a_workspace_of_the_preferred_size(fake):
     """The decode path's finishing kernel rounds V to bf16; calls with less workspace keep the reduction, whose V is fp32."""
     fake_hip.run(fake, """
