@@ -804,6 +804,14 @@ int do_decode(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, cons
     return do_decode_second(ctx, plan, pb, descs, n, a, c, stream);
 }
 
+// Whether lora_plan() made the plan: it leaves what the batch uses in the capacities, lora_plan_device what any batch could (one
+// segment more than slots; every segment at r_max).  A host plan that uses every slot at full rank, with rows that have no adapter
+// besides, looks like the latter: nothing but a choice between equals may hang on this.
+bool built_by_host(const lora_plan_t *plan) {
+    const int64_t segs = std::min<int64_t>(plan->n_adapters, plan->n_req);
+    return plan->seg_cap <= plan->n_adapters || 8 * (int64_t)plan->ext_cap < segs * plan->r_max;
+}
+
 // (multi: several projections of the same X that go through one launch)
 int do_shrink(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, const lora_linear_desc *d, hipStream_t stream,
               const lora_linear_desc *const *multi = nullptr, int n_multi = 0) {
@@ -867,14 +875,21 @@ int do_shrink(lora_ctx *ctx, const lora_plan_t *plan, const PlanBounds &pb, cons
     a.rank_block = rank_block;
     a.rank_groups = ad ? (plan->r_max + rank_block - 1) / rank_block : 1;
     // Workgroups of four waves, two per CU, when there are more than that many: one's chain of dependent loads rides on the
-    // other's stream (three projections of 4096 -> 4096, 1216 rows, 100 adapters of rank 8 to 64, 1008 workgroups: 31.2 -> 25.4 us;
-    // gate and up, 672: 24.1 -> 20.3).  Fewer workgroups stay at eight waves: a unit's stream is what lasts then (336
-    // workgroups, K = 4096: 13.5 us against 17.3; K = 11008: 25 against 37).
-    // (four waves take two of a unit's eight slices of K each: from one stage of 128 bytes per slice on)
-    const bool long_k = (int64_t)d->K * (d->dtype == LORA_DTYPE_BF16 ? 2 : 4) >= 8 * 128;
-    // With X staged in LDS (small batches: units of a few rows) there is room for one workgroup per CU of either kind.
+    // other's stream (eight and four waves, us: three projections of 4096 -> 4096, 1216 rows, 100 adapters of rank 8 to 64, 1008
+    // workgroups, 34.3 / 30.1; gate and up, 672, 24.2 / 20.0; three projections of K = 2048, 1000 one-row adapters, 93.3 / 72.1).
+    // Fewer workgroups stay at eight waves: a unit's stream is what lasts then (336 workgroups, K = 4096: 13.5 us against 17.3).
+    // So does K from 16 KB a row on, for the same reason (1000 one-row adapters, K in bf16: 4096 56.3 / 55.2, 5120 69.8 / 69.2, 7168
+    // 89.8 / 91.1, 8192 97.8 / 102.2, 11008 134.6 / 139.8; 300 adapters, two projections, 8192 69.4 / 79.6, 11008 90.5 / 101.8), K with
+    // less than one stage of 128 bytes for each of a unit's eight slices, launches with X staged in LDS (small batches: units of a
+    // few rows), of which either kind fits a CU once, and plans built on the device, whose grids are for every slot (300 of
+    // 1000 in use: 25.7 / 29.7).  (Under capture a host plan's grid is an upper bound as well; the shape has to follow it, so that a
+    // captured launch is the one that a batch using all of it would get.)
     a.xlds_bytes = ad && plan->T <= 256 ? 64 * 1024 : 0;
-    a.waves = long_k && a.xlds_bytes == 0 && (int64_t)a.max_units * a.rank_groups * std::max(n_multi, 1) > 2 * (int64_t)ctx->num_cu ? 4 : 8;
+    const int64_t row_bytes = (int64_t)d->K * (d->dtype == LORA_DTYPE_BF16 ? 2 : 4);
+    a.waves = built_by_host(plan) && row_bytes >= 8 * 128 && row_bytes < 16 * 1024 && a.xlds_bytes == 0 &&
+                      (int64_t)a.max_units * a.rank_groups * std::max(n_multi, 1) > 2 * (int64_t)ctx->num_cu
+                  ? 4
+                  : 8;
     KernelTimer timer;
     const bool timed = next_timer(ctx, kProfShrink, &timer);
     LORA_HIP(launch_shrink(a, d->dtype, stream, timed ? &timer : nullptr));

@@ -67,12 +67,14 @@ def test_shrink_rank_blocks_count_every_projection(fake, T, rank, sets, block):
     """)
 
 
-@pytest.mark.parametrize("dtype", [0, 1])
-@pytest.mark.parametrize("T,n_ad,K,waves", [(200, 100, 4096, 8), (200, 100, 5120, 8), (256, 250, 11008, 8), (257, 250, 4096, 4),
-                                            (1500, 600, 4096, 4), (600, 20, 4096, 8), (1500, 600, 136, 8), (1500, 600, 512, 4)])
-def test_shrink_waves_of_a_workgroup(fake, T, n_ad, K, waves, dtype):
+@pytest.mark.parametrize("T,n_ad,K,dtype,waves", [
+    (200, 100, 4096, 1, 8), (200, 100, 4096, 0, 8), (200, 100, 5120, 1, 8), (256, 250, 1024, 0, 8), (257, 250, 1024, 0, 4),
+    (257, 250, 4096, 1, 4), (600, 20, 4096, 1, 8), (1500, 600, 136, 1, 8), (1500, 600, 512, 1, 4), (1500, 600, 256, 0, 4),
+    (1500, 600, 8184, 1, 4), (1500, 600, 8192, 1, 8), (1500, 600, 11008, 1, 8), (1500, 600, 4088, 0, 4), (1500, 600, 4096, 0, 8)])
+def test_shrink_waves_of_a_workgroup(fake, T, n_ad, K, dtype, waves):
     """Four waves only where two such workgroups fit a CU (no staging of X, which batches of at most 256 rows have), the grid
-    has more than two per CU, and K has a stage for each of the eight slices."""
+    has more than two per CU, and a row of X is from 1 KB -- a stage for each of the eight slices -- to 16 KB long.  A plan built on the
+    device, whose grid is for every slot, gets eight."""
     fake_hip.run(fake, f"""
         T, n_ad, K, waves, dtype = {T}, {n_ad}, {K}, {waves}, {dtype}
         plan = make_plan(np.arange(T) % n_ad, np.ones(T, int), np.full(n_ad, 64))
@@ -80,10 +82,16 @@ def test_shrink_waves_of_a_workgroup(fake, T, n_ad, K, waves, dtype):
         d = [make_desc(plan, K, 264, dtype) for _ in range(3)]
         for v in d:
             v.X = d[0].X
-        F.fake_reset()
-        B.lora_linear_multi(ctx, plan, d, 0)
-        blocks = [b for name, _, b in launched() if "shrink_kernel" in name]
-        assert blocks == [(64 * waves, 1, 1)], blocks
+
+        def shrink(plan):
+            F.fake_reset()
+            B.lora_linear_multi(ctx, plan, d, 0)
+            return [b for name, _, b in launched() if "shrink_kernel" in name]
+
+        assert shrink(plan) == [(64 * waves, 1, 1)], shrink(plan)
+        n = B.lora_plan_bytes(T, T, n_ad, 64)
+        device = B.lora_plan_device(ctx, mem(4 * T), mem(4 * T), T, mem(4 * n_ad), n_ad, 64, T, mem(n), n, 0)
+        assert shrink(device) == [(512, 1, 1)], shrink(device)
     """)
 
 
