@@ -8,10 +8,11 @@
 // than W0 in such a batch -- arrive through a two-deep, latency-bound pipeline.  Here the same work
 // is a weight-streaming problem laid out like the shrink:
 //
-//   * a workgroup = one work unit of the plan's list (<= 64 rows of one segment, <= 16 in small plans) x 256 output columns;
+//   * a workgroup = one work unit of the plan's list (<= 64 rows of one segment, <= 16 in small plans) x 256 output
+//     columns (512 or 1024 where the ranks are large);
 //   * the unit's rows of V (<= 64 x r, a few KB) are staged in LDS once; as MFMA operand they are
 //     read from there, so global loads carry B_a only;
-//   * each of the 2 waves walks 16-column blocks; MFMA 16x16x32 with the 16 output columns as M
+//   * each of the 2 waves (4, 8) walks 16-column blocks; MFMA 16x16x32 with the 16 output columns as M
 //     (operand rows = rows of B_a, contiguous along the rank) and 16 token rows as N; four groups
 //     of loads (16 KB per wave) are in flight while one is multiplied, across block boundaries;
 //   * steps come in pairs that share one 128-byte piece of every B_a row (step 2m takes the even
@@ -32,14 +33,15 @@ namespace {
 // 256 columns a workgroup (eight, four, two waves): 1216 rows on 100 adapters of rank 8 to 64, gate and up 37.3 / 31.0 / 28.1 us,
 // one 4096 -> 4096 16.6 / 15.0 / 14.2; 1500 one-token requests 18.8 / 17.0 / 16.0; 365 rows 7.9 / 5.8 / 5.6; 2048 rows on some 170
 // adapters of rank 128, 5120 -> 13824 (714 MB of B_a and D) 170 / 163 / 164.
-constexpr int kExWaves = 2;
-constexpr int kExBlocksPerWave = 8;                        // 16-column blocks per wave
-constexpr int kExCols = kExWaves * kExBlocksPerWave * 16;  // output columns per workgroup
+// Four or eight waves where the LDS for a unit's V leaves too few workgroups of two on a CU: see expand_waves.
+constexpr int kExBlocksPerWave = 8;                                           // 16-column blocks per wave
+constexpr int ex_cols(int waves) { return waves * kExBlocksPerWave * 16; }  // output columns per workgroup
 constexpr int kExGroup = 4;                                       // MFMA steps per load group
 constexpr int kExRing = 4;                                        // load groups in flight per wave
 constexpr int kExPad = 1;                                         // chunks of padding per staged row of V
+constexpr size_t kLdsBytesPerCu = 160 * 1024;
 
-template <typename E, int TB>
+template <typename E, int WAVES, int TB>
 __device__ __forceinline__ void expand_unit(const ExpandArgs &p, const E *Ba, int r, int slot0, int nrows, int nwg0,
                                             unsigned char *smem) {
     constexpr int CE = Elem<E>::CE;
@@ -70,8 +72,8 @@ __device__ __forceinline__ void expand_unit(const ExpandArgs &p, const E *Ba, in
     auto chunk_of = [&](int st) { return (st >> 1) * 8 + 2 * lg + (st & 1); };
 
     // this wave's column blocks, b = 0 .. kExBlocksPerWave-1 (those below N): pairs of adjacent blocks (32 columns:
-    // a row's two stores fall into one 128-byte line), pair p of wave w at column 32 * (w + 8 p)
-    auto block_n0 = [&](int b) { return nwg0 + (2 * wave + (b & 1) + 2 * kExWaves * (b >> 1)) * 16; };
+    // a row's two stores fall into one 128-byte line), pair p of wave w at column 32 * (w + WAVES p)
+    auto block_n0 = [&](int b) { return nwg0 + (2 * wave + (b & 1) + 2 * WAVES * (b >> 1)) * 16; };
     int nblk = 0;
 #pragma unroll
     for (int b = 0; b < kExBlocksPerWave; ++b) nblk += block_n0(b) < p.N ? 1 : 0;
@@ -126,7 +128,7 @@ __device__ __forceinline__ void expand_unit(const ExpandArgs &p, const E *Ba, in
     // ---- stage the unit's rows of V (original row order in memory: gather through the row map) ----
     // V first: it comes from L2 and loads return in order -- behind B_a's loads from HBM it would arrive last.
     LORA_TS(p.trace, 2);  // row map read
-    for (int e = tid; e < nrows * rchunks; e += kExWaves * 64) {
+    for (int e = tid; e < nrows * rchunks; e += WAVES * 64) {
         const int t = e / rchunks, c = e - t * rchunks;
         vs[t * vstride + c] = load_chunk(V + (int64_t)p.plan.perm[slot0 + t] * p.r_max + (int64_t)c * CE);
     }
@@ -153,13 +155,13 @@ __device__ __forceinline__ void expand_unit(const ExpandArgs &p, const E *Ba, in
     }
 }
 
-// The common shapes -- a whole group of 256 columns, rank <= 128 (bf16) -- with every index a compile-time constant:
+// The common shapes -- a whole group of columns, rank <= 128 (bf16) -- with every index a compile-time constant:
 // S MFMA steps per 16-column block (2: at most 8 chunks of rank, 4: at most 16), the B_a loads of RING blocks in flight
 // per wave (all 8: everything is requested before the first MFMA), the results of all 8 blocks kept in
 // registers and stored after the last load has been consumed.  Loads and stores are counted by one in-order
 // counter, so a store issued between loads makes the next wait for a load wait for the store's acknowledgement
 // from memory as well; and no load sits behind a branch, so that the compiler can count the loads in flight.
-template <typename E, int TB, int S, int RING>
+template <typename E, int WAVES, int TB, int S, int RING>
 __device__ __forceinline__ void expand_unit_whole(const ExpandArgs &p, const E *Ba, int r, int slot0, int nrows, int nwg0,
                                                   unsigned char *smem) {
     constexpr int CE = Elem<E>::CE;
@@ -172,12 +174,12 @@ __device__ __forceinline__ void expand_unit_whole(const ExpandArgs &p, const E *
     const E *V = static_cast<const E *>(p.V);
 
     // ---- the unit's rows of V (at most 16 TB rows x 4 S chunks), requested first ----
-    constexpr int VL = (TB * 16 * 4 * S + kExWaves * 64 - 1) / (kExWaves * 64);
+    constexpr int VL = (TB * 16 * 4 * S + WAVES * 64 - 1) / (WAVES * 64);
     chunk_t vreg[VL];
     int vdst[VL];
 #pragma unroll
     for (int u = 0; u < VL; ++u) {
-        const int e = tid + u * (kExWaves * 64);
+        const int e = tid + u * (WAVES * 64);
         const bool ok = e < nrows * rchunks;
         const int t = ok ? e / rchunks : 0, c = ok ? e - t * rchunks : 0;
         vdst[u] = ok ? t * vstride + c : -1;
@@ -185,7 +187,7 @@ __device__ __forceinline__ void expand_unit_whole(const ExpandArgs &p, const E *
     }
     // ---- B_a: lane -> (column block_n0 + li, chunk of the step); chunks past the rank are read from chunk 0
     //      and meet a zeroed V operand ----
-    auto block_n0 = [&](int b) { return nwg0 + (2 * wave + (b & 1) + 2 * kExWaves * (b >> 1)) * 16; };
+    auto block_n0 = [&](int b) { return nwg0 + (2 * wave + (b & 1) + 2 * WAVES * (b >> 1)) * 16; };
     int kc[S];
     bool kok[S];
 #pragma unroll
@@ -243,8 +245,9 @@ __device__ __forceinline__ void expand_unit_whole(const ExpandArgs &p, const E *
 // half the loads in flight, fits 128 registers (4 waves per SIMD): twice as many workgroups share a CU, and a unit of a few
 // rows is a chain of dependent round trips (work list, row map and adapter table, operands) more than it is a
 // stream, and one workgroup's chain overlaps the others' loads.
-template <typename E, bool SMALL>
-__global__ __launch_bounds__(kExWaves * 64, SMALL ? 4 : 2) void expand_kernel(ExpandArgs p0) {
+template <typename E, int WAVES, bool SMALL>
+__global__ __launch_bounds__(WAVES * 64, SMALL ? 4 : 2) void expand_kernel(ExpandArgs p0) {
+    constexpr int COLS = ex_cols(WAVES);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     LORA_TS(p0.trace, 0);
     // several projections of the same batch: the single-projection grids one after the other
@@ -260,7 +263,7 @@ __global__ __launch_bounds__(kExWaves * 64, SMALL ? 4 : 2) void expand_kernel(Ex
         p.ldd = p0.set[si].ldd;
         p.N = p0.set[si].N;
         p.skip_long = p0.set[si].skip_long;
-        p.col_groups = (p.N + kExCols - 1) / kExCols;
+        p.col_groups = (p.N + COLS - 1) / COLS;
     }
     const int unit = bid / p.col_groups;
     const int cg = bid - unit * p.col_groups;
@@ -275,82 +278,109 @@ __global__ __launch_bounds__(kExWaves * 64, SMALL ? 4 : 2) void expand_kernel(Ex
     LORA_TS(p.trace, 1);  // work-list record read
     if (Ba == nullptr) {  // slot emptied after the plan was built: flag it, contribute nothing
         if (threadIdx.x == 0) atomicMin(&p.plan.scalars[kScEvicted], kErrNotResident);
-        const int n_lo = cg * kExCols, n_hi = min(n_lo + kExCols, p.N);
-        for (int e = threadIdx.x; e < nrows * (n_hi - n_lo); e += kExWaves * 64) {
+        const int n_lo = cg * COLS, n_hi = min(n_lo + COLS, p.N);
+        for (int e = threadIdx.x; e < nrows * (n_hi - n_lo); e += WAVES * 64) {
             const int t = e / (n_hi - n_lo), n = n_lo + e - t * (n_hi - n_lo);
             p.D[(int64_t)p.plan.perm[slot0 + t] * p.ldd + n] = 0.f;
         }
         return;
     }
     const int rchunks = r / Elem<E>::CE;
-    if ((cg + 1) * kExCols <= p.N && rchunks <= 16) {  // a whole column group, at most 4 MFMA steps along the rank
+    if ((cg + 1) * COLS <= p.N && rchunks <= 16) {  // a whole column group, at most 4 MFMA steps along the rank
         if constexpr (SMALL) {
             if (rchunks <= 8)
-                expand_unit_whole<E, 1, 2, 8>(p, Ba, r, slot0, nrows, cg * kExCols, smem);
+                expand_unit_whole<E, WAVES, 1, 2, 8>(p, Ba, r, slot0, nrows, cg * COLS, smem);
             else
-                expand_unit_whole<E, 1, 4, 4>(p, Ba, r, slot0, nrows, cg * kExCols, smem);
+                expand_unit_whole<E, WAVES, 1, 4, 4>(p, Ba, r, slot0, nrows, cg * COLS, smem);
         } else if (nrows <= 16) {
             if (rchunks <= 8)
-                expand_unit_whole<E, 1, 2, 8>(p, Ba, r, slot0, nrows, cg * kExCols, smem);
+                expand_unit_whole<E, WAVES, 1, 2, 8>(p, Ba, r, slot0, nrows, cg * COLS, smem);
             else
-                expand_unit_whole<E, 1, 4, 8>(p, Ba, r, slot0, nrows, cg * kExCols, smem);
+                expand_unit_whole<E, WAVES, 1, 4, 8>(p, Ba, r, slot0, nrows, cg * COLS, smem);
         } else {
             if (rchunks <= 8)
-                expand_unit_whole<E, 4, 2, 8>(p, Ba, r, slot0, nrows, cg * kExCols, smem);
+                expand_unit_whole<E, WAVES, 4, 2, 8>(p, Ba, r, slot0, nrows, cg * COLS, smem);
             else
-                expand_unit_whole<E, 4, 4, 4>(p, Ba, r, slot0, nrows, cg * kExCols, smem);
+                expand_unit_whole<E, WAVES, 4, 4, 4>(p, Ba, r, slot0, nrows, cg * COLS, smem);
         }
     } else if (SMALL || nrows <= 16) {
-        expand_unit<E, 1>(p, Ba, r, slot0, nrows, cg * kExCols, smem);
+        expand_unit<E, WAVES, 1>(p, Ba, r, slot0, nrows, cg * COLS, smem);
     } else {
-        expand_unit<E, 4>(p, Ba, r, slot0, nrows, cg * kExCols, smem);
+        expand_unit<E, WAVES, 4>(p, Ba, r, slot0, nrows, cg * COLS, smem);
     }
     LORA_TS(p.trace, 5);
 }
 
 }  // namespace
 
-size_t expand_smem_bytes(int r_max, int dtype) {
+static constexpr size_t expand_smem_bytes(int r_max, int dtype, int unit_rows) {
     const int ce = dtype == 1 ? 8 : 4;
-    return (size_t)kShrinkRows * (size_t)(r_max / ce + kExPad) * 16;
+    return (size_t)unit_rows * (size_t)(r_max / ce + kExPad) * 16;
 }
 
-// (ranks above ~480 need more than the default 64 KB of dynamic LDS: granted per kernel and device before the first launch)
+// Waves per workgroup: as few as let the workgroups whose rows of V fit a CU's LDS hold the waves that its registers do, 8 or
+// 16 of the small form.  Two, four and eight waves, us: 2000 rows on 150 adapters, 2048 -> 4096, bf16 rank 512 (67 KB) 222 / 165 / 171,
+// fp32 rank 256 (67 KB) 335 / 215 / 223, rank 512 (132 KB) 1012 / 565 / 421; 600 rows on 64 adapters, units of 16 rows, fp32 rank 512
+// (33 KB) - / 118 / 117.  (With one such adapter in a pool of rank 16 the fewest are best: bf16 rank 512 31.9 / 32.9 / 36.4, fp32 rank
+// 512 84.5 / 85.6 / 96.5.)
+static int expand_waves(size_t smem, bool small) {
+    const long wgs = (long)(kLdsBytesPerCu / smem), held = small ? 16 : 8;
+    return wgs * 2 >= held ? 2 : wgs * 4 >= held ? 4 : 8;
+}
+
+template <typename E, int WAVES>
+static hipError_t init_expand() {
+    // (ranks above ~480 need more than the default 64 KB of dynamic LDS: granted per kernel and device before the first launch)
+    const int dtype = sizeof(E) == 2 ? 1 : 0;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(expand_kernel<E, WAVES, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)expand_smem_bytes(kMaxRank, dtype, kShrinkRowsSmall));
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(expand_kernel<E, WAVES, false>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)expand_smem_bytes(kMaxRank, dtype, kShrinkRows));
+    return e;
+}
+static_assert(kLdsBytesPerCu / expand_smem_bytes(kMaxRank, 1, kShrinkRows) * 4 >= 8, "bf16 needs four waves at most");
 hipError_t init_expand_kernels() {
-    const void *fns[4] = {reinterpret_cast<const void *>(expand_kernel<__bf16, true>), reinterpret_cast<const void *>(expand_kernel<__bf16, false>),
-                          reinterpret_cast<const void *>(expand_kernel<float, true>), reinterpret_cast<const void *>(expand_kernel<float, false>)};
-    for (int i = 0; i < 4; ++i) {
-        const size_t smem = expand_smem_bytes(kMaxRank, i < 2 ? 1 : 0);
-        hipError_t e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    hipError_t e = init_expand<__bf16, 2>();
+    if (e == hipSuccess) e = init_expand<__bf16, 4>();
+    if (e == hipSuccess) e = init_expand<float, 2>();
+    if (e == hipSuccess) e = init_expand<float, 4>();
+    if (e == hipSuccess) e = init_expand<float, 8>();
+    return e;
+}
+
+template <typename E, int WAVES>
+static hipError_t launch_expand_waves(const ExpandArgs &a, bool small, long grid, size_t smem, hipStream_t stream, const KernelTimer *timer) {
+    const dim3 g((unsigned)grid), t(WAVES * 64);
+    return small ? launch_kernel(expand_kernel<E, WAVES, true>, g, t, smem, stream, timer, a)
+                 : launch_kernel(expand_kernel<E, WAVES, false>, g, t, smem, stream, timer, a);
 }
 
 hipError_t launch_expand(const ExpandArgs &a0, int dtype, hipStream_t stream, const KernelTimer *timer) {
     if (a0.max_units <= 0 || (a0.n_sets == 0 && a0.N <= 0)) return hipSuccess;
     ExpandArgs a = a0;
+    const bool small = a.unit_rows <= kShrinkRowsSmall;
+    const size_t smem = expand_smem_bytes(a.r_max, dtype, small ? kShrinkRowsSmall : kShrinkRows);
+    const int waves = expand_waves(smem, small), cols = ex_cols(waves);
     long grid;
     if (a.n_sets > 0) {
         grid = 0;
         for (int i = 0; i < a.n_sets; ++i) {
             a.set[i].block0 = (int32_t)grid;
-            grid += (long)a.max_units * ((a.set[i].N + kExCols - 1) / kExCols);
+            grid += (long)a.max_units * ((a.set[i].N + cols - 1) / cols);
         }
     } else {
-        a.col_groups = (a.N + kExCols - 1) / kExCols;
+        a.col_groups = (a.N + cols - 1) / cols;
         grid = (long)a.max_units * a.col_groups;
     }
     if (grid <= 0) return hipSuccess;
-    const size_t smem = expand_smem_bytes(a.r_max, dtype);
-    const bool small = a.unit_rows <= kShrinkRowsSmall;
     auto launch = [&](const ExpandArgs &b) {
-        const dim3 g((unsigned)grid), t(kExWaves * 64);
         if (dtype == 1)
-            return small ? launch_kernel(expand_kernel<__bf16, true>, g, t, smem, stream, timer, b)
-                         : launch_kernel(expand_kernel<__bf16, false>, g, t, smem, stream, timer, b);
-        return small ? launch_kernel(expand_kernel<float, true>, g, t, smem, stream, timer, b)
-                     : launch_kernel(expand_kernel<float, false>, g, t, smem, stream, timer, b);
+            return waves == 2 ? launch_expand_waves<__bf16, 2>(b, small, grid, smem, stream, timer)
+                              : launch_expand_waves<__bf16, 4>(b, small, grid, smem, stream, timer);
+        return waves == 2   ? launch_expand_waves<float, 2>(b, small, grid, smem, stream, timer)
+               : waves == 4 ? launch_expand_waves<float, 4>(b, small, grid, smem, stream, timer)
+                            : launch_expand_waves<float, 8>(b, small, grid, smem, stream, timer);
     };
 #ifdef LORA_TRACE
     return trace_launch("expand", grid, [&](long long *buf) {

@@ -95,6 +95,31 @@ def test_shrink_waves_of_a_workgroup(fake, T, n_ad, K, dtype, waves):
     """)
 
 
+@pytest.mark.parametrize("T,n_ad,rank,dtype,waves,kb", [
+    (600, 64, 64, 1, 2, 2.25), (600, 64, 512, 1, 2, 16.25), (600, 64, 128, 0, 2, 8.25), (600, 64, 256, 0, 2, 16.25),
+    (600, 64, 320, 0, 4, 20.25), (600, 64, 512, 0, 4, 32.25), (2000, 150, 256, 1, 2, 33), (2000, 150, 320, 1, 4, 41),
+    (2000, 150, 512, 1, 4, 65), (2000, 150, 128, 0, 2, 33), (2000, 150, 256, 0, 4, 65), (2000, 150, 320, 0, 8, 81), (2000, 150, 512, 0, 8, 129)])
+def test_expand_waves_of_a_workgroup(fake, T, n_ad, rank, dtype, waves, kb):
+    """LDS for the rows of V that a unit of the plan can have, and as few waves as keep 8 (16 with units of 16 rows) on a CU of 160 KB."""
+    fake_hip.run(fake, f"""
+        T, n_ad, rank, dtype, waves, kb = {T}, {n_ad}, {rank}, {dtype}, {waves}, {kb}
+        plan = make_plan(np.arange(T) % n_ad, np.ones(T, int), np.full(n_ad, rank))
+        rows = plan.unit_rows
+        assert rows == (16 if T == 600 else 64)
+        assert kb * 1024 == rows * (rank * (2 if dtype else 4) + 16)
+        B.lora_ctx_set_option(ctx, "expand_split", 1)
+        F.fake_reset()
+        d = make_desc(plan, 2048, 2600, dtype)
+        B.lora_linear(ctx, plan, d, 0)
+        units = T // rows + n_ad
+        shape = [(g, b) for name, g, b in launched() if "expand_kernel" in name]
+        assert shape == [((units * -(-2600 // (128 * waves)), 1, 1), (64 * waves, 1, 1))], shape
+        held = 16 if rows == 16 else 8
+        assert waves * (160 // kb) >= held
+        assert waves == 2 or waves // 2 * (160 // kb) < held
+    """)
+
+
 def test_finishing_kernel_only_with_a_workspace_of_the_preferred_size(fake):
     """The decode path's finishing kernel rounds V to bf16; calls with less workspace keep the reduction, whose V is fp32."""
     fake_hip.run(fake, """
