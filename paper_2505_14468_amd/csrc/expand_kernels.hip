@@ -128,9 +128,20 @@ __device__ __forceinline__ void expand_unit(const ExpandArgs &p, const E *Ba, in
     // ---- stage the unit's rows of V (original row order in memory: gather through the row map) ----
     // V first: it comes from L2 and loads return in order -- behind B_a's loads from HBM it would arrive last.
     LORA_TS(p.trace, 2);  // row map read
-    for (int e = tid; e < nrows * rchunks; e += WAVES * 64) {
-        const int t = e / rchunks, c = e - t * rchunks;
-        vs[t * vstride + c] = load_chunk(V + (int64_t)p.plan.perm[slot0 + t] * p.r_max + (int64_t)c * CE);
+    // (Four pieces per thread at a time, unguarded: a loop of one would be two round trips per piece.)
+    const int pieces = nrows * rchunks;
+    for (int e0 = tid; e0 < pieces; e0 += 4 * WAVES * 64) {
+        chunk_t v[4];
+        int dst[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = min(e0 + u * WAVES * 64, pieces - 1);
+            const int t = e / rchunks, c = e - t * rchunks;
+            dst[u] = t * vstride + c;
+            v[u] = load_chunk(V + (int64_t)p.plan.perm[slot0 + t] * p.r_max + (int64_t)c * CE);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) vs[dst[u]] = v[u];  // (past the last piece: the last one again)
     }
     // ---- a ring of kExRing groups of B_a loads in flight per wave ----
     chunk_t ring[kExRing][kExGroup];
@@ -155,12 +166,13 @@ __device__ __forceinline__ void expand_unit(const ExpandArgs &p, const E *Ba, in
     }
 }
 
-// The common shapes -- a whole group of columns, rank <= 128 (bf16) -- with every index a compile-time constant:
+// The common shapes -- rank <= 128 (bf16) -- with every index a compile-time constant:
 // S MFMA steps per 16-column block (2: at most 8 chunks of rank, 4: at most 16), the B_a loads of RING blocks in flight
 // per wave (all 8: everything is requested before the first MFMA), the results of all 8 blocks kept in
 // registers and stored after the last load has been consumed.  Loads and stores are counted by one in-order
 // counter, so a store issued between loads makes the next wait for a load wait for the store's acknowledgement
-// from memory as well; and no load sits behind a branch, so that the compiler can count the loads in flight.
+// from memory as well; and no load sits behind a branch, so that the compiler can count the loads in flight.  In the last group of
+// columns, if it is not a whole one, the rows of B_a past N are clamped and their columns not stored.
 template <typename E, int WAVES, int TB, int S, int RING>
 __device__ __forceinline__ void expand_unit_whole(const ExpandArgs &p, const E *Ba, int r, int slot0, int nrows, int nwg0,
                                                   unsigned char *smem) {
@@ -197,7 +209,7 @@ __device__ __forceinline__ void expand_unit_whole(const ExpandArgs &p, const E *
         kc[st] = kok[st] ? c : 0;
     }
     auto load_block = [&](int b, chunk_t (&wf)[S]) {
-        const E *brow = Ba + (int64_t)(block_n0(b) + li) * r;
+        const E *brow = Ba + (int64_t)min(block_n0(b) + li, p.N - 1) * r;
 #pragma unroll
         for (int st = 0; st < S; ++st) wf[st] = load_chunk(brow + kc[st] * CE);
     };
@@ -236,8 +248,22 @@ __device__ __forceinline__ void expand_unit_whole(const ExpandArgs &p, const E *
         const int t = tb * 16 + li;
         if (t >= nrows) continue;
         float *drow = p.D + (int64_t)p.plan.perm[slot0 + t] * p.ldd;
+        if (nwg0 + ex_cols(WAVES) <= p.N) {
 #pragma unroll
-        for (int b = 0; b < NBLK; ++b) store4(drow + block_n0(b) + lg * 4, acc[b][tb][0], acc[b][tb][1], acc[b][tb][2], acc[b][tb][3]);
+            for (int b = 0; b < NBLK; ++b) store4(drow + block_n0(b) + lg * 4, acc[b][tb][0], acc[b][tb][1], acc[b][tb][2], acc[b][tb][3]);
+            continue;
+        }
+#pragma unroll
+        for (int b = 0; b < NBLK; ++b) {
+            const int n = block_n0(b) + lg * 4;
+            if (n + 3 < p.N) {
+                store4(drow + n, acc[b][tb][0], acc[b][tb][1], acc[b][tb][2], acc[b][tb][3]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < p.N) drow[n + e] = acc[b][tb][e];
+            }
+        }
     }
 }
 
@@ -286,7 +312,7 @@ __global__ __launch_bounds__(WAVES * 64, SMALL ? 4 : 2) void expand_kernel(Expan
         return;
     }
     const int rchunks = r / Elem<E>::CE;
-    if ((cg + 1) * COLS <= p.N && rchunks <= 16) {  // a whole column group, at most 4 MFMA steps along the rank
+    if (rchunks <= 16) {  // at most 4 MFMA steps along the rank
         if constexpr (SMALL) {
             if (rchunks <= 8)
                 expand_unit_whole<E, WAVES, 1, 2, 8>(p, Ba, r, slot0, nrows, cg * COLS, smem);
