@@ -9,7 +9,7 @@
 // is a weight-streaming problem laid out like the shrink:
 //
 //   * a workgroup = one work unit of the plan's list (<= 64 rows of one segment, <= 16 in small plans) x 256 output
-//     columns (512 or 1024 where the ranks are large);
+//     columns (128 to 1024 where the ranks are large);
 //   * the unit's rows of V (<= 64 x r, a few KB) are staged in LDS once; as MFMA operand they are
 //     read from there, so global loads carry B_a only;
 //   * each of the 2 waves (4, 8) walks 16-column blocks; MFMA 16x16x32 with the 16 output columns as M
@@ -34,14 +34,18 @@ namespace {
 // one 4096 -> 4096 16.6 / 15.0 / 14.2; 1500 one-token requests 18.8 / 17.0 / 16.0; 365 rows 7.9 / 5.8 / 5.6; 2048 rows on some 170
 // adapters of rank 128, 5120 -> 13824 (714 MB of B_a and D) 170 / 163 / 164.
 // Four or eight waves where the LDS for a unit's V leaves too few workgroups of two on a CU: see expand_waves.
-constexpr int kExBlocksPerWave = 8;                                           // 16-column blocks per wave
-constexpr int ex_cols(int waves) { return waves * kExBlocksPerWave * 16; }  // output columns per workgroup
+constexpr int ex_cols(int waves, int blocks) { return waves * blocks * 16; }  // output columns per workgroup (16-column blocks per wave)
 constexpr int kExGroup = 4;                                       // MFMA steps per load group
 constexpr int kExRing = 4;                                        // load groups in flight per wave
 constexpr int kExPad = 1;                                         // chunks of padding per staged row of V
 constexpr size_t kLdsBytesPerCu = 160 * 1024;
+// Four blocks per wave instead of eight where the rows of B_a are long: what a wave streams for eight lasts longer than a unit's
+// set-up.  Eight and four, us: bf16 rank 128, 600 rows on 100 adapters, N 358 5.5 / 5.2, 2048 12.0 / 10.7, 4096 22.3 / 19.5, 11008 61.8
+// / 57.2; fp32 rank 128, N 358 18.1 / 12.6, 749 22.4 / 16.1, 4096 53.5 / 50.2, 11008 129 / 124; but rank 16 to 32 bf16 4096 -> 4096, 1500
+// rows 16.4 / 18.0, rank 8 to 64, 1216 rows 16.0 / 17.8, fp32 rank 16, 600 rows, N 4096 12.7 / 12.2, 1500 rows, N 2048 29.0 / 34.4.
+constexpr int kExLongRow = 256;  // bytes
 
-template <typename E, int WAVES, int TB>
+template <typename E, int WAVES, int NBLK, int TB>
 __device__ __forceinline__ void expand_unit(const ExpandArgs &p, const E *Ba, int r, int slot0, int nrows, int nwg0,
                                             unsigned char *smem) {
     constexpr int CE = Elem<E>::CE;
@@ -71,12 +75,12 @@ __device__ __forceinline__ void expand_unit(const ExpandArgs &p, const E *Ba, in
     const int groups = (steps + kExGroup - 1) / kExGroup;
     auto chunk_of = [&](int st) { return (st >> 1) * 8 + 2 * lg + (st & 1); };
 
-    // this wave's column blocks, b = 0 .. kExBlocksPerWave-1 (those below N): pairs of adjacent blocks (32 columns:
+    // this wave's column blocks, b = 0 .. NBLK-1 (those below N): pairs of adjacent blocks (32 columns:
     // a row's two stores fall into one 128-byte line), pair p of wave w at column 32 * (w + WAVES p)
     auto block_n0 = [&](int b) { return nwg0 + (2 * wave + (b & 1) + 2 * WAVES * (b >> 1)) * 16; };
     int nblk = 0;
 #pragma unroll
-    for (int b = 0; b < kExBlocksPerWave; ++b) nblk += block_n0(b) < p.N ? 1 : 0;
+    for (int b = 0; b < NBLK; ++b) nblk += block_n0(b) < p.N ? 1 : 0;
     const int total = nblk * groups;  // (block, group) pairs, walked in order
 
     auto load_group = [&](int q, chunk_t (&wf)[kExGroup]) {
@@ -129,19 +133,20 @@ __device__ __forceinline__ void expand_unit(const ExpandArgs &p, const E *Ba, in
     // V first: it comes from L2 and loads return in order -- behind B_a's loads from HBM it would arrive last.
     LORA_TS(p.trace, 2);  // row map read
     // (Four pieces per thread at a time, unguarded: a loop of one would be two round trips per piece.)
+    constexpr int VP = 4;
     const int pieces = nrows * rchunks;
-    for (int e0 = tid; e0 < pieces; e0 += 4 * WAVES * 64) {
-        chunk_t v[4];
-        int dst[4];
+    for (int e0 = tid; e0 < pieces; e0 += VP * WAVES * 64) {
+        chunk_t v[VP];
+        int dst[VP];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < VP; ++u) {
             const int e = min(e0 + u * WAVES * 64, pieces - 1);
             const int t = e / rchunks, c = e - t * rchunks;
             dst[u] = t * vstride + c;
             v[u] = load_chunk(V + (int64_t)p.plan.perm[slot0 + t] * p.r_max + (int64_t)c * CE);
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) vs[dst[u]] = v[u];  // (past the last piece: the last one again)
+        for (int u = 0; u < VP; ++u) vs[dst[u]] = v[u];  // (past the last piece: the last one again)
     }
     // ---- a ring of kExRing groups of B_a loads in flight per wave ----
     chunk_t ring[kExRing][kExGroup];
@@ -168,16 +173,16 @@ __device__ __forceinline__ void expand_unit(const ExpandArgs &p, const E *Ba, in
 
 // The common shapes -- rank <= 128 (bf16) -- with every index a compile-time constant:
 // S MFMA steps per 16-column block (2: at most 8 chunks of rank, 4: at most 16), the B_a loads of RING blocks in flight
-// per wave (all 8: everything is requested before the first MFMA), the results of all 8 blocks kept in
+// per wave (all of them: everything is requested before the first MFMA), the results of all NBLK blocks kept in
 // registers and stored after the last load has been consumed.  Loads and stores are counted by one in-order
 // counter, so a store issued between loads makes the next wait for a load wait for the store's acknowledgement
 // from memory as well; and no load sits behind a branch, so that the compiler can count the loads in flight.  In the last group of
 // columns, if it is not a whole one, the rows of B_a past N are clamped and their columns not stored.
-template <typename E, int WAVES, int TB, int S, int RING>
-__device__ __forceinline__ void expand_unit_whole(const ExpandArgs &p, const E *Ba, int r, int slot0, int nrows, int nwg0,
+template <typename E, int WAVES, int NBLK, int TB, int S, int RING0>
+__device__ __forceinline__ void expand_unit_short(const ExpandArgs &p, const E *Ba, int r, int slot0, int nrows, int nwg0,
                                                   unsigned char *smem) {
     constexpr int CE = Elem<E>::CE;
-    constexpr int NBLK = kExBlocksPerWave;
+    constexpr int RING = RING0 < NBLK ? RING0 : NBLK;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lg = lane >> 4;
     const int rchunks = r / CE;
@@ -248,7 +253,7 @@ __device__ __forceinline__ void expand_unit_whole(const ExpandArgs &p, const E *
         const int t = tb * 16 + li;
         if (t >= nrows) continue;
         float *drow = p.D + (int64_t)p.plan.perm[slot0 + t] * p.ldd;
-        if (nwg0 + ex_cols(WAVES) <= p.N) {
+        if (nwg0 + ex_cols(WAVES, NBLK) <= p.N) {
 #pragma unroll
             for (int b = 0; b < NBLK; ++b) store4(drow + block_n0(b) + lg * 4, acc[b][tb][0], acc[b][tb][1], acc[b][tb][2], acc[b][tb][3]);
             continue;
@@ -271,9 +276,9 @@ __device__ __forceinline__ void expand_unit_whole(const ExpandArgs &p, const E *
 // half the loads in flight, fits 128 registers (4 waves per SIMD): twice as many workgroups share a CU, and a unit of a few
 // rows is a chain of dependent round trips (work list, row map and adapter table, operands) more than it is a
 // stream, and one workgroup's chain overlaps the others' loads.
-template <typename E, int WAVES, bool SMALL>
+template <typename E, int WAVES, int NBLK, bool SMALL>
 __global__ __launch_bounds__(WAVES * 64, SMALL ? 4 : 2) void expand_kernel(ExpandArgs p0) {
-    constexpr int COLS = ex_cols(WAVES);
+    constexpr int COLS = ex_cols(WAVES, NBLK);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     LORA_TS(p0.trace, 0);
     // several projections of the same batch: the single-projection grids one after the other
@@ -315,24 +320,24 @@ __global__ __launch_bounds__(WAVES * 64, SMALL ? 4 : 2) void expand_kernel(Expan
     if (rchunks <= 16) {  // at most 4 MFMA steps along the rank
         if constexpr (SMALL) {
             if (rchunks <= 8)
-                expand_unit_whole<E, WAVES, 1, 2, 8>(p, Ba, r, slot0, nrows, cg * COLS, smem);
+                expand_unit_short<E, WAVES, NBLK, 1, 2, 8>(p, Ba, r, slot0, nrows, cg * COLS, smem);
             else
-                expand_unit_whole<E, WAVES, 1, 4, 4>(p, Ba, r, slot0, nrows, cg * COLS, smem);
+                expand_unit_short<E, WAVES, NBLK, 1, 4, 4>(p, Ba, r, slot0, nrows, cg * COLS, smem);
         } else if (nrows <= 16) {
             if (rchunks <= 8)
-                expand_unit_whole<E, WAVES, 1, 2, 8>(p, Ba, r, slot0, nrows, cg * COLS, smem);
+                expand_unit_short<E, WAVES, NBLK, 1, 2, 8>(p, Ba, r, slot0, nrows, cg * COLS, smem);
             else
-                expand_unit_whole<E, WAVES, 1, 4, 8>(p, Ba, r, slot0, nrows, cg * COLS, smem);
+                expand_unit_short<E, WAVES, NBLK, 1, 4, 8>(p, Ba, r, slot0, nrows, cg * COLS, smem);
         } else {
             if (rchunks <= 8)
-                expand_unit_whole<E, WAVES, 4, 2, 8>(p, Ba, r, slot0, nrows, cg * COLS, smem);
+                expand_unit_short<E, WAVES, NBLK, 4, 2, 8>(p, Ba, r, slot0, nrows, cg * COLS, smem);
             else
-                expand_unit_whole<E, WAVES, 4, 4, 4>(p, Ba, r, slot0, nrows, cg * COLS, smem);
+                expand_unit_short<E, WAVES, NBLK, 4, 4, 4>(p, Ba, r, slot0, nrows, cg * COLS, smem);
         }
     } else if (SMALL || nrows <= 16) {
-        expand_unit<E, WAVES, 1>(p, Ba, r, slot0, nrows, cg * COLS, smem);
+        expand_unit<E, WAVES, NBLK, 1>(p, Ba, r, slot0, nrows, cg * COLS, smem);
     } else {
-        expand_unit<E, WAVES, 4>(p, Ba, r, slot0, nrows, cg * COLS, smem);
+        expand_unit<E, WAVES, NBLK, 4>(p, Ba, r, slot0, nrows, cg * COLS, smem);
     }
     LORA_TS(p.trace, 5);
 }
@@ -354,20 +359,22 @@ static int expand_waves(size_t smem, bool small) {
     return wgs * 2 >= held ? 2 : wgs * 4 >= held ? 4 : 8;
 }
 
-template <typename E, int WAVES>
+template <typename E, int WAVES, int NBLK = 8>
 static hipError_t init_expand() {
     // (ranks above ~480 need more than the default 64 KB of dynamic LDS: granted per kernel and device before the first launch)
     const int dtype = sizeof(E) == 2 ? 1 : 0;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(expand_kernel<E, WAVES, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(expand_kernel<E, WAVES, NBLK, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)expand_smem_bytes(kMaxRank, dtype, kShrinkRowsSmall));
     if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(expand_kernel<E, WAVES, false>), hipFuncAttributeMaxDynamicSharedMemorySize,
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(expand_kernel<E, WAVES, NBLK, false>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)expand_smem_bytes(kMaxRank, dtype, kShrinkRows));
     return e;
 }
 static_assert(kLdsBytesPerCu / expand_smem_bytes(kMaxRank, 1, kShrinkRows) * 4 >= 8, "bf16 needs four waves at most");
 hipError_t init_expand_kernels() {
     hipError_t e = init_expand<__bf16, 2>();
+    if (e == hipSuccess) e = init_expand<__bf16, 2, 4>();
+    if (e == hipSuccess) e = init_expand<float, 2, 4>();
     if (e == hipSuccess) e = init_expand<__bf16, 4>();
     if (e == hipSuccess) e = init_expand<float, 2>();
     if (e == hipSuccess) e = init_expand<float, 4>();
@@ -375,11 +382,11 @@ hipError_t init_expand_kernels() {
     return e;
 }
 
-template <typename E, int WAVES>
+template <typename E, int WAVES, int NBLK = 8>
 static hipError_t launch_expand_waves(const ExpandArgs &a, bool small, long grid, size_t smem, hipStream_t stream, const KernelTimer *timer) {
     const dim3 g((unsigned)grid), t(WAVES * 64);
-    return small ? launch_kernel(expand_kernel<E, WAVES, true>, g, t, smem, stream, timer, a)
-                 : launch_kernel(expand_kernel<E, WAVES, false>, g, t, smem, stream, timer, a);
+    return small ? launch_kernel(expand_kernel<E, WAVES, NBLK, true>, g, t, smem, stream, timer, a)
+                 : launch_kernel(expand_kernel<E, WAVES, NBLK, false>, g, t, smem, stream, timer, a);
 }
 
 hipError_t launch_expand(const ExpandArgs &a0, int dtype, hipStream_t stream, const KernelTimer *timer) {
@@ -387,20 +394,29 @@ hipError_t launch_expand(const ExpandArgs &a0, int dtype, hipStream_t stream, co
     ExpandArgs a = a0;
     const bool small = a.unit_rows <= kShrinkRowsSmall;
     const size_t smem = expand_smem_bytes(a.r_max, dtype, small ? kShrinkRowsSmall : kShrinkRows);
-    const int waves = expand_waves(smem, small), cols = ex_cols(waves);
-    long grid;
-    if (a.n_sets > 0) {
-        grid = 0;
-        for (int i = 0; i < a.n_sets; ++i) {
-            a.set[i].block0 = (int32_t)grid;
-            grid += (long)a.max_units * ((a.set[i].N + cols - 1) / cols);
+    const int waves = expand_waves(smem, small);
+    int cols = 0;
+    long grid = 0;
+    auto lay_out = [&](int blocks) {
+        cols = ex_cols(waves, blocks);
+        if (a.n_sets > 0) {
+            grid = 0;
+            for (int i = 0; i < a.n_sets; ++i) {
+                a.set[i].block0 = (int32_t)grid;
+                grid += (long)a.max_units * ((a.set[i].N + cols - 1) / cols);
+            }
+        } else {
+            a.col_groups = (a.N + cols - 1) / cols;
+            grid = (long)a.max_units * a.col_groups;
         }
-    } else {
-        a.col_groups = (a.N + cols - 1) / cols;
-        grid = (long)a.max_units * a.col_groups;
-    }
+    };
+    const bool halves = waves == 2 && a.r_max * (dtype == 1 ? 2 : 4) >= kExLongRow;
+    lay_out(halves ? 4 : 8);
     if (grid <= 0) return hipSuccess;
     auto launch = [&](const ExpandArgs &b) {
+        if (halves)
+            return dtype == 1 ? launch_expand_waves<__bf16, 2, 4>(b, small, grid, smem, stream, timer)
+                              : launch_expand_waves<float, 2, 4>(b, small, grid, smem, stream, timer);
         if (dtype == 1)
             return waves == 2 ? launch_expand_waves<__bf16, 2>(b, small, grid, smem, stream, timer)
                               : launch_expand_waves<__bf16, 4>(b, small, grid, smem, stream, timer);

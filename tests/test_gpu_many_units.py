@@ -43,11 +43,11 @@ def test_bf16_against_the_oracle(K, N):
     reset_options()
 
 
-@pytest.mark.parametrize("dtype,rank", [("bf16", 320), ("bf16", 512), ("f32", 256), ("f32", 320), ("f32", 512)])
+@pytest.mark.parametrize("dtype,rank", [("bf16", 64), ("bf16", 128), ("bf16", 320), ("bf16", 512), ("f32", 32), ("f32", 128), ("f32", 256), ("f32", 320), ("f32", 512)])
 @pytest.mark.parametrize("rows", [16, 64])
-def test_wide_expand_workgroups_are_exact(dtype, rank, rows):
-    """Ranks whose V leaves room for few workgroups on a CU, units of both sizes, small ranks beside the large: whole column
-    groups of the two-, four- and eight-wave forms and what is left of them, integers that every sum and V in bf16 keep exactly."""
+def test_expand_workgroups_are_exact(dtype, rank, rows):
+    """Ranks up to those whose V leaves room for few workgroups on a CU, units of both sizes, small ranks beside the large: whole
+    column groups of the two-, four- and eight-wave forms and what is left of them, integers that every sum and V in bf16 keep exactly."""
     from gpu_common import ctx, gpu_linear, reset_options
     from oracle import oracle_workload
     from workloads import bf16_bits_from_f32, f32_from_bf16_bits

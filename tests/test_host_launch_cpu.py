@@ -96,11 +96,12 @@ def test_shrink_waves_of_a_workgroup(fake, T, n_ad, K, dtype, waves):
 
 
 @pytest.mark.parametrize("T,n_ad,rank,dtype,waves,kb", [
-    (600, 64, 64, 1, 2, 2.25), (600, 64, 512, 1, 2, 16.25), (600, 64, 128, 0, 2, 8.25), (600, 64, 256, 0, 2, 16.25),
+    (600, 64, 64, 1, 2, 2.25), (600, 64, 120, 1, 2, 4), (600, 64, 56, 0, 2, 3.75), (600, 64, 128, 1, 2, 4.25), (600, 64, 512, 1, 2, 16.25), (600, 64, 128, 0, 2, 8.25), (600, 64, 256, 0, 2, 16.25),
     (600, 64, 320, 0, 4, 20.25), (600, 64, 512, 0, 4, 32.25), (2000, 150, 256, 1, 2, 33), (2000, 150, 320, 1, 4, 41),
     (2000, 150, 512, 1, 4, 65), (2000, 150, 128, 0, 2, 33), (2000, 150, 256, 0, 4, 65), (2000, 150, 320, 0, 8, 81), (2000, 150, 512, 0, 8, 129)])
 def test_expand_waves_of_a_workgroup(fake, T, n_ad, rank, dtype, waves, kb):
-    """LDS for the rows of V that a unit of the plan can have, and as few waves as keep 8 (16 with units of 16 rows) on a CU of 160 KB."""
+    """LDS for the rows of V that a unit of the plan can have, and as few waves as keep 8 (16 with units of 16 rows) on a CU of 160 KB;
+    eight 16-column blocks per wave, four with two waves and rows of B_a of 256 bytes and more."""
     fake_hip.run(fake, f"""
         T, n_ad, rank, dtype, waves, kb = {T}, {n_ad}, {rank}, {dtype}, {waves}, {kb}
         plan = make_plan(np.arange(T) % n_ad, np.ones(T, int), np.full(n_ad, rank))
@@ -113,7 +114,8 @@ def test_expand_waves_of_a_workgroup(fake, T, n_ad, rank, dtype, waves, kb):
         B.lora_linear(ctx, plan, d, 0)
         units = T // rows + n_ad
         shape = [(g, b) for name, g, b in launched() if "expand_kernel" in name]
-        assert shape == [((units * -(-2600 // (128 * waves)), 1, 1), (64 * waves, 1, 1))], shape
+        blocks = 4 if waves == 2 and rank * (2 if dtype else 4) >= 256 else 8
+        assert shape == [((units * -(-2600 // (16 * blocks * waves)), 1, 1), (64 * waves, 1, 1))], shape
         held = 16 if rows == 16 else 8
         assert waves * (160 // kb) >= held
         assert waves == 2 or waves // 2 * (160 // kb) < held
