@@ -467,14 +467,16 @@ GemmChoice choose_gemm_sets(const lora_ctx *ctx, int64_t T, int32_t K, const int
     }
     const int cus = ctx ? ctx->num_cu : 256;
     // (192x128: 1500 rows on 4096 -> 4096 in fp32 481 -> 368 us per layer, in bf16 65 -> 62; 1300 rows on 5120 -> 13824 221 -> 205)
-    // Time model: rounds of one tile per CU, a tile costing its area over its MFMA efficiency (measured per
-    // round at K = 4096: 256x256 104 us, 256x224 100 us, 256x192 88 us, 256x128 64 us, 128x192 51 us, 128x128 34 us, all on 4 waves).
-    // Since then every round has become shorter (256x256 107 us where the same kernel took 116, 256x192 78, 128x192 46, 128x128 33.5,
-    // one part), the order is the same but for 128x128 in bf16 on long contraction axes, which holds twice the operand traffic
-    // per flop against the power: 0.72 instead of 0.77 takes 256x192 in its place where the two were close -- 1380 rows 5120 ->
-    // 13824 214 -> 173 us, 1764 rows 4096 -> 11008 162 -> 138, 868 rows 4096 -> 22016 166 -> 149, 3830 rows 5120 -> 5120 175 -> 161 --
-    // but not below K = 4096, where the larger tile's start and end weigh more (3184 rows 2048 -> 6000: 73 and 77; 6413 rows 1024
-    // -> 3000: 43 and 48).  At 0.68 it would also give way to 128x192, which loses (556 rows 4096 -> 22016: 125 and 133).
+    // Time model: rounds of one tile per CU, a tile costing its area over its MFMA efficiency.  The efficiencies are those of the
+    // kernel that staged its tiles through registers (us per round at K = 4096: 256x256 104, 256x224 100, 256x192 88, 256x128 64, 128x192
+    // 51, 128x128 34), and choices that were measured against each other rest on them.  They are not what a round takes now -- bf16,
+    // K = 4096: 256x256 97.9, 256x224 87.4, 256x192 75.7, 256x128 55.1, 128x192 43.7, 192x128 43.6, 128x128 32.6, 64x64 20.3, area per time
+    // relative to 256x256 0.98, 0.97, 0.89, 0.84, 0.84, 0.75, 0.30; K = 1024: 0.98, 0.97, 0.85, 0.78, 0.79, 0.71, 0.33; K = 11008: 0.99,
+    // 0.97, 0.90, 0.86, 0.86, 0.78, 0.31; fp32: 1.00 to 0.97, 64x64 0.91 -- and the model knows no start and end of a tile.
+    // Of 128x128 against 256x192, the pair where that cost most, 24 shapes in which the two are close by this table, 128x128 over
+    // 256x192: K = 2048 0.88 to 0.97; 3072 0.96 to 1.00, and 1.13 to 1.23 with N = 22016; 3584 0.96 to 1.01, 1.13 to 1.26; 4096 0.97 to 1.03,
+    // 1.07 to 1.19; 5120 1.02 to 1.31; 8192 1.01 to 1.22; 11008 1.15 to 1.36.  So from K = 4096 on 128x128 counts 0.72 instead of 0.77, which
+    // takes 256x192 there.  At 0.68 it would also give way to 128x192, which loses (556 rows 4096 -> 22016: 125 us and 133).
     const double eff128 = dtype == LORA_DTYPE_BF16 && K >= 4096 ? 0.72 : 0.77;
     struct Cand {
         int variant, bm, bn;
