@@ -61,12 +61,11 @@ def holder(d, n_clients):
     return 0 if same else 1
 
 
-def step(d, what, name, others):
-    """Say that client `name` (None: nobody) has come to `what`, and wait until all of `others` have."""
-    if name is not None:
-        open(os.path.join(d, f"{what}_{name}"), "w").close()
+def step(d, what, name, clients):
+    """Say that client `name` has come to `what`, and wait until all clients have."""
+    open(os.path.join(d, f"{what}_{name}"), "w").close()
     t0 = time.time()
-    while not all(os.path.exists(os.path.join(d, f"{what}_{o}")) for o in others):
+    while not all(os.path.exists(os.path.join(d, f"{what}_{i}")) for i in range(clients)):
         if time.time() - t0 > 120:
             raise RuntimeError(f"waited for {what}")
         time.sleep(0.01)
@@ -87,16 +86,17 @@ def client(d, name):
     info = json.load(open(os.path.join(d, "handle.json")))
     ctx = rt.Context(0)
     torch.cuda.synchronize()
-    # What is free on the device counts every process's allocations, so nobody else allocates between the two readings: all
-    # clients are set up first, then they open the handle one after the other, then they go on together.
-    step(d, "ready", name, [str(i) for i in range(info["clients"])])
-    step(d, "opened", None, [str(i) for i in range(int(name))])
+    # What is free on the device counts every process's allocations: between the two readings the clients, all set up before, do
+    # nothing but open the handle, all at once, and what has gone is what all their mappings take.
+    step(d, "ready", name, info["clients"])
     free0, _ = torch.cuda.mem_get_info()
+    step(d, "open", name, info["clients"])
     t1 = time.perf_counter()
     ptr = B.lora_backbone_open(0, bytes.fromhex(info["handle"]))
     open_ms = (time.perf_counter() - t1) * 1e3
+    step(d, "opened", name, info["clients"])
     free1, _ = torch.cuda.mem_get_info()
-    step(d, "opened", name, [str(i) for i in range(info["clients"])])
+    step(d, "go_on", name, info["clients"])
     W0 = torch.as_tensor(_Raw(ptr, (N, K)), device="cuda").view(torch.bfloat16)  # zero-copy: the holder's memory
     assert W0.data_ptr() == ptr
     rng = np.random.default_rng(int(name) + 1)
@@ -117,7 +117,7 @@ def client(d, name):
     del W0
     B.lora_backbone_close(0, ptr)
     ctx.close()
-    out = {"err_over_rms": worst, "open_ms": open_ms, "device_bytes_taken_by_the_mapping": int(free0 - free1),
+    out = {"err_over_rms": worst, "open_ms": open_ms, "device_bytes_taken_by_the_mappings": int(free0 - free1),
            "backbone_bytes": info["bytes"]}
     with open(os.path.join(d, f"client_{name}.json"), "w") as f:
         json.dump(out, f)
