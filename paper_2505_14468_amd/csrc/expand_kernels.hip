@@ -410,8 +410,12 @@ hipError_t launch_expand(const ExpandArgs &a0, int dtype, hipStream_t stream, co
             grid = (long)a.max_units * a.col_groups;
         }
     };
-    const bool halves = waves == 2 && a.r_max * (dtype == 1 ? 2 : 4) >= kExLongRow;
+    bool halves = waves == 2 && a.r_max * (dtype == 1 ? 2 : 4) >= kExLongRow;
     lay_out(halves ? 4 : 8);
+    if (halves && grid * (waves * 64) >= (1l << 32)) {  // (a launch has fewer than 2^32 threads)
+        halves = false;
+        lay_out(8);
+    }
     if (grid <= 0) return hipSuccess;
     auto launch = [&](const ExpandArgs &b) {
         if (halves)

@@ -122,6 +122,20 @@ def test_expand_waves_of_a_workgroup(fake, T, n_ad, rank, dtype, waves, kb):
     """)
 
 
+def test_expand_grid_stays_launchable(fake):
+    """65536 one-row requests on as many adapters of rank 128, 65536 columns: four blocks per wave would be more than 2^32 threads."""
+    fake_hip.run(fake, """
+        n, N = 65536, 65536
+        ids, ones, ranks = np.arange(n), np.ones(n, int), np.full(n, 128)
+        plan = make_plan(ids, ones, ranks)
+        d = make_desc(plan, 16, N)
+        F.fake_reset()
+        B.lora_linear(ctx, plan, d, 0)
+        shape = [(g, b) for name, g, b in launched() if "expand_kernel" in name]
+        assert shape == [(((n // 64 + n) * (N // 256), 1, 1), (128, 1, 1))], shape
+    """)
+
+
 def test_finishing_kernel_only_with_a_workspace_of_the_preferred_size(fake):
     """The decode path's finishing kernel rounds V to bf16; calls with less workspace keep the reduction, whose V is fp32."""
     fake_hip.run(fake, """
