@@ -39,10 +39,10 @@ METRIC = "multi-LoRA linear TFLOP/s + adapter-path GB/s (roofline %), ms/layer"
 PEAK_HBM_GBPS = 8000.0      # MI355X HBM3E, published
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA, published
 PEAK_F32_TFLOPS = 157.3     # MI355X fp32 matrix, published
-# ceilings measured on this part (a long streaming read; a register-only bf16 MFMA loop on random operands, whose
-# clock is power-limited to ~1.7 GHz): context beside the published peaks, which `frac` is computed against
+# ceilings measured on this part (a long streaming read; a register-only loop of 16x16x32 bf16 MFMAs, the tiled GEMM's shape, on
+# normal operands, with the clock that the power limit leaves it): context beside the published peaks, which `frac` is computed against
 MEASURED_HBM_GBPS = 6500.0
-MEASURED_BF16_TFLOPS = 1700.0
+MEASURED_BF16_TFLOPS = 2040.0
 HBM_BOUND = {0: False, 1: True, 2: False, 3: False, 4: False}  # which roofline bounds the dominant kernel
 PLAN_REUSE = 7 * 32  # layer calls that share one plan in a model step (seven projections x 32 decoder layers)
 HEADLINE = 2
