@@ -1,6 +1,6 @@
-"""Batches of more work units than two workgroups per CU: the shrink's four-wave workgroups (units of one row to several blocks of
-64, ranks past one block of 64, a contraction axis with and without a partial stage, fewer stages than waves) and the expand
-kernel's column groups (whole, ragged, a single column past one)."""
+"""Batches of more work units than two workgroups per CU: the shrink's four-wave workgroups, and the eight-wave ones that a short
+contraction axis keeps (units of one row to several blocks of 64, ranks past one block of 64, K with and without a partial
+stage), and the expand kernel's column groups (whole, ragged, a single column past one)."""
 import numpy as np
 import pytest
 
